@@ -101,7 +101,7 @@ double band_reduce_bytes(int64_t n, int nb, size_t cs)
 }
 double narrow_bytes(int64_t n, size_t cs)
 {
-    const int64_t nw = cs == 8 ? 24 : 48;
+    const int64_t nw = cs == 8 ? 16 : 24;
     double cols = 0.0;
     for (int64_t i0 = 0; i0 < n - 2; i0 += nw) cols += (double)(n - i0);
     return cols * 24.0 * 2.0 * (double)cs;

@@ -203,6 +203,59 @@ def test_stage2_on_random_band(dtype, n, nb):
     assert np.abs(s - ref).max() <= 10 * n * eps * ref[0]
 
 
+def _narrow_chase(dense, dtype, nb=8):
+    """svb_gb2bd on an upper band of nb super-diagonals given as a dense matrix; (d, e) in fp64."""
+    n = dense.shape[0]
+    ldab = 3 * nb
+    bh = np.zeros((n, ldab), dtype=workloads.NP_DTYPE[dtype])
+    for j in range(n):
+        for i in range(max(0, j - nb), j + 1):
+            bh[j, i - j + 2 * nb - 1] = dense[i, j]
+    band = torch.from_numpy(bh).cuda()
+    d = torch.zeros(n, dtype=TORCH_DT[dtype], device="cuda")
+    e = torch.zeros(n, dtype=TORCH_DT[dtype], device="cuda")
+    code = svb.SVB_F64 if dtype == "f64" else svb.SVB_F32
+    rc, wb = svb.svb_gb2bd_workspace_bytes(n, nb)
+    work = torch.empty(max(wb, 1), dtype=torch.uint8, device="cuda")
+    print(f"[case] narrow chase n={n} {dtype}", flush=True)
+    assert svb.svb_gb2bd(code, n, nb, band, ldab, d, e, work, wb) == 0
+    torch.cuda.synchronize()
+    return d.cpu().numpy().astype(np.float64), e.cpu().numpy().astype(np.float64)[: n - 1]
+
+
+def _random_band(n, dtype, seed):
+    ii, jj = np.indices((n, n))
+    g = workloads.gaussian_matrix(seed, n, n)
+    return np.where((jj - ii >= 0) & (jj - ii <= 8), g, 0.0).astype(workloads.NP_DTYPE[dtype])
+
+
+@pytest.mark.parametrize("dtype,n,expo", [
+    # one to a few sweeps, a bundle's edges (16 sweeps in f64, 24 in f32; n - 2 sweeps), the ring's first wrap
+    ("f32", 3, 0), ("f32", 4, 0), ("f32", 12, 0), ("f32", 26, 0), ("f32", 27, 0), ("f32", 51, 0), ("f32", 985, 0),
+    ("f64", 4, 0), ("f64", 11, 0), ("f64", 18, 0), ("f64", 19, 0), ("f64", 35, 0), ("f64", 660, 0),
+    # entries whose squares leave the range in which the reflector's scalars are formed directly
+    ("f32", 70, -60), ("f32", 70, 55), ("f64", 70, -500), ("f64", 70, 490)])
+def test_narrow_chase_edges(dtype, n, expo):
+    dense = np.ldexp(_random_band(n, dtype, 9000 + n), expo).astype(workloads.NP_DTYPE[dtype])
+    dh, eh = (np.ldexp(v, -expo) for v in _narrow_chase(dense, dtype))
+    ref64 = np.ldexp(dense.astype(np.float64), -expo)
+    s = np.zeros(n)
+    assert svb.svb_bdsvals(n, dh, eh, s) == 0
+    ref = oracle.svdvals(ref64)
+    assert np.abs(s - ref).max() <= 10 * n * workloads.EPS[dtype] * ref[0]
+
+
+def test_narrow_chase_keeps_a_bidiagonal_exactly():
+    # every pivot has a zero tail: H = I exactly, also across zero rows
+    n = 300
+    for dtype in ("f32", "f64"):
+        dense = np.triu(np.tril(_random_band(n, dtype, 77), 1))
+        dense[40:44] = 0
+        dh, eh = _narrow_chase(dense, dtype)
+        np.testing.assert_array_equal(dh, np.diag(dense).astype(np.float64))
+        np.testing.assert_array_equal(eh, np.diag(dense, 1).astype(np.float64))
+
+
 @pytest.mark.parametrize("name", ["c3a", "c3b", "c4", "c5b", "c5a"])
 def test_full_size_configs_against_stored_oracle(name):
     """Configs 3a/3b/4/5b/5a at full size against the oracle's stored singular values
