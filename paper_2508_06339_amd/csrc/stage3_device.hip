@@ -5,10 +5,16 @@
 // the same bisection that the host entry point svb_bdsvals performs is also
 // available on the GPU).
 //
-// Count of singular values below x: with B^T B - x^2 I = L D L^T,
-//   t_1 = -x^2,  D_j = d_j^2 + t_j,  t_{j+1} = -x^2 + e_j^2 * t_j / D_j,
-// the number of negative D_j (the differential stationary qd form of the Sturm
-// sequence: one division per row, n rows).  Squares are taken after scaling by
+// Count of singular values below x, by the Sturm sequence of the Golub-Kahan tridiagonal (zero
+// diagonal, off-diagonals d_1, e_1, d_2, ..): with r_k = (-1)^k det(T_k - x I),
+//   r_{2j+1} = x r_{2j} - e_{j-1}^2 r_{2j-1},   r_{2j+2} = x r_{2j+1} - d_j^2 r_{2j},
+// the number of sign changes is the number of singular values >= x.  Two fused multiply-adds per row
+// are all that depends on the row before, no division; computed r are those of a matrix whose
+// entries differ by a few units in the last place, so small values keep their relative accuracy.
+// The pair is scaled back to [1/2, 1) every eight rows (a row shrinks it by no more than x^2 and the
+// rounding of a cancellation: every two rows for x below 2^-50); a count in which it fell below
+// 2^-800 in between (exact zeros) is done again with the differential stationary qd recurrence, which
+// forms ratios and needs a reciprocal per row.  Squares are taken after scaling by
 // the largest entry, always in fp64.  A first kernel counts at 4096 shared points of
 // [0, bound]; every singular value then starts from the cell it falls in and is refined by
 // multisection (several points per round, one lane each).
@@ -20,7 +26,8 @@ namespace {
 
 constexpr int kPrepThreads = 1024;
 
-// ws[0] = scale, ws[1] = upper bound for sigma_max / scale; d2 = ws + 8, e2 = d2 + n.
+// ws[0] = scale, ws[1] = upper bound for sigma_max / scale; from ws + 8 on the squares of the scaled
+// entries, row by row: e_{j-1}^2, d_j^2 (e_{-1} = 0).
 template <typename C>
 __global__ __launch_bounds__(kPrepThreads) void bd_prep_kernel(const C* __restrict__ d, const C* __restrict__ e,
                                                                int64_t n, double* __restrict__ ws)
@@ -56,13 +63,12 @@ __global__ __launch_bounds__(kPrepThreads) void bd_prep_kernel(const C* __restri
         ws[0] = (zmax != zmax) ? NAN : scale;
         ws[1] = bound / scale * (1.0 + 1e-14) + 1e-300;
     }
-    double* d2 = ws + 8;
-    double* e2 = d2 + n;
+    double* z = ws + 8;
     for (int64_t j = tid; j < n; j += kPrepThreads) {
         const double a = (double)d[j] / scale;
-        const double b = j + 1 < n ? (double)e[j] / scale : 0.0;
-        d2[j] = a * a;
-        e2[j] = b * b;
+        const double b = j > 0 ? (double)e[j - 1] / scale : 0.0;
+        z[2 * j] = b * b;
+        z[2 * j + 1] = a * a;
     }
 }
 
@@ -76,35 +82,109 @@ __device__ __forceinline__ double lane_value(double v, int lane)
     return __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
-// Number of singular values below x (x2 = x^2, one value per lane) by the recurrence in the
-// header.  All 64 lanes of the wave walk the same rows, so the rows are fetched 64 at a time,
-// one per lane, and handed round as wave-uniform scalars: no memory access sits on the
-// dependent chain of the recurrence.  Rows past n are padded so that they never count.
-__device__ __forceinline__ int64_t sturm_count(const double* __restrict__ d2, const double* __restrict__ e2,
-                                               int64_t n, double x2)
+// Number of singular values below x by the qd recurrence
+//   t_1 = -x^2,  D_j = d_j^2 + t_j,  t_{j+1} = -x^2 + e_j^2 * t_j / D_j   (the number of negative D_j).
+// All 64 lanes of the wave walk the same rows, so the rows are fetched 64 at a time, one per lane,
+// and handed round as wave-uniform scalars.  Rows past n are padded so that they never count.
+__device__ __attribute__((noinline)) int64_t qd_count(const double* __restrict__ z, int64_t n, double x)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const double pivmin = 1e-300;
-    double t = -x2;
+    const double pivmin = 1e-300, x2 = x * x;
+    double s = 0.0;      // t_j / D_j of the row before
     int64_t cnt = 0;
-    double dn = lane < n ? d2[lane] : 1e300, en = lane < n ? e2[lane] : 0.0;
     for (int64_t j0 = 0; j0 < n; j0 += kWave) {
-        const double dj = dn, ej = en;
-        const int64_t jn = j0 + kWave + lane;
-        dn = jn < n ? d2[jn] : 1e300;
-        en = jn < n ? e2[jn] : 0.0;
-#pragma unroll
+        const bool in = j0 + lane < n;
+        const double ej = in ? z[2 * (j0 + lane)] : 0.0, dj = in ? z[2 * (j0 + lane) + 1] : 1e300;
+#pragma unroll 8
         for (int jj = 0; jj < kWave; ++jj) {
             const double dd = lane_value(dj, jj), ee = lane_value(ej, jj);
+            const double t = ee * s - x2;
             double D = dd + t;
             if (fabs(D) < pivmin) D = -pivmin;
             cnt += D < 0.0 ? 1 : 0;
             double r = __builtin_amdgcn_rcp(D);      // reciprocal + one Newton step instead of a full division
             r = fma(r, fma(-D, r, 1.0), r);
-            t = ee * (t * r) - x2;
+            s = t * r;
         }
     }
     return cnt;
+}
+
+// Number of singular values below x (one x > 0 per lane, every lane of the wave active) by the
+// recurrence in the header.  The rows are the same for every lane: they come in as scalars, a
+// block of eight ahead.  What bounds it is the issue of its instructions (per row two products,
+// two fused multiply-adds, two shifts that collect the signs, and the rescaling: about 7, of 5
+// cycles each from a lone wave; the dependent chain is 16 cycles a row): 50 cycles a row measured
+// against 92 for the qd form above; the whole stage at n = 8192: 7.02 -> 3.37 ms (f64), 4.04 -> 1.81
+// (f32), at n = 32768: 50 -> 23 and 27 -> 12.
+template <int EVERY>
+__device__ __forceinline__ int64_t sequence_count(const double* __restrict__ z, int64_t n, double x)
+{
+    constexpr int R = 8;
+    double h = 0.0, b = 1.0;          // r_{2j-1}, r_{2j}
+    unsigned signs = 0;               // of the last 32 members of the sequence, the latest in bit 0
+    int changes = 0;
+    double low = 1.0;                 // smallest size the pair had before a rescaling
+    auto row = [&](double ee, double dd) {
+        const double nh = fma(x, b, -(ee * h));
+        const double nb = fma(x, nh, -(dd * b));
+        signs = __builtin_amdgcn_alignbit(signs, (unsigned)(__builtin_bit_cast(unsigned long long, nh) >> 32), 31);
+        signs = __builtin_amdgcn_alignbit(signs, (unsigned)(__builtin_bit_cast(unsigned long long, nb) >> 32), 31);
+        h = nh;
+        b = nb;
+    };
+    auto rescale = [&]() {
+        const double m = fmax(fabs(h), fabs(b));
+        low = fmin(low, m);
+        const int e = -__builtin_amdgcn_frexp_exp(m);
+        h = __builtin_amdgcn_ldexp(h, e);
+        b = __builtin_amdgcn_ldexp(b, e);
+    };
+    // Two blocks of rows in scalar registers: one is on its way while the other is worked on.  Left to
+    // itself the compiler moves the loads to where their values are used, and every block waits for
+    // them: the fence keeps them in front of the rows, the empty statement takes delivery behind them.
+    const int nblk = (int)(n / R);
+    double za[2 * R], zb[2 * R];
+    auto fetch = [&](double (&q)[2 * R], int k) {
+        const double* __restrict__ p = z + (int64_t)(k < nblk ? k : 0) * (2 * R);
+#pragma unroll
+        for (int i = 0; i < 2 * R; ++i) q[i] = p[i];
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto block = [&](const double (&q)[2 * R]) {
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            row(q[2 * i], q[2 * i + 1]);
+            if ((i + 1) % EVERY == 0) rescale();
+        }
+        changes += __builtin_popcount((signs ^ (signs >> 1)) & 0xffffu);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto arrived = [&](double (&q)[2 * R]) {
+#pragma unroll
+        for (int i = 0; i < 2 * R; ++i) asm volatile("" : "+s"(q[i]));
+    };
+    if (nblk > 0) fetch(za, 0);
+    for (int k = 0; k < nblk; k += 2) {
+        arrived(za);
+        fetch(zb, k + 1);
+        block(za);
+        if (k + 1 == nblk) break;
+        arrived(zb);
+        fetch(za, k + 2);
+        block(zb);
+    }
+    for (int64_t j = (int64_t)nblk * R; j < n; ++j) {
+        row(z[2 * j], z[2 * j + 1]);
+        changes += __builtin_popcount((signs ^ (signs >> 1)) & 3u);
+        rescale();
+    }
+    if (__any(low < 0x1p-800)) return qd_count(z, n, x);
+    return n - changes;
+}
+__device__ __forceinline__ int64_t sturm_count(const double* __restrict__ z, int64_t n, double x)
+{
+    return __any(x < 0x1p-50) ? sequence_count<2>(z, n, x) : sequence_count<8>(z, n, x);
 }
 
 // counts at the points x_i = bound * i / kGrid, i = 1 .. kGrid - 1 (x_0 counts 0, x_kGrid counts n)
@@ -112,12 +192,11 @@ __global__ __launch_bounds__(64) void bd_grid_kernel(const double* __restrict__ 
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;   // 0 .. kGrid-1, all lanes stay active
     const double scale = ws[0], hi0 = ws[1];
-    const double* __restrict__ d2 = ws + 8;
-    const double* __restrict__ e2 = d2 + n;
+    const double* __restrict__ z = ws + 8;
     int64_t c = 0;
     if (scale == scale) {
         const double x = hi0 * ((double)i / kGrid);
-        c = sturm_count(d2, e2, n, x * x);
+        c = sturm_count(z, n, x);
     }
     gcnt[i] = i == 0 ? 0 : (int)min(c, n);
     if (i == 0) gcnt[kGrid] = (int)n;
@@ -138,8 +217,7 @@ __global__ __launch_bounds__(64) void bd_multisect_kernel(const double* __restri
     const int64_t kraw = (int64_t)blockIdx.x * VPW + grp;  // ascending index
     const int64_t k = min(kraw, n - 1);   // surplus lanes repeat the last value: the wave stays whole
     const double scale = ws[0], hi0 = ws[1];
-    const double* __restrict__ d2 = ws + 8;
-    const double* __restrict__ e2 = d2 + n;
+    const double* __restrict__ z = ws + 8;
     if (scale != scale) {  // non-finite input: poison the output, the caller maps it to a status
         if (kraw < n && q == 0) sigma[n - 1 - k] = (C)NAN;
         return;
@@ -164,7 +242,7 @@ __global__ __launch_bounds__(64) void bd_multisect_kernel(const double* __restri
         if (!__any(open)) break;            // wave-uniform exit: the row hand-over needs every lane
         // this lane's point; rounding may put it on an end of the interval, where the count is known
         const double x = fmin(fmax(fma(w, frac, lo), lo), hi);
-        const int64_t cnt = sturm_count(d2, e2, n, x * x);
+        const int64_t cnt = sturm_count(z, n, x);
         const bool above = x >= hi || (x > lo && cnt >= k + 1);   // the value lies below this point
         // the points of a value are ascending, so its lanes read: below .. below, above .. above
         const unsigned long long m = __ballot(above) >> (grp * P);
@@ -183,7 +261,7 @@ __global__ __launch_bounds__(64) void bd_multisect_kernel(const double* __restri
 
 }  // namespace
 
-// doubles: scale, bound, 6 spare, d^2, e^2; then the counts at the partition points
+// doubles: scale, bound, 6 spare, the squares (two a row); then the counts at the partition points
 size_t bdsvals_dev_workspace_bytes(int64_t n) { return (size_t)(8 + 2 * n) * sizeof(double) + (size_t)(kGrid + 8) * sizeof(int); }
 
 template <typename C>

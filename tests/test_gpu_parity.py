@@ -385,6 +385,40 @@ def test_stage3_device_closed_form_and_oracle(dtype, n):
         assert np.all(np.isnan(run(bad, eh)))
 
 
+@pytest.mark.parametrize("kind,n", [("random", 1), ("random", 7), ("random", 8), ("random", 9), ("random", 16),
+                                    ("random", 17), ("random", 71), ("equal", 64), ("split", 200), ("graded", 120),
+                                    ("singular", 90)])
+def test_stage3_device_sequence_edges(kind, n):
+    # the Sturm sequence runs in blocks of eight rows (remainders, the odd block), and a count whose
+    # scaled pair underflows is redone with the quotient form: equal diagonals without coupling (the
+    # sequence is exactly zero at the value), blocks without or with tiny couplings, entries falling
+    # by 2^-8 a row (values far below the largest one, to their own relative accuracy), zero diagonals
+    dh = 1.0 + workloads.uniform01(501 + n, 0, n)
+    eh = workloads.uniform01(502 + n, 0, n)[: n - 1]
+    if kind == "equal":
+        dh[:], eh[:] = 1.0, 0.0
+    elif kind == "split":
+        eh[::5], eh[1::7] = 0.0, 2.0 ** -200
+    elif kind == "graded":
+        dh, eh = np.ldexp(dh, -8 * np.arange(n)), np.ldexp(eh, -8 * np.arange(n - 1))
+    elif kind == "singular":
+        dh[::9] = 0.0
+    d = torch.from_numpy(dh).cuda()
+    e = torch.from_numpy(np.concatenate([eh, [0.0]])).cuda()
+    sig = torch.zeros(n, dtype=torch.float64, device="cuda")
+    rc, wb = svb.svb_bdsvals_dev_workspace_bytes(n)
+    work = torch.empty(wb, dtype=torch.uint8, device="cuda")
+    assert svb.svb_bdsvals_dev(svb.SVB_F64, n, d, e, sig, 0.0, work, wb) == 0
+    s = sig.cpu().numpy()
+    ref = oracle.bdsvals(dh, eh)
+    assert np.all(np.diff(s) <= 0)
+    assert np.abs(s - ref).max() <= 64 * 2.0 ** -52 * ref[0]
+    if kind == "graded":
+        # 2 n entries perturbed by a few units in the last place, and the width at which an interval
+        # counts as closed in any case (1e-38 times a bound on the largest value of at most 2 ref[0])
+        assert np.all(np.abs(s - ref) <= 4 * n * 2.0 ** -52 * ref + 2e-38 * ref[0])
+
+
 @pytest.mark.parametrize("points", [1, 2, 4, 8, 16])
 def test_stage3_device_points_per_value(monkeypatch, points):
     # every multisection width against the oracle's bidiagonal solver, f64 and f32, a size that
