@@ -1,0 +1,64 @@
+// Lane-to-lane operations that stay in the vector registers (gfx950): broadcasts inside rows of 16
+// lanes (data-parallel primitives) and swaps of lane groups.  A value fetched this way costs an
+// instruction or two (5 cycles each) against 50 for a trip through LDS and 70 for a shuffle.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace svb {
+
+// value of lane K (lanes 0 .. 7 of a row of 16) or 8 + K (lanes 8 .. 15)
+template <int K> __device__ __forceinline__ int half_row_lane(int v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, v, 0x150 + K, 0xF, 0xF, true);
+    return __builtin_amdgcn_update_dpp(lo, v, 0x150 + 8 + K, 0xF, 0xC, false);
+}
+// value of lane K of this lane's row of 16
+template <int K> __device__ __forceinline__ int row_lane(int v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, 0x150 + K, 0xF, 0xF, true);
+}
+// sum of the two rows of 16 of each half of the wave / of the two halves, in all of them (the two
+// operands of a swap are the same register: it leaves the value and its partner's)
+__device__ __forceinline__ float rows_sum(float v)
+{
+    const unsigned u = __builtin_bit_cast(unsigned, v);
+    const auto t = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    const unsigned t0 = t[0], t1 = t[1];   // (a bit cast of t[1] itself would read t[0])
+    const unsigned q = __builtin_bit_cast(unsigned, __builtin_bit_cast(float, t0) + __builtin_bit_cast(float, t1));
+    const auto h = __builtin_amdgcn_permlane32_swap(q, q, false, false);
+    const unsigned h0 = h[0], h1 = h[1];
+    return __builtin_bit_cast(float, h0) + __builtin_bit_cast(float, h1);
+}
+struct Words { unsigned lo, hi; };
+__device__ __forceinline__ double rows_sum(double v)
+{
+    const Words u = __builtin_bit_cast(Words, v);
+    const auto a = __builtin_amdgcn_permlane16_swap(u.lo, u.lo, false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(u.hi, u.hi, false, false);
+    const double w = __builtin_bit_cast(double, Words{a[0], b[0]}) + __builtin_bit_cast(double, Words{a[1], b[1]});
+    const Words q = __builtin_bit_cast(Words, w);
+    const auto c = __builtin_amdgcn_permlane32_swap(q.lo, q.lo, false, false);
+    const auto d = __builtin_amdgcn_permlane32_swap(q.hi, q.hi, false, false);
+    return __builtin_bit_cast(double, Words{c[0], d[0]}) + __builtin_bit_cast(double, Words{c[1], d[1]});
+}
+template <int K> __device__ __forceinline__ float half_row_lane(float v)
+{
+    return __builtin_bit_cast(float, half_row_lane<K>(__builtin_bit_cast(int, v)));
+}
+template <int K> __device__ __forceinline__ double half_row_lane(double v)
+{
+    const Words u = __builtin_bit_cast(Words, v);
+    return __builtin_bit_cast(double, Words{(unsigned)half_row_lane<K>((int)u.lo), (unsigned)half_row_lane<K>((int)u.hi)});
+}
+template <int K> __device__ __forceinline__ float row_lane(float v)
+{
+    return __builtin_bit_cast(float, row_lane<K>(__builtin_bit_cast(int, v)));
+}
+template <int K> __device__ __forceinline__ double row_lane(double v)
+{
+    const Words u = __builtin_bit_cast(Words, v);
+    return __builtin_bit_cast(double, Words{(unsigned)row_lane<K>((int)u.lo), (unsigned)row_lane<K>((int)u.hi)});
+}
+
+}  // namespace svb

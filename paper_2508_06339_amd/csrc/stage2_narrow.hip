@@ -25,6 +25,7 @@
 #include <type_traits>
 
 #include "svb_internal.h"
+#include "lane_ops.h"
 
 namespace svb {
 
@@ -56,18 +57,6 @@ __device__ __forceinline__ void lds_set(int* p, int v)
 // operations of one wave in order, so a counter written after the data is seen after the data.
 __device__ __forceinline__ void order_lds() { asm volatile("" ::: "memory"); }
 
-// value of lane L of this lane's row of 16 (data-parallel primitive, no LDS traffic)
-template <int L> __device__ __forceinline__ float row_lane(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x150 + L, 0xF, 0xF, true));
-}
-template <int L> __device__ __forceinline__ double row_lane(double v)
-{
-    const long long b = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), 0x150 + L, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x150 + L, 0xF, 0xF, true);
-    return __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
-}
 // the pivot (p_0 .. p_7) from lanes 8 .. 15 of the row
 template <typename C> __device__ __forceinline__ void row_pivot(C x, C (&p)[8])
 {

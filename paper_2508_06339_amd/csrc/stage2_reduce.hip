@@ -29,6 +29,7 @@
 //
 // Packed band: entry (i,j) at band[(i - j + ku) + j*ldab], ku = 2B-1, ldab >= 3B.
 #include "svb_internal.h"
+#include "lane_ops.h"
 #include "mfma_frag.h"
 
 namespace svb {
@@ -81,7 +82,6 @@ template <int CTRL> __device__ __forceinline__ double dpp_get(double v)
 constexpr int kDppXor1 = 0xB1;        // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;        // quad_perm [2,3,0,1]
 constexpr int kDppHalfMirror = 0x141; // lane i <-> 7-i inside groups of 8
-constexpr int kDppMirror = 0x140;     // lane i <-> 15-i inside rows of 16
 
 // sum over the four lanes of a quad, result in all four
 template <typename C> __device__ __forceinline__ C quad_allsum(C v)
@@ -90,49 +90,7 @@ template <typename C> __device__ __forceinline__ C quad_allsum(C v)
     v += dpp_get<kDppXor2>(v);
     return v;
 }
-// value of one lane as a wave-uniform scalar
-__device__ __forceinline__ float lane_value(float v, int lane)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
-}
-__device__ __forceinline__ double lane_value(double v, int lane)
-{
-    const long long b = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lane);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-    return __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
-}
 constexpr int kDppRor8 = 0x128;       // lane i <-> i^8 inside rows of 16 (rotate by 8)
-
-// Sums of eight per-lane values over the 64 lanes of a wave, as wave-uniform scalars.
-// The first three stages halve the number of values while doubling the lanes summed
-// (each lane keeps the half selected by one of its index bits and hands the other half to
-// its partner: partners i^7 with bit 2, i^1 with bit 0, i^2 with bit 1), so that after them
-// lane i holds, summed over its group of eight lanes, the value with index
-// 4*bit1(i) + 2*bit0(i) + bit2(i); two more stages sum over the row of 16 and over the four rows.
-template <typename C> __device__ __forceinline__ void wave_sum8(const C (&a)[8], C (&out)[8])
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
-    C b[4], c[2];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const C keep = b2 ? a[2 * j + 1] : a[2 * j], send = b2 ? a[2 * j] : a[2 * j + 1];
-        b[j] = keep + dpp_get<kDppHalfMirror>(send);
-    }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const C keep = b0 ? b[2 * j + 1] : b[2 * j], send = b0 ? b[2 * j] : b[2 * j + 1];
-        c[j] = keep + dpp_get<kDppXor1>(send);
-    }
-    const C keep = b1 ? c[1] : c[0], send = b1 ? c[0] : c[1];
-    C v = keep + dpp_get<kDppXor2>(send);
-    v += dpp_get<kDppRor8>(v);
-    v += __shfl_xor(v, 16, kWave);
-    v += __shfl_xor(v, 32, kWave);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) out[i] = lane_value(v, ((i >> 1) & 1) + 2 * ((i >> 2) & 1) + 4 * (i & 1));
-}
 
 __device__ __forceinline__ float rrcp(float x)
 {
@@ -171,19 +129,159 @@ template <int D> __device__ __forceinline__ void load_v(const double* v, double 
     }
 }
 
+// One reflector (number K) of the panel factorisation below.  This lane holds elements 8 i + sg,
+// i < QN, of line ln.
+template <typename C, int QN, int D, int K>
+__device__ __forceinline__ void panel_reflector(C (&x)[QN], C (&trow)[D], C& my_inv, C& my_beta, int ln, int sg)
+{
+    // the pivot line's elements of this lane's segment, its tail (elements beyond K) only
+    C pv[QN];
+    // the line's product with the tail and its element K, summed over the eight segments
+    C da = 0, db = 0;
+#pragma unroll
+    for (int i = 0; i < QN; ++i) {
+        pv[i] = half_row_lane<K>(x[i]);
+        if (i == 0) pv[i] = sg > K ? pv[i] : (C)0;
+        if (i & 1) db = fma(pv[i], x[i], db);
+        else da = fma(pv[i], x[i], da);
+    }
+    C d = da + db, a = sg == K ? x[0] : (C)0;
+    d += dpp_get<kDppRor8>(d);
+    a += dpp_get<kDppRor8>(a);
+    d = rows_sum(d);
+    a = rows_sum(a);
+    const C alpha = row_lane<K>(a), ss = row_lane<K>(d);
+    const C nrm = newton_sqrt(fma(alpha, alpha, ss));
+    C beta = copysign(nrm, -alpha);
+    const C den = alpha - beta;
+    C inv = rrcp(den), tau = -den * rrcp(beta);
+    // (a tail whose sum of squares is zero or below the normal range: H = I, the tail is dropped)
+    const bool ident = ss < (sizeof(C) == 8 ? (C)0x1p-1022 : (C)0x1p-126f);
+    beta = ident ? alpha : beta;
+    inv = ident ? (C)0 : inv;
+    tau = ident ? (C)0 : tau;
+    // v_K^T line, v_K = (1, inv * tail); lines before K hold their tails unscaled
+    const C c = fma(inv, d, a) * my_inv;
+    // T(0:K, K) = -tau T(0:K, 0:K) (V^T v_K), T(K, K) = tau; this lane builds row ln
+    {
+        C acc = 0;
+        if constexpr (K > 0) acc = fma(trow[0], row_lane<0>(c), acc);
+        if constexpr (K > 1) acc = fma(trow[1], row_lane<1>(c), acc);
+        if constexpr (K > 2) acc = fma(trow[2], row_lane<2>(c), acc);
+        if constexpr (K > 3) acc = fma(trow[3], row_lane<3>(c), acc);
+        if constexpr (K > 4) acc = fma(trow[4], row_lane<4>(c), acc);
+        if constexpr (K > 5) acc = fma(trow[5], row_lane<5>(c), acc);
+        if constexpr (K > 6) acc = fma(trow[6], row_lane<6>(c), acc);
+        trow[K] = ln == K ? tau : (ln < K ? -tau * acc : (C)0);
+    }
+    const C sj = ln > K ? tau * c : (C)0, w = sj * inv;
+#pragma unroll
+    for (int i = 0; i < QN; ++i) x[i] = fma(-w, pv[i], x[i]);
+    x[0] -= sg == K ? sj : (C)0;
+    my_inv = ln == K ? inv : my_inv;
+    my_beta = ln == K ? beta : my_beta;
+}
+
 // Householder factorisation of a D x B panel held in LDS, by one wave: panel element (k, e),
 // k < D along the short and e < B along the long direction, lives at P[k*sk + e*se].
 // Reflector k is built from line k, elements k .. B-1, and applied to lines k+1 .. D-1
 // (H = I - tau v v^T, v_k = 1, beta = -sign(alpha)*norm).  On exit the panel holds the
 // triangular factor (element (k,e) for e <= k, zeros beyond), Vs the vectors
 // (Vs[vidx(e) + k]) and Ts the D x D upper triangular T of the compact-WY form
-// H_0 H_1 .. H_{D-1} = I - V T V^T, row-major.  One D-vector reduction over the wave per
-// reflector yields its norm, the products with the lines below and the products v_j^T v_k
-// that T needs; the sums are wave-uniform scalars.  D = 8.
-// With G the panel lies in the packed band in device memory (device-scope accesses, elements
-// e >= ne outside the matrix: read as zero, not written).
-template <typename C, int B, int D, bool G = false>
-__device__ __forceinline__ void panel_wave(C* P, int64_t sk, int64_t se, C* Vs, C* Ts, int ne = B)
+// H_0 H_1 .. H_{D-1} = I - V T V^T, row-major.  D = 8.
+// The panels are the longest part of a step and one dependent chain; what they cost is instructions
+// (5 cycles each from a lone wave) and latencies (8 cycles a dependent one, 70 a shuffle through LDS,
+// 55 a branch on a vector comparison).  So: eight lanes per line, each with every eighth element; the
+// pivot line comes to the others through row broadcasts, and the sums over a line take one rotation
+// and two lane-group swaps; no branch, no shuffle, no scalar register on the way.  (The form before:
+// a lane per element with all eight lines, eight sums over the wave and sixteen lane reads per
+// reflector.)  Per panel, before -> now: f32 3.6 -> 1.65 us (nb = 32), 2.2 (64),
+// 2.5 (128), f64 5.2 -> 2.4 (32), 3.2 (64); the whole reduction at n = 8192: 27.6 -> 21.0 ms (f32, nb = 64).
+template <typename C, int B, int D>
+__device__ __forceinline__ void panel_wave(C* P, int sk, int se, C* Vs, C* Ts)
+{
+    static_assert(D == 8, "eight lines, one per lane of a group of eight");
+    constexpr int QN = B / 8;
+    const int lane = threadIdx.x & (kWave - 1), ln = lane & 7, sg = lane >> 3;
+    C x[QN];
+#pragma unroll
+    for (int i = 0; i < QN; ++i) x[i] = P[ln * sk + (8 * i + sg) * se];
+    C trow[D], my_inv = 1, my_beta = 0;
+    panel_reflector<C, QN, D, 0>(x, trow, my_inv, my_beta, ln, sg);
+    panel_reflector<C, QN, D, 1>(x, trow, my_inv, my_beta, ln, sg);
+    panel_reflector<C, QN, D, 2>(x, trow, my_inv, my_beta, ln, sg);
+    panel_reflector<C, QN, D, 3>(x, trow, my_inv, my_beta, ln, sg);
+    panel_reflector<C, QN, D, 4>(x, trow, my_inv, my_beta, ln, sg);
+    panel_reflector<C, QN, D, 5>(x, trow, my_inv, my_beta, ln, sg);
+    panel_reflector<C, QN, D, 6>(x, trow, my_inv, my_beta, ln, sg);
+    panel_reflector<C, QN, D, 7>(x, trow, my_inv, my_beta, ln, sg);
+    // factor back into the panel, vectors to Vs
+#pragma unroll
+    for (int i = 0; i < QN; ++i) {
+        const int e = 8 * i + sg;
+        C f = 0, v = x[i] * my_inv;
+        if (i == 0) {
+            f = sg < ln ? x[0] : (sg == ln ? my_beta : (C)0);
+            v = sg < ln ? (C)0 : (sg == ln ? (C)1 : v);
+        }
+        P[ln * sk + e * se] = f;
+        Vs[vidx<B, D>(e) + ln] = v;
+    }
+    if (lane < D) {
+#pragma unroll
+        for (int k = 0; k < D; ++k) Ts[ln * D + k] = trow[k];
+    }
+}
+
+// The same factorisation with a lane per element (every 64th of all eight lines): eight sums over the
+// wave per reflector.  Kept for the in-band form of the kernel (two blocks do not fit in LDS: f64 at
+// B = 128), whose 128 registers a lane the form above does not fit beside the lines: 16.9 against
+// 15.4 us a column for the whole reduction.
+// value of one lane as a wave-uniform scalar
+__device__ __forceinline__ float lane_value(float v, int lane)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+__device__ __forceinline__ double lane_value(double v, int lane)
+{
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), lane);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
+// Sums of eight per-lane values over the 64 lanes of a wave, as wave-uniform scalars.
+// The first three stages halve the number of values while doubling the lanes summed
+// (each lane keeps the half selected by one of its index bits and hands the other half to
+// its partner: partners i^7 with bit 2, i^1 with bit 0, i^2 with bit 1), so that after them
+// lane i holds, summed over its group of eight lanes, the value with index
+// 4*bit1(i) + 2*bit0(i) + bit2(i); two more stages sum over the row of 16 and over the four rows.
+template <typename C> __device__ __forceinline__ void wave_sum8(const C (&a)[8], C (&out)[8])
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4;
+    C b[4], c[2];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const C keep = b2 ? a[2 * j + 1] : a[2 * j], send = b2 ? a[2 * j] : a[2 * j + 1];
+        b[j] = keep + dpp_get<kDppHalfMirror>(send);
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const C keep = b0 ? b[2 * j + 1] : b[2 * j], send = b0 ? b[2 * j] : b[2 * j + 1];
+        c[j] = keep + dpp_get<kDppXor1>(send);
+    }
+    const C keep = b1 ? c[1] : c[0], send = b1 ? c[0] : c[1];
+    C v = keep + dpp_get<kDppXor2>(send);
+    v += dpp_get<kDppRor8>(v);
+    v += __shfl_xor(v, 16, kWave);
+    v += __shfl_xor(v, 32, kWave);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) out[i] = lane_value(v, ((i >> 1) & 1) + 2 * ((i >> 2) & 1) + 4 * (i & 1));
+}
+
+template <typename C, int B, int D, bool G>
+__device__ __forceinline__ void panel_wave_spread(C* P, int64_t sk, int64_t se, C* Vs, C* Ts, int ne)
 {
     constexpr int QN = (B + kWave - 1) / kWave;
     const int lane = threadIdx.x & (kWave - 1);
@@ -618,7 +716,7 @@ __global__ __launch_bounds__(ReduceShape<B>::NT) void band_reduce_kernel(C* __re
             const int ncol = (int)min((int64_t)B, n - c0);                            // columns c0 .. inside the matrix
             const int64_t rho = (t == 0) ? c00 - D : c0 - B;                          // first row of X
             if (pw) {
-                if (UG) panel_wave<C, B, D, true>(band + (rho - c0 + ku) + c0 * ldab, 1, ldm1, Vs, Ts, ncol);
+                if constexpr (UG) panel_wave_spread<C, B, D, true>(band + (rho - c0 + ku) + c0 * ldab, 1, ldm1, Vs, Ts, ncol);
                 else panel_wave<C, B, D>(S + xoff, 1, LD, Vs, Ts);
             } else if (UG && traffic && t > 0) {
                 // this step's Z is requested here (its registers would otherwise be live across the
@@ -697,7 +795,8 @@ __global__ __launch_bounds__(ReduceShape<B>::NT) void band_reduce_kernel(C* __re
             // ---- S4: left panel (QR of Z's first D columns)  ||  A3 requested, U back, A3 in
             const int seen2 = UG ? poll(s) : 0;
             if (pw) {
-                panel_wave<C, B, D>(S + ZO, LD, 1, Vs, Ts);
+                if constexpr (UG) panel_wave_spread<C, B, D, false>(S + ZO, LD, 1, Vs, Ts, B);
+                else panel_wave<C, B, D>(S + ZO, LD, 1, Vs, Ts);
             } else if (!UG && traffic) {
                 const Blk ub = block_at(c0 - B, c0), a3 = block_at(c0, c0 + B);
 #pragma unroll
