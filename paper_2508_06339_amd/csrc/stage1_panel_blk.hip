@@ -7,7 +7,7 @@
 // holds columns 16w .. 16w+15.  The columns are factored 16 at a time:
 //   1. the owning wave hands its 16 columns to LDS;
 //   2. all threads factor that 16-column block with Householder reflectors
-//      (Algorithm 3's loop, the column split over row groups, two barriers per
+//      (Algorithm 3's loop, the column split over row groups, one barrier per
 //      reflector) -- the only part that works reflector by reflector;
 //   3. the block's reflectors are applied to the columns right of it as ONE
 //      block reflector on MFMA:  C_w -= V_b (T_b^T (V_b^T C_w));
@@ -20,7 +20,10 @@
 // Reflector convention: H = I - tau v v^T, v_k = 1, beta = -sign(alpha)*norm,
 // tau = (beta - alpha)/beta (Algorithm 3's 2x^2/(x^2+|tail|^2)); a zero tail
 // gives tau = 0 instead of the paper's 10*eps rule.
+#include <utility>
+
 #include "svb_internal.h"
+#include "lane_ops.h"
 #include "mfma_frag.h"
 #include <hip/hip_ext.h>
 
@@ -41,12 +44,9 @@ template <typename C, int NB, int HT> struct PanelBlkGeom {
     static constexpr int oBs = 0;
     static constexpr int oTs = oBs + 16 * LDB;           // T, block (bi, bj) row-major at blk(bi, bj) * 16 * LDT
     static constexpr int oZs = oTs + NBLK * 16 * LDT;    // Z = (V_w^T V_b) T_b, [column][row]
-    static constexpr int oXs = oZs + 16 * LDZ;           // pivot column, two buffers
-    static constexpr int XST = RPT + 4;                  // a row group's slot in the pivot-column buffer
-    static constexpr int XSB = 4 * NW * XST;             // one buffer (padded: the four groups of a wave on different banks)
-    static constexpr int oPart = oXs + 2 * XSB;          // partial inner products, [wave][column]
-    static constexpr int oRowk = oPart + NW * 16;        // pivot row, two buffers
-    static constexpr int oGs = oRowk + 2 * 16;           // v_c^T v_k inside the block, [k][c]
+    static constexpr int oPart = oZs + 16 * LDZ;         // partial inner products, two buffers of [wave][lane]
+    static constexpr int oRowk = oPart + 2 * NW * 64;    // pivot row (four copies), two buffers
+    static constexpr int oGs = oRowk + 2 * 64;           // v_c^T v_k inside the block, [k][c]
     static constexpr int oRs = oGs + 16 * 16;            // R block, [column][row]
     static constexpr int oTb = oRs + 16 * LDT;           // T_b, [column][row]
     static constexpr int oTau = oTb + 16 * LDT;
@@ -80,19 +80,18 @@ template <typename C, int N> __device__ __forceinline__ void lds_stn(C* p, const
     }
 }
 
-// value of lane (l ^ 1) / (l ^ 2) inside quads of four lanes
-template <int CTRL> __device__ __forceinline__ float quad_get(float v)
+// workgroup barrier that orders LDS traffic only (s_waitcnt lgkmcnt(0)): global accesses stay in flight
+__device__ __forceinline__ void lds_barrier()
 {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __builtin_amdgcn_s_barrier();
 }
-template <int CTRL> __device__ __forceinline__ double quad_get(double v)
+
+// f(0), f(1), .. with the index as a compile-time constant
+template <typename Fn, int... K> __device__ __forceinline__ void static_steps(Fn&& f, std::integer_sequence<int, K...>)
 {
-    const long long b = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, true);
-    return __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
+    (f(std::integral_constant<int, K>{}), ...);
 }
-constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E;   // quad_perm [1,0,3,2] and [2,3,0,1]
 
 __device__ __forceinline__ int tblk(int bi, int bj) { return bj * (bj + 1) / 2 + bi; }
 
@@ -177,14 +176,13 @@ __device__ __forceinline__ void panel_blk_body(C* __restrict__ P, int64_t ldp,
     using F = Frag<C>;
     using G = PanelBlkGeom<C, NB, HT>;
     typedef typename F::acc_t acc_t;
-    constexpr int NW = G::NW, NT = G::NT, H = G::H, RPT = G::RPT, NRGU = G::NRGU, XST = G::XST, XSB = G::XSB;
+    constexpr int NW = G::NW, NT = G::NT, H = G::H, RPT = G::RPT, NRGU = G::NRGU;
     constexpr int LDB = G::LDB, LDT = G::LDT, LDZ = G::LDZ;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     C* sm = reinterpret_cast<C*>(smem_raw);
     C* Bs = sm + G::oBs;
     C* Ts = sm + G::oTs;
     C* Zs = sm + G::oZs;
-    C* xs = sm + G::oXs;
     C* part = sm + G::oPart;
     C* rowk = sm + G::oRowk;
     C* Gs = sm + G::oGs;
@@ -199,9 +197,9 @@ __device__ __forceinline__ void panel_blk_body(C* __restrict__ P, int64_t ldp,
     C* Rd = Pnext + (int64_t)d * NB;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i = lane & 15, gq = lane >> 4;      // MFMA fragment coordinates
-    // step 2: column of the block and row group; the four row groups of a wave sit in one quad
-    // of lanes, so their partial sums meet through DPP
-    const int pc = lane >> 2, prg = 4 * wave + (lane & 3);
+    // step 2: column of the block and row group; a row group's sixteen columns sit in one row of
+    // sixteen lanes, so the pivot column reaches the others through row broadcasts
+    const int pc = i, prg = 4 * wave + gq;
     const int64_t mycol = 16 * wave + i;
 
 #ifdef SVB_PANEL_TIMING
@@ -282,65 +280,64 @@ __device__ __forceinline__ void panel_blk_body(C* __restrict__ P, int64_t ldp,
 #pragma unroll
             for (int r = 0; r < RPT; ++r) a[r] = 0;
         }
-        C my_inv = 0;
+        // A reflector: the pivot column comes from the lane that holds it by row broadcasts (no LDS, no
+        // barrier), its products with the columns are summed over the wave's four row groups by two swaps
+        // of lane groups and over the waves through LDS, behind the one barrier.  Nothing branches (a
+        // branch on a vector comparison costs over 50 cycles, a plain instruction 5).  What is left is the
+        // issue of about 3 RPT instructions plus 80.  The form before it (pivot column written to and read
+        // from LDS, two barriers, a branch on the column) took 2100 cycles a reflector at NB = 64 in f32.
+        // Panel launches, before -> now: f32 n = 8192 102 -> 78 us on average (stage 1 52.4 -> 46.7 ms),
+        // f64 n = 4096 114 -> 83 (25.4 -> 21.9), f32 n = 32768 at NB = 128 248 -> 215 ms in all.
+        constexpr bool kKeep = NB < 128;   // with eight waves (256 registers a lane) the column is fetched twice instead of kept
+        C my_inv = 0, my_tau = 0;
+        const bool top = prg == 0;   // the row group that holds the block's own sixteen rows
         PT_MARK(2);
+        static_steps([&](auto kc) {
+            constexpr int ki = decltype(kc)::value, buf = ki & 1;
+            if (wave == 0) rowk[buf * 64 + lane] = a[ki];   // (the first sixteen are the pivot row)
+            C x[kKeep ? RPT : 1];
+            C p4[4] = {0, 0, 0, 0};
 #pragma unroll
-        for (int ki = 0; ki < 16; ++ki) {
-            const int buf = ki & 1;
-            if (prg == 0) rowk[buf * 16 + pc] = a[ki];
-            if (pc == ki && rows_on) {
-                C o[RPT];
+            for (int r = 0; r < RPT; ++r) {
+                C q = row_lane<ki>(a[r]);
+                if (r <= ki) q = top ? (C)0 : q;            // the tail only
+                if (kKeep) x[r] = q;
+                p4[r & 3] = fma(q, a[r], p4[r & 3]);
+            }
+            part[buf * NW * 64 + wave * 64 + lane] = rows_sum((p4[0] + p4[1]) + (p4[2] + p4[3]));
+            lds_barrier();
+            C D = 0;
 #pragma unroll
-                for (int r = 0; r < RPT; ++r) o[r] = (prg == 0 && r <= ki) ? (C)0 : a[r];
-                lds_stn<C, RPT>(&xs[buf * XSB + prg * XST], o);
-            }
-            __syncthreads();
-            C x[RPT];
-            C p = 0;
-            if (rows_on) {
-                lds_ldn<C, RPT>(&xs[buf * XSB + prg * XST], x);
-                C p4[4] = {0, 0, 0, 0};
+            for (int w = 0; w < NW; ++w) D += part[buf * NW * 64 + w * 64 + pc];
+            const C akc = rowk[buf * 64 + pc];
+            const C ss = row_lane<ki>(D), alpha = row_lane<ki>(akc);
+            C beta = copysign(newton_sqrt(fma(alpha, alpha, ss)), -alpha);
+            const C den = alpha - beta;
+            C inv = newton_rcp(den), tau = -den * newton_rcp(beta);
+            // (a tail whose sum of squares is zero or below the normal range: H = I)
+            const bool ident = ss < (sizeof(C) == 8 ? (C)0x1p-1022 : (C)0x1p-126f);
+            beta = ident ? alpha : beta;
+            inv = ident ? (C)0 : inv;
+            tau = ident ? (C)0 : tau;
+            const C wk = fma(inv, D, akc);   // v_k^T (column pc), v_k's tail taken unscaled times inv
+            const C f = pc > ki ? tau * wk : (C)0, coef = f * inv;
+            // v_pc^T v_k for pc < k (v_pc's tail is stored unscaled; the other entries are not read)
+            if (wave == 0) Gs[ki * 16 + pc] = my_inv * wk;
+            my_inv = pc == ki ? inv : my_inv;
+            my_tau = pc == ki ? tau : my_tau;
 #pragma unroll
-                for (int r = 0; r < RPT; ++r) p4[r & 3] += x[r] * a[r];
-                p = (p4[0] + p4[1]) + (p4[2] + p4[3]);
-            } else {
-#pragma unroll
-                for (int r = 0; r < RPT; ++r) x[r] = 0;
+            for (int r = 0; r < RPT; ++r) {
+                // (nothing changes at and above the pivot row, nor in the pivot column: coef = 0)
+                if (!kKeep) asm volatile("" : "+v"(a[r]));   // the second fetch is not merged with the first
+                C q = kKeep ? x[r] : row_lane<ki>(a[r]);
+                if (!kKeep && r <= ki) q = top ? (C)0 : q;
+                a[r] = fma(-coef, q, a[r]);
             }
-            p += quad_get<kQuadXor1>(p);
-            p += quad_get<kQuadXor2>(p);
-            if ((lane & 3) == 0) part[wave * 16 + pc] = p;
-            __syncthreads();
-            C D = 0, ss = 0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                D += part[w * 16 + pc];
-                ss += part[w * 16 + ki];
-            }
-            const C alpha = rowk[buf * 16 + ki], akc = rowk[buf * 16 + pc];
-            C tau, beta, inv;
-            if (ss == (C)0) {
-                tau = 0; beta = alpha; inv = 0;
-            } else {
-                const C nrm = newton_sqrt(alpha * alpha + ss);
-                beta = alpha >= (C)0 ? -nrm : nrm;
-                tau = (beta - alpha) * newton_rcp(beta);
-                inv = newton_rcp(alpha - beta);
-            }
-            const C wk = akc + inv * D;   // v_k^T (column pc), v_k's tail taken unscaled times inv
-            const C f = tau * wk;
-            if (prg == 0) {
-                if (pc < ki) Gs[ki * 16 + pc] = my_inv * wk;   // v_pc^T v_k (v_pc's tail is stored unscaled)
-                if (pc == ki) taus[ki] = tau;
-            }
-            if (pc == ki) my_inv = inv;
-            if (prg == 0) a[ki] = (pc > ki) ? akc - f : ((pc == ki) ? beta : akc);
-            if (pc > ki && tau != (C)0) {
-                const C coef = f * inv;
-#pragma unroll
-                for (int r = 0; r < RPT; ++r) a[r] -= coef * x[r];   // x is zero at and above the pivot row
-            }
-        }
+            const C pivot_row = pc == ki ? beta : akc - f;
+            a[ki] = top ? pivot_row : a[ki];
+            __builtin_amdgcn_sched_barrier(0);
+        }, std::make_integer_sequence<int, 16>{});
+        if (top) taus[pc] = my_tau;
         PT_MARK(3);
         // explicit V block (unit diagonal, zeros above) back to LDS; R block aside
         if (rows_on) {

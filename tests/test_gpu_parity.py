@@ -256,6 +256,35 @@ def test_narrow_chase_keeps_a_bidiagonal_exactly():
         np.testing.assert_array_equal(eh, np.diag(dense, 1).astype(np.float64))
 
 
+@pytest.mark.parametrize("dtype,n,nb", [("f32", 200, 32), ("f32", 333, 64), ("f32", 400, 128), ("f64", 200, 32),
+                                         ("f64", 333, 64), ("f64", 300, 128)])
+def test_reflectors_with_zero_and_tiny_tails(dtype, n, nb):
+    # pivots whose tail is zero, or so small that its sum of squares leaves the normal range (H = I, the
+    # tail dropped: below 2^-63 in f32, 2^-511 in f64, far below eps times the largest entry), among
+    # ordinary ones: zero and duplicated columns and rows, rows and columns scaled to that size.  Dense
+    # (panels of stage 1) and as a band (panels of the band reduction).
+    a = workloads.gaussian_matrix(4711 + n, n, n)
+    tiny = -75 if dtype == "f32" else -530
+    a[:, 5:9] = 0.0
+    a[:, 20] = a[:, 21]
+    a[40:44, :] = 0.0
+    a[60:70, :] = np.ldexp(a[60:70, :], tiny)
+    a[:, 80:85] = np.ldexp(a[:, 80:85], tiny)
+    a = a.astype(workloads.NP_DTYPE[dtype])
+    tol = 10 * n * workloads.EPS[dtype]
+    rc, s, _ = _svdvals_general(np.asfortranarray(a), nb)
+    assert rc == 0
+    ref = oracle.svdvals(a.astype(np.float64))
+    assert np.abs(s - ref).max() <= tol * ref[0]
+    ii, jj = np.indices((n, n))
+    band = np.where((jj - ii >= 0) & (jj - ii <= nb), a, 0).astype(a.dtype)
+    dh, eh = _narrow_chase(band, dtype, nb)
+    sb = np.zeros(n)
+    assert svb.svb_bdsvals(n, dh, eh, sb) == 0
+    ref = oracle.svdvals(band.astype(np.float64))
+    assert np.abs(sb - ref).max() <= tol * ref[0]
+
+
 @pytest.mark.parametrize("name", ["c3a", "c3b", "c4", "c5b", "c5a"])
 def test_full_size_configs_against_stored_oracle(name):
     """Configs 3a/3b/4/5b/5a at full size against the oracle's stored singular values
