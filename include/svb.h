@@ -186,7 +186,7 @@ int svb_bdsvals(int64_t n, const double* d, const double* e, double* sigma);
 
 /*
  * Stage 3 on the device (what svb_svdvals runs unless SVB_STAGE3=host): Sturm
- * counts by the differential stationary qd recurrence, each interval refined
+ * counts by the sign sequence of the Golub-Kahan tridiagonal, each interval refined
  * by multisection (several lanes per singular value, one point of the
  * interval each).
  *   band_dt   SVB_F64 or SVB_F32: type of d, e and sigma.
