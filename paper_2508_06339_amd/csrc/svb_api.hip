@@ -86,9 +86,10 @@ size_t gb2bd_bytes(int64_t n, int nb)
 }
 
 // two-phase stage 2 (band -> 8 super-diagonals -> bidiagonal) unless switched off or unsupported
-bool two_phase(int nb, size_t elem_size, int64_t n)
+// (the band reduction's lane offsets into a block are 32-bit: a leading dimension beyond 2^26 takes the one-phase chase)
+bool two_phase(int nb, size_t elem_size, int64_t n, int64_t ldab)
 {
-    return nb != 8 && n >= 3 && env_int("SVB_CHASE_IMPL", 2) == 2 && band_reduce_supported(nb, elem_size);
+    return nb != 8 && n >= 3 && ldab <= ((int64_t)1 << 26) && env_int("SVB_CHASE_IMPL", 2) == 2 && band_reduce_supported(nb, elem_size);
 }
 
 // Algorithmic bytes of the two stage-2 kernels: the band reduction reads and writes every nb x nb
@@ -121,7 +122,7 @@ int gb2bd_typed(int64_t n, int nb, C* band, int64_t ldab, C* d, C* e, void* work
         launch_extract_bidiag<C>(band, ldab, n, 8, d, e, ctrl, nullptr, s);
         return rc;
     }
-    if (two_phase(nb, sizeof(C), n)) {
+    if (two_phase(nb, sizeof(C), n, ldab)) {
         int* ctrl2 = reinterpret_cast<int*>(static_cast<unsigned char*>(work) + gb2bd_first_bytes(n, nb));
         prof_begin(SVB_PROF_BAND_REDUCE, s, 0.0, band_reduce_bytes(n, nb, sizeof(C)));
         int rc = run_band_reduce<C>(n, nb, band, ldab, ctrl, s);
