@@ -173,7 +173,7 @@ template <int NW_, int WC_> struct NarrowShape {
 template <typename C, typename SH>
 __global__ __launch_bounds__(SH::NT) void chase_narrow_kernel(C* __restrict__ band, int64_t ldab, int64_t ku,
                                                               int64_t n, int* __restrict__ ctrl,
-                                                              int* __restrict__ flushed, int spin_limit)
+                                                              int* __restrict__ flushed, int stride, int spin_limit)
 {
     constexpr int D = SH::D, RS = SH::RS, NW = SH::NW, WC = SH::WC, WAVES = SH::WAVES;
     constexpr int UNITS = sizeof(C) == 8 ? 4 : 8;   // units of 8 columns a traffic wave moves at a time, at most
@@ -366,7 +366,7 @@ __global__ __launch_bounds__(SH::NT) void chase_narrow_kernel(C* __restrict__ ba
                         if (__builtin_amdgcn_readfirstlane(lds_get(&sh_fail))) break;
                         if (room > 0) {
                             seen = __builtin_amdgcn_readfirstlane(
-                                __hip_atomic_load(&flushed[b - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                                __hip_atomic_load(&flushed[(b - 1) * stride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
                             if (seen < n && (seen - i0) / D <= u) {
                                 // the wait for the previous bundle is bounded
                                 if (++spins > spin_limit) {
@@ -399,7 +399,7 @@ __global__ __launch_bounds__(SH::NT) void chase_narrow_kernel(C* __restrict__ ba
                     }
                     // (the next answer of the previous bundle travels with the columns)
                     if (seen < n)
-                        seen = __hip_atomic_load(&flushed[b - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        seen = __hip_atomic_load(&flushed[(b - 1) * stride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
                     for (int x = 0; x < UNITS; ++x)
                         if (x < nu) {
@@ -464,12 +464,12 @@ __global__ __launch_bounds__(SH::NT) void chase_narrow_kernel(C* __restrict__ ba
                     __builtin_amdgcn_s_waitcnt(0x0f70);
                     order_lds();
                     if (lane == 0)
-                        __hip_atomic_store(&flushed[b], u == last ? kAllFlushed : (int)(i0 + u * D), __ATOMIC_RELAXED,
+                        __hip_atomic_store(&flushed[b * stride], u == last ? kAllFlushed : (int)(i0 + u * D), __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
                 }
                 // (also when a wait has expired: the next bundle must not wait for this one)
                 if (lane == 0)
-                    __hip_atomic_store(&flushed[b], kAllFlushed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(&flushed[b * stride], kAllFlushed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             __builtin_amdgcn_s_setprio(0);
         }
@@ -477,15 +477,16 @@ __global__ __launch_bounds__(SH::NT) void chase_narrow_kernel(C* __restrict__ ba
     }
 }
 
-__global__ __launch_bounds__(256) void narrow_clear_kernel(int* __restrict__ p, int64_t count)
+__global__ __launch_bounds__(256) void narrow_clear_kernel(int* __restrict__ p, int64_t np, int* __restrict__ q, int64_t nq)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x)
-        p[i] = 0;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < np + nq; i += (int64_t)gridDim.x * blockDim.x)
+        (i < np ? p[i] : q[i - np]) = 0;
 }
 
 }  // namespace
 
-// ctrl: 64 ints (ticket, error flag) followed by one flushed counter per bundle
+// ctrl: 64 ints (ticket, error flag) followed by one flushed counter per bundle, unless the caller has room to keep
+// these apart (`spread`, 8 ints a bundle): one bundle polls while another writes beside it
 size_t chase_narrow_workspace_bytes(int64_t n) { return (size_t)(64 + n / 8 + 8) * sizeof(int); }
 
 // Sweeps per bundle.  Latencies set the pace (measured: a plain vector instruction 5 cycles from the
@@ -500,7 +501,7 @@ size_t chase_narrow_workspace_bytes(int64_t n) { return (size_t)(64 + n / 8 + 8)
 // columns (102 KB), beyond which nothing is gained (1536 columns: 1.42 instead of 1.38 us at n = 256, 1.52
 // instead of 1.53 at 8192).
 template <typename C>
-int run_chase_narrow(int64_t n, C* band, int64_t ldab, int64_t ku, int* ctrl, hipStream_t s)
+int run_chase_narrow(int64_t n, C* band, int64_t ldab, int64_t ku, int* ctrl, int* spread, hipStream_t s)
 {
     using SH = std::conditional_t<sizeof(C) == 8, NarrowShape<16, 704>, NarrowShape<24, 1024>>;
     if (n < 3) return SVB_OK;
@@ -512,16 +513,18 @@ int run_chase_narrow(int64_t n, C* band, int64_t ldab, int64_t ku, int* ctrl, hi
         attr_set = true;
     }
     const int64_t nbundles = (n - 2 + SH::NW - 1) / SH::NW;
-    const int64_t count = 64 + nbundles + 1;
-    int cb = (int)((count + 255) / 256);
-    hipLaunchKernelGGL(narrow_clear_kernel, dim3(cb > 256 ? 256 : cb), dim3(256), 0, s, ctrl, count);
+    int* const flushed = spread ? spread : ctrl + 64;
+    const int stride = spread ? 8 : 1;
+    const int64_t count = nbundles * stride;
+    int cb = (int)((64 + count + 255) / 256);
+    hipLaunchKernelGGL(narrow_clear_kernel, dim3(cb > 256 ? 256 : cb), dim3(256), 0, s, ctrl, (int64_t)64, flushed, count);
     const int grid = (int)min((int64_t)env_int("SVB_NARROW_GRID", 128), nbundles);
     const int spin_limit = env_int("SVB_CHASE_SPIN", 1 << 20);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(SH::NT), smem, s, band, ldab, ku, n, ctrl, ctrl + 64, spin_limit);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(SH::NT), smem, s, band, ldab, ku, n, ctrl, flushed, stride, spin_limit);
     return hipGetLastError() == hipSuccess ? SVB_OK : SVB_ERR_DEVICE;
 }
 
-template int run_chase_narrow<double>(int64_t, double*, int64_t, int64_t, int*, hipStream_t);
-template int run_chase_narrow<float>(int64_t, float*, int64_t, int64_t, int*, hipStream_t);
+template int run_chase_narrow<double>(int64_t, double*, int64_t, int64_t, int*, int*, hipStream_t);
+template int run_chase_narrow<float>(int64_t, float*, int64_t, int64_t, int*, int*, hipStream_t);
 
 }  // namespace svb

@@ -117,7 +117,7 @@ int gb2bd_typed(int64_t n, int nb, C* band, int64_t ldab, C* d, C* e, void* work
     if (nb == 8) {
         // narrow band: bundles of sweeps inside LDS windows
         prof_begin(SVB_PROF_NARROW, s, 0.0, narrow_bytes(n, sizeof(C)));
-        const int rc = run_chase_narrow<C>(n, band, ldab, 15, ctrl, s);
+        const int rc = run_chase_narrow<C>(n, band, ldab, 15, ctrl, nullptr, s);
         prof_end(s);
         launch_extract_bidiag<C>(band, ldab, n, 8, d, e, ctrl, nullptr, s);
         return rc;
@@ -129,7 +129,8 @@ int gb2bd_typed(int64_t n, int nb, C* band, int64_t ldab, C* d, C* e, void* work
         prof_end(s);
         if (rc == SVB_OK) {
             prof_begin(SVB_PROF_NARROW, s, 0.0, narrow_bytes(n, sizeof(C)));
-            rc = run_chase_narrow<C>(n, band, ldab, 2 * (int64_t)nb - 1, ctrl2, s);
+            // (the sweep counters of the first phase have done their work: n ints)
+            rc = run_chase_narrow<C>(n, band, ldab, 2 * (int64_t)nb - 1, ctrl2, ctrl + 64, s);
             prof_end(s);
         }
         launch_extract_bidiag<C>(band, ldab, n, nb, d, e, ctrl, ctrl2, s);

@@ -204,7 +204,7 @@ void launch_extract_bidiag(const C* band, int64_t ldab, int64_t n, int b, C* d, 
                            const int* ctrl2, hipStream_t s);
 // narrow band (8 super-diagonals) -> bidiagonal inside LDS windows; entry (i,j) at band[(i-j+ku) + j*ldab]
 template <typename C>
-int run_chase_narrow(int64_t n, C* band, int64_t ldab, int64_t ku, int* ctrl, hipStream_t s);
+int run_chase_narrow(int64_t n, C* band, int64_t ldab, int64_t ku, int* ctrl, int* spread, hipStream_t s);
 size_t chase_narrow_workspace_bytes(int64_t n);
 // band of nb super-diagonals -> band of 8 (blocked chase, same storage); false / SVB_ERR_UNSUPPORTED
 // where two nb x nb blocks do not fit in LDS
