@@ -72,6 +72,7 @@ __global__ __launch_bounds__(kPrepThreads) void bd_prep_kernel(const C* __restri
     }
 }
 
+constexpr int64_t kMinGuess = 300;        // rows from which a round costs more than the interpolation
 constexpr double kSmallPoint = 0x1p-50;   // below: two rows between rescalings, else eight
 constexpr int kGrid = 4096;   // points of the shared first partition of [0, bound]
 
@@ -118,8 +119,10 @@ __device__ __attribute__((noinline)) int64_t qd_count(const double* __restrict__
 // cycles each from a lone wave; the dependent chain is 16 cycles a row): 50 cycles a row measured
 // against 92 for the qd form above; the whole stage at n = 8192: 7.02 -> 3.37 ms (f64), 4.04 -> 1.81
 // (f32), at n = 32768: 50 -> 23 and 27 -> 12.
-template <int EVERY>
-__device__ __forceinline__ int64_t sequence_count(const double* __restrict__ z, int64_t n, double x)
+// f 2^fe: the last member of the sequence, det up to its sign, a polynomial in x whose zeros are the values
+// (f = NaN where the count was done again in the other form); formed if POLY, for some 5 % of the time.
+template <int EVERY, bool POLY>
+__device__ __forceinline__ int64_t sequence_count(const double* __restrict__ z, int64_t n, double x, double& f, int& fe)
 {
     constexpr int R = 8;
     double h = 0.0, b = 1.0;          // r_{2j-1}, r_{2j}
@@ -130,7 +133,7 @@ __device__ __forceinline__ int64_t sequence_count(const double* __restrict__ z, 
     // Points of either kind are judged by the same number in both forms: the outcome depends on x alone,
     // not on the other lanes of the wave.
     double low = 1.0, low_block = 1.0;
-    int moved = 0;
+    int moved = 0, shift = 0;
     auto row = [&](double ee, double dd) {
         const double nh = fma(x, b, -(ee * h));
         const double nb = fma(x, nh, -(dd * b));
@@ -143,6 +146,7 @@ __device__ __forceinline__ int64_t sequence_count(const double* __restrict__ z, 
         const double m = fmax(fabs(h), fabs(b));
         const int e = -__builtin_amdgcn_frexp_exp(m);
         low = fmin(low, m);
+        if (POLY) shift += e;
         if (EVERY < R) {
             if (last) low_block = fmin(low_block, __builtin_amdgcn_ldexp(m, moved));
             moved = last ? 0 : moved - e;
@@ -193,15 +197,19 @@ __device__ __forceinline__ int64_t sequence_count(const double* __restrict__ z, 
     // at the same point, whatever the rest of their waves does, or they could come out in the wrong order)
     const bool redo = (EVERY < R && x >= kSmallPoint ? low_block : low) < 0x1p-800;
     int64_t count = n - changes;
+    if (POLY) {
+        f = redo ? (double)NAN : b;
+        fe = -shift;
+    }
     if (__any(redo)) {
         const int64_t c = qd_count(z, n, x);
         count = redo ? c : count;
     }
     return count;
 }
-__device__ __forceinline__ int64_t sturm_count(const double* __restrict__ z, int64_t n, double x)
+template <bool POLY> __device__ __forceinline__ int64_t sturm_count(const double* __restrict__ z, int64_t n, double x, double& f, int& fe)
 {
-    return __any(x < kSmallPoint) ? sequence_count<2>(z, n, x) : sequence_count<8>(z, n, x);
+    return __any(x < kSmallPoint) ? sequence_count<2, POLY>(z, n, x, f, fe) : sequence_count<8, POLY>(z, n, x, f, fe);
 }
 
 // counts at the points x_i = bound * i / kGrid, i = 1 .. kGrid - 1 (x_0 counts 0, x_kGrid counts n)
@@ -213,18 +221,53 @@ __global__ __launch_bounds__(64) void bd_grid_kernel(const double* __restrict__ 
     int64_t c = 0;
     if (scale == scale) {
         const double x = hi0 * ((double)max(i, 1) / kGrid);   // (x = 0 would send its wave the slow ways)
-        c = sturm_count(z, n, x);
+        double f;
+        int fe;
+        c = sturm_count<false>(z, n, x, f, fe);
     }
     gcnt[i] = i == 0 ? 0 : (int)min(c, n);
     if (i == 0) gcnt[kGrid] = (int)n;
 }
 
-// Multisection: P lanes per singular value, each counting at one of P equally spaced interior
-// points of the value's current interval, which shrinks by P + 1 per round (P = 1 is plain
-// bisection).  The Sturm recurrence is one long dependent chain per point and a wave costs the
+// Where the polynomial through the nodes of a bracket vanishes inside it: t in (0, 1), 0 and 1 being the bracket's
+// ends, nodes 0 and 1.  NC nodes; Newton's form, Newton's method kept inside a shrinking bracket.
+template <int M>
+__device__ __forceinline__ double interpolated_zero(const double (&t)[6], const double (&c)[6], double y0, double y1)
+{
+    double a = 0.0, b = 1.0, x = y0 / (y0 - y1);
+#pragma unroll 1
+    for (int it = 0; it < 7; ++it) {
+        double p = c[M - 1], dp = 0.0;
+#pragma unroll
+        for (int i = M - 2; i >= 0; --i) {
+            dp = fma(dp, x - t[i], p);
+            p = fma(p, x - t[i], c[i]);
+        }
+        if ((p < 0.0) == (y0 < 0.0)) a = x;
+        else b = x;
+        const double nx = x - p / dp;
+        x = nx > a && nx < b ? nx : 0.5 * (a + b);
+    }
+    return x;
+}
+
+// Multisection: P lanes per singular value, each counting at one of P interior points of the value's current
+// interval.  The Sturm recurrence is one long dependent chain per point and a wave costs the
 // same whether it refines 64 values by 2 or 4 values by 17 per round, so while the compute
 // units have waves to spare the extra points are free and the number of rounds drops.
-template <typename C, int P>
+// The points are equally spaced (the interval shrinks by P + 1) until the value is alone in its interval.  From
+// then on the counts' recurrence has more to say: its last member is a polynomial that changes sign at the value,
+// known at the P points and the ends.  The next points are laid around the zero of the interpolating polynomial
+// through the nodes next to the value (up to six, none beyond another value), at distances delta,
+// delta 4, delta 16, .. (P = 16) on both sides, delta being half of what two more nodes can be expected to change, or
+// what the tolerance still asks for.  The counts alone decide which interval is taken, so a bad guess costs a round
+// and nothing else; the points are equally spaced after a round that gained less than that, where the interpolation has
+// not settled, and where equal spacing is enough to end.
+// Values that share an interval see the same points, those that do not are in order already: they come out in order.
+// Bidiagonal of a Gaussian matrix, rounds and ms with equal spacing only -> with guesses (whole stage): f64 n = 500 0.161
+// -> 0.133, n = 6000 10 -> 5, 2.49 -> 1.66, n = 20000 13.0 -> 8.7; f32 n = 6000 5 -> 3, 1.38 -> 1.16.  What is left at
+// n = 6000 is a wave and a half per SIMD, the last of which take seven rounds.
+template <typename C, int P, bool GUESS>
 __global__ __launch_bounds__(64) void bd_multisect_kernel(const double* __restrict__ ws, int64_t n,
                                                            C* __restrict__ sigma, double rel_tol,
                                                            double floor_frac, const int* __restrict__ gcnt)
@@ -243,6 +286,13 @@ __global__ __launch_bounds__(64) void bd_multisect_kernel(const double* __restri
         if (kraw < n && q == 0) sigma[n - 1 - k] = (C)0;
         return;
     }
+    // the round's nodes of every value: 0 the interval's lower end, P + 1 its upper end
+    __shared__ double sx[VPW][P + 2], sf[VPW][P + 2];
+    __shared__ int se[VPW][P + 2], sc[VPW][P + 2];
+    double* const X = sx[grp];
+    double* const Fv = sf[grp];
+    int* const E = se[grp];
+    int* const N = sc[grp];
     // first interval from the shared partition: gcnt[a] < k+1 <= gcnt[b] with b = a+1
     int a = 0, b = kGrid;
     while (b - a > 1) {
@@ -251,27 +301,97 @@ __global__ __launch_bounds__(64) void bd_multisect_kernel(const double* __restri
         else a = m;
     }
     double lo = hi0 * ((double)a / kGrid), hi = b == kGrid ? hi0 : hi0 * ((double)b / kGrid);
-    const double frac = (double)(q + 1) / (P + 1);
+    double flo = NAN, fhi = NAN;          // the polynomial at the ends, where known
+    int elo = 0, ehi = 0, nlo = gcnt[a], nhi = gcnt[b];
+    // equally spaced points: inside the interval, or, where the polynomial at an end is not known, with the ends
+    const double frac = (double)(q + 1) / (P + 1), frac_ends = (double)q / (P > 1 ? P - 1 : 1);
+    bool guess = false;
+    double centre = 0.0, delta = 0.0;
+    // this lane's offset from a guess, in units of delta: -G^(P/2-1) .. -1, 1 .. G^(P/2-1), G = 4, 16, 256
+    const int step = GUESS ? 32 / P * (q < P / 2 ? P / 2 - 1 - q : q - P / 2) : 0;
+    const double offset = __builtin_amdgcn_ldexp(q < P / 2 ? -1.0 : 1.0, step);
     for (int it = 0; it < 200; ++it) {
         const double w = hi - lo, mid = 0.5 * (lo + hi);
         // width relative to the value, or to floor_frac times the bound on the largest value if that is more
-        const bool open = (w > rel_tol * fmax(hi, floor_frac * hi0) + 1e-38 * hi0) && (mid > lo && mid < hi);
+        const double wanted = rel_tol * fmax(hi, floor_frac * hi0) + 1e-38 * hi0;
+        const bool open = (w > wanted) && (mid > lo && mid < hi);
         if (!__any(open)) break;            // wave-uniform exit: the row hand-over needs every lane
         // this lane's point; rounding may put it on an end of the interval, where the count is known
-        const double x = fmin(fmax(fma(w, frac, lo), lo), hi);
-        const int64_t cnt = sturm_count(z, n, x);
+        const double x = fmin(fmax(guess ? fma(delta, offset, centre)
+                                              : fma(w, GUESS && flo + fhi != flo + fhi ? frac_ends : frac, lo), lo), hi);
+        double f = 0.0;
+        int fe = 0;
+        const int64_t cnt = sturm_count<GUESS>(z, n, x, f, fe);
         const bool above = x >= hi || (x > lo && cnt >= k + 1);   // the value lies below this point
         // the points of a value are ascending, so its lanes read: below .. below, above .. above
         const unsigned long long m = __ballot(above) >> (grp * P);
         const unsigned long long mine = P == 64 ? m : (m & ((1ull << P) - 1ull));
-        const int f = mine ? __builtin_ctzll(mine) : P;          // first point above the value
-        if (open) {
-            // (the same expressions the lanes f - 1 and f evaluated their points with)
-            const double nlo = f == 0 ? lo : fmin(fmax(fma(w, (double)f / (P + 1), lo), lo), hi);
-            const double nhi = f == P ? hi : fmin(fmax(fma(w, (double)(f + 1) / (P + 1), lo), lo), hi);
-            lo = nlo;
-            hi = nhi;
+        const int first = mine ? __builtin_ctzll(mine) : P;          // first point above the value
+        X[q + 1] = x; Fv[q + 1] = f; E[q + 1] = fe; N[q + 1] = (int)min(cnt, n);
+        if (q == 0) {
+            X[0] = lo; Fv[0] = flo; E[0] = elo; N[0] = nlo;
+            X[P + 1] = hi; Fv[P + 1] = fhi; E[P + 1] = ehi; N[P + 1] = nhi;
         }
+        __syncthreads();
+        if (open) {
+            lo = X[first]; flo = Fv[first]; elo = E[first]; nlo = N[first];
+            hi = X[first + 1]; fhi = Fv[first + 1]; ehi = E[first + 1]; nhi = N[first + 1];
+            const bool gained = (hi - lo) * (P - 1) <= w * 1.0001;
+            guess = false;
+            if (GUESS && gained && nlo == k && nhi == k + 1 && flo * fhi < 0.0) {
+                // nodes outwards from the bracket, those between the neighbouring values only
+                double t[6], y[6], c[6];
+                const double wi = 1.0 / (hi - lo);
+                const int e0 = max(elo, ehi);
+                t[0] = 0.0; t[1] = 1.0;
+                y[0] = __builtin_amdgcn_ldexp(flo, elo - e0);
+                y[1] = __builtin_amdgcn_ldexp(fhi, ehi - e0);
+                int l = first, r = first + 1, nodes = 2;
+#pragma unroll
+                for (int j = 2; j < 6; ++j) {
+                    const int i = (j & 1) ? r + 1 : l - 1;
+                    const int ic = min(max(i, 0), P + 1);
+                    const double xi = X[ic], fi = Fv[ic];
+                    const bool use = nodes == j && i >= 0 && i <= P + 1 && fi == fi && fi != 0.0 &&
+                                     ((j & 1) ? (xi > X[r] && N[ic] == k + 1) : (xi < X[l] && N[ic] == k));
+                    t[j] = (xi - lo) * wi;
+                    y[j] = __builtin_amdgcn_ldexp(fi, min(max(E[ic] - e0, -1000), 500));
+                    if (use) {
+                        ++nodes;
+                        if (j & 1) r = i;
+                        else l = i;
+                    }
+                }
+                // divided differences
+#pragma unroll
+                for (int j = 0; j < 6; ++j) c[j] = y[j];
+#pragma unroll
+                for (int d = 1; d < 6; ++d)
+#pragma unroll
+                    for (int j = 5; j >= d; --j)
+                        if (j < nodes) c[j] = (c[j] - c[j - 1]) / (t[j] - t[j - d]);
+                double z0, z1;
+                if (nodes == 6) {
+                    z0 = interpolated_zero<6>(t, c, y[0], y[1]);
+                    z1 = interpolated_zero<4>(t, c, y[0], y[1]);
+                } else if (nodes >= 4) {
+                    z0 = interpolated_zero<4>(t, c, y[0], y[1]);
+                    z1 = interpolated_zero<3>(t, c, y[0], y[1]);
+                } else {
+                    z0 = y[0] / (y[0] - y[1]);
+                    z1 = z0 + z0 * (1.0 - z0);
+                }
+                const double wn = hi - lo, want = rel_tol * fmax(hi, floor_frac * hi0) + 1e-38 * hi0;
+                centre = fma(wn, z0, lo);
+                // (the next two nodes would change about d1 d1 / d2 more, d1 and d2 being what the last and the ones
+                // before them changed)
+                const double d1 = fabs(z0 - z1), d2 = fabs(z1 - y[0] / (y[0] - y[1]));
+                const double d = nodes >= 4 ? 0.5 * fmin(fmax(d1 * d1 / fmax(d2, 1e-300), d1 * (1.0 / 4096)), d1) : 0.25 * d1;
+                delta = fmax(wn * d, 0.45 * want);
+                guess = centre >= lo && centre <= hi && d1 < 0.05 && wn > (P + 1) * want;
+            }
+        }
+        __syncthreads();
     }
     if (kraw < n && q == 0) sigma[n - 1 - k] = (C)(0.5 * (lo + hi) * scale);
 }
@@ -297,11 +417,13 @@ int run_bdsvals_dev(int64_t n, const C* d, const C* e, C* sigma, void* work, dou
         hipLaunchKernelGGL(kern, dim3((unsigned)((n + vpw - 1) / vpw)), dim3(64), 0, s, ws, n, sigma, rel_tol, floor_frac,
                            gcnt);
     };
-    if (p >= 16) launch(bd_multisect_kernel<C, 16>, 16);
-    else if (p >= 8) launch(bd_multisect_kernel<C, 8>, 8);
-    else if (p >= 4) launch(bd_multisect_kernel<C, 4>, 4);
-    else if (p >= 2) launch(bd_multisect_kernel<C, 2>, 2);
-    else launch(bd_multisect_kernel<C, 1>, 1);
+    // (four points at least to interpolate, and rows enough that a round costs more than the interpolation)
+    const bool guess = n >= kMinGuess;
+    if (p >= 16) guess ? launch(bd_multisect_kernel<C, 16, true>, 16) : launch(bd_multisect_kernel<C, 16, false>, 16);
+    else if (p >= 8) guess ? launch(bd_multisect_kernel<C, 8, true>, 8) : launch(bd_multisect_kernel<C, 8, false>, 8);
+    else if (p >= 4) guess ? launch(bd_multisect_kernel<C, 4, true>, 4) : launch(bd_multisect_kernel<C, 4, false>, 4);
+    else if (p >= 2) launch(bd_multisect_kernel<C, 2, false>, 2);
+    else launch(bd_multisect_kernel<C, 1, false>, 1);
     return hipGetLastError() == hipSuccess ? SVB_OK : SVB_ERR_DEVICE;
 }
 
