@@ -89,13 +89,6 @@ constexpr int kDppXor1 = 0xB1;        // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;        // quad_perm [2,3,0,1]
 constexpr int kDppHalfMirror = 0x141; // lane i <-> 7-i inside groups of 8
 
-// sum over the four lanes of a quad, result in all four
-template <typename C> __device__ __forceinline__ C quad_allsum(C v)
-{
-    v += dpp_get<kDppXor1>(v);
-    v += dpp_get<kDppXor2>(v);
-    return v;
-}
 constexpr int kDppRor8 = 0x128;       // lane i <-> i^8 inside rows of 16 (rotate by 8)
 
 __device__ __forceinline__ float rrcp(float x)
@@ -122,24 +115,6 @@ template <typename Fn, int... K> __device__ __forceinline__ void static_steps(Fn
 // four segments of the long direction are shifted against each other so that the four
 // parts of a line read different LDS banks
 template <int B, int D> __device__ __forceinline__ int vidx(int e) { return e * D + (e / (B / 4)) * D; }
-
-// D consecutive values of the V buffer with 16-byte LDS reads
-template <int D> __device__ __forceinline__ void load_v(const float* v, float (&out)[D])
-{
-#pragma unroll
-    for (int k = 0; k < D; k += 4) {
-        const float4 t = *reinterpret_cast<const float4*>(v + k);
-        out[k] = t.x; out[k + 1] = t.y; out[k + 2] = t.z; out[k + 3] = t.w;
-    }
-}
-template <int D> __device__ __forceinline__ void load_v(const double* v, double (&out)[D])
-{
-#pragma unroll
-    for (int k = 0; k < D; k += 2) {
-        const double2 t = *reinterpret_cast<const double2*>(v + k);
-        out[k] = t.x; out[k + 1] = t.y;
-    }
-}
 
 // The panels form sums of squares, so a line whose entries are all below 2 is moved up by a power of two
 // first and its part of the triangular factor back (H depends on a line's direction only, and is
@@ -500,58 +475,76 @@ __device__ __forceinline__ void apply_tile(C* base, int es, int ls, int nvalid, 
     }
 }
 
-// The same for a line of the packed band in device memory (device-scope accesses): elements
-// base[e*es], e < ne, eight lanes per line (an eighth of the line each, held in registers
-// between the two passes).  With IL the eight lanes own interleaved elements (e = 8*jj + p),
-// which keeps their accesses together when the line is contiguous in memory.
-template <typename C, int B, int D, bool IL>
-__device__ __forceinline__ void apply_line_g(C* base, int64_t es, bool valid, int ne, const C* Vs, const C* Ts)
+// The same for sixteen lines of the packed band in device memory (device-scope accesses), held in registers
+// between the two products: element e of line n at p + n*ls + e*es, e < ne, lines n < nvalid.  All loads go out
+// together, without a predicate where the tile is whole.  What bounds it are the pieces of 128 (rows) and 32 bytes
+// (columns) the lanes of an access fall into.  Eight lanes per line, two rounds of eight lines, V re-read from LDS for
+// every line, took 35 us for the rows of a step of the in-band kernel (f64, B = 128), 10 so; the columns are at 14 in
+// both.  The reduction at n = 8192: 124 -> 86 ms.
+template <typename C, int B, int D>
+__device__ __forceinline__ void apply_tile_g(C* p, int64_t es, int64_t ls, int nvalid, int ne, const C* Vs, const C* Ts)
 {
-    constexpr int SEG = B / 8;
-    const int p = threadIdx.x & 7;
-    C a[SEG];
-    C w[D];
+    using F = Frag<C>;
+    typedef typename F::acc_t acc_t;
+    constexpr int NTL = B / 16;
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    const int i = lane & 15, gq = lane >> 4, j = i & 7;
+    const bool valid = i < nvalid, full = nvalid >= 16 && ne >= B;
+    const int64_t off = i * ls + F::roff(0, gq) * es;
+    const int64_t e1 = F::roff(1, 0) * es, e2 = 16 * es - 3 * e1;   // to the next register / tile
+    ne = valid ? ne - F::roff(0, gq) : 0;
+    acc_t y[NTL];
+    if (full) {
+        const C* q = p;
 #pragma unroll
-    for (int k = 0; k < D; ++k) w[k] = 0;
-    if (valid) {
+        for (int a = 0; a < NTL; ++a)
 #pragma unroll
-        for (int jj = 0; jj < SEG; ++jj) {
-            const int e = IL ? 8 * jj + p : p * SEG + jj;
-            a[jj] = (e < ne) ? rgld(base + e * es) : (C)0;
-        }
+            for (int r = 0; r < 4; ++r) {
+                y[a][r] = rgld(q + off);
+                q += r < 3 ? e1 : e2;
+            }
+    } else {
+        const C* q = p;
 #pragma unroll
-        for (int jj = 0; jj < SEG; ++jj) {
-            const int e = IL ? 8 * jj + p : p * SEG + jj;
-            C v[D];
-            load_v<D>(Vs + vidx<B, D>(e), v);
+        for (int a = 0; a < NTL; ++a)
 #pragma unroll
-            for (int k = 0; k < D; ++k) w[k] += a[jj] * v[k];
-        }
+            for (int r = 0; r < 4; ++r) {
+                C v = 0;
+                if (16 * a + F::roff(r, 0) < ne) v = rgld(q + off);
+                y[a][r] = v;
+                q += r < 3 ? e1 : e2;
+            }
     }
+    acc_t w, z;
 #pragma unroll
-    for (int k = 0; k < D; ++k) {
-        w[k] = quad_allsum(w[k]);
-        w[k] += dpp_get<kDppHalfMirror>(w[k]);   // the other quad of the eight
-    }
-    C z[D];
+    for (int r = 0; r < 4; ++r) { w[r] = 0; z[r] = 0; }
 #pragma unroll
-    for (int k = 0; k < D; ++k) {
-        C acc = 0;
+    for (int a = 0; a < NTL; ++a)
 #pragma unroll
-        for (int j = 0; j <= k; ++j) acc += w[j] * Ts[j * D + k];
-        z[k] = acc;
-    }
-    if (valid) {
+        for (int r = 0; r < 4; ++r) w = F::mma(Vs[vidx<B, D>(16 * a + F::roff(r, gq)) + j], y[a][r], w);
 #pragma unroll
-        for (int jj = 0; jj < SEG; ++jj) {
-            const int e = IL ? 8 * jj + p : p * SEG + jj;
-            C v[D];
-            load_v<D>(Vs + vidx<B, D>(e), v);
-            C x = a[jj];
+    for (int r = 0; r < 2; ++r) z = F::mma(-Ts[F::roff(r, gq) * D + j], w[r], z);
 #pragma unroll
-            for (int k = 0; k < D; ++k) x -= z[k] * v[k];
-            if (e < ne) rgst(base + e * es, x);
-        }
+    for (int a = 0; a < NTL; ++a)
+#pragma unroll
+        for (int r = 0; r < 2; ++r) y[a] = F::mma(Vs[vidx<B, D>(16 * a + i) + F::roff(r, gq)], z[r], y[a]);
+    if (full) {
+#pragma unroll
+        for (int a = 0; a < NTL; ++a)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                rgst(p + off, y[a][r]);
+                p += r < 3 ? e1 : e2;
+            }
+    } else {
+#pragma unroll
+        for (int a = 0; a < NTL; ++a)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (16 * a + F::roff(r, 0) < ne) rgst(p + off, y[a][r]);
+                p += r < 3 ? e1 : e2;
+            }
     }
 }
 
@@ -1131,7 +1124,7 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
     // and LDS.  The panel wave's work overlaps the traffic: the right panel of step t with the
     // write-back of Z of step t-1, the left panel with the write-back of U.
     using SH = InbandShape<B>;
-    static_assert(SH::NT == 1024, "waves 0-7 on LDS lines, waves 8-15 on band lines");
+    static_assert(SH::NT == 1024 && sizeof(C) == 8, "waves 0-7 on LDS lines, waves 8-15 on band lines, sixteen each; Frag of f64");
     constexpr int LD = B + 1, PER = SH::PER, JS = SH::JS;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     C* S = reinterpret_cast<C*>(smem_raw);        // rows and columns c0 .. c0+B-1: S[row + col*LD]
@@ -1144,7 +1137,6 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
     const bool lead = tid == SH::PWV * kWave;                      // first lane of the panel wave
     const int tw = wv - 1;                       // index among the traffic waves
     const bool traffic = !pw && tw < SH::NTW;
-    const int line = (tid >> 6) * 16 + (lane >> 2);                // line of the apply phases
     // this lane's block row and first block column
     const int ii = (tw % SH::GPC) * kWave + (B >= kWave ? lane : lane % B);
     const int jj0 = (tw / SH::GPC) * SH::CPG + (B >= kWave ? 0 : lane / B);
@@ -1183,15 +1175,15 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
     // wait_for: waits (one lane) until sweep s-1 has reached `need`, `seen` being an earlier
     // poll; an expired wait sets sh_fail
     auto poll = [&](int64_t s) -> int {
-        return (lead && s > 0) ? __hip_atomic_load(&progress[s - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        return (lead && s > 0) ? __hip_atomic_load(&progress[(s - 1) * kProgressStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
     };
     auto publish = [&](int64_t s, int value) {
-        if (lead) __hip_atomic_store(&progress[s], value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lead) __hip_atomic_store(&progress[s * kProgressStride], value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     auto wait_for = [&](int64_t s, int need, int seen) {
         if (lead && s > 0 && seen < need) {
             int spins = 0;
-            while (__hip_atomic_load(&progress[s - 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need) {
+            while (__hip_atomic_load(&progress[(s - 1) * kProgressStride], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need) {
                 if (++spins > spin_limit) {
                     atomicExch(&ctrl[1], 1);
                     sh_fail = 1;
@@ -1211,7 +1203,7 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
             const int arrived = atomicAdd(&sh_back, 1);
             if (arrived == SH::NTW - 1) {
                 sh_back = 0;
-                __hip_atomic_store(&progress[s], value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&progress[s * kProgressStride], value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
     };
@@ -1225,7 +1217,7 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
             sh_back = 0;
         }
         __syncthreads();
-        const int64_t s = sh_s;
+        const int64_t s = __builtin_amdgcn_readfirstlane(sh_s);
         __syncthreads();
         if (s >= nsweeps) break;
         const int64_t c00 = (s + 1) * D;
@@ -1301,18 +1293,13 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
             RMARK(2);
             // ---- S3: block reflector onto the rows below X
             {
-                // (waves 0 .. 7: the rows of Z, in LDS, four lanes per line; waves 8 .. 15: rows D .. B-1
-                // of U, in the band, eight lanes per line, two rounds; none in the first step, whose X
-                // is the sweep's own rows)
-                if (line < B) {
+                // (waves 0 .. 7: the rows of Z, in LDS; waves 8 .. 15: rows D .. B-1 of U, in the band; none in the
+                // first step, whose X is the sweep's own rows)
+                if (wv < 8) {
                     apply_tile<C, B, D>(S + 16 * wv, LD, 1, 16, Vs, Ts);
                 } else if (t > 0) {
-#pragma unroll 1
-                    for (int rd = 0; rd < 2; ++rd) {
-                        const int row = D + rd * (B / 2) + (wv - 8) * 8 + (lane >> 3);
-                        apply_line_g<C, B, D, false>(band + ((c0 - B + row) - c0 + ku) + c0 * ldab, ldm1,
-                                                     row < B, ncol, Vs, Ts);
-                    }
+                    const int row = D + 16 * (wv - 8);
+                    apply_tile_g<C, B, D>(band + ((c0 - B + row) - c0 + ku) + c0 * ldab, ldm1, 1, B - row, ncol, Vs, Ts);
                     stores_done();
                 }
             }
@@ -1334,17 +1321,15 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
             seen_next = poll(s);
             // ---- S5: block reflector onto the other columns of Z and onto A3
             {
-                // lines 0 .. B-1: columns D .. B-1 of Z, in LDS; lines B .. 2B-1: the columns of the
-                // block right of Z, in the band
-                if (line < B) {
+                // waves 0 .. 7: columns D .. B-1 of Z, in LDS; waves 8 .. 15: the columns of the block right of Z, in
+                // the band
+                if (wv < 8) {
                     apply_tile<C, B, D>(S + (D + 16 * wv) * LD, 1, LD, B - D - 16 * wv, Vs, Ts);
                 } else {
                     const int nrow = (int)min((int64_t)B, n - c0);
-#pragma unroll 1
-                    for (int rd = 0; rd < 2; ++rd) {
-                        const int64_t cg = c0 + B + rd * (B / 2) + (wv - 8) * 8 + (lane >> 3);
-                        apply_line_g<C, B, D, true>(band + (c0 - cg + ku) + cg * ldab, 1, cg < n, nrow, Vs, Ts);
-                    }
+                    const int64_t cg = c0 + B + 16 * (wv - 8);
+                    apply_tile_g<C, B, D>(band + (c0 - cg + ku) + cg * ldab, 1, ldm1, (int)max((int64_t)0, min((int64_t)16, n - cg)),
+                                          nrow, Vs, Ts);
                     stores_done();
                 }
             }
@@ -1362,7 +1347,7 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         }
         __syncthreads();
-        if (lead) __hip_atomic_store(&progress[s], kSweepDone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lead) __hip_atomic_store(&progress[s * kProgressStride], kSweepDone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
     }
 #ifdef SVB_CHASE_TIMING
@@ -1405,7 +1390,7 @@ int launch_band_reduce(int64_t n, C* band, int64_t ldab, int* ctrl, hipStream_t 
         attr_set = true;
     }
     const int64_t nsweeps = (n - 1) / D;
-    const int64_t count = 64 + nsweeps * (inband ? 1 : kProgressStride);
+    const int64_t count = 64 + nsweeps * kProgressStride;
     const int cb = (int)((count + 255) / 256);
     hipLaunchKernelGGL(reduce_clear_kernel, dim3(cb > 256 ? 256 : cb), dim3(256), 0, s, ctrl, count);
     if (nsweeps <= 0) return SVB_OK;
