@@ -119,10 +119,11 @@ template <int B, int D> __device__ __forceinline__ int vidx(int e) { return e * 
 // The panels form sums of squares, so a line whose entries are all below 2 is moved up by a power of two
 // first and its part of the triangular factor back (H depends on a line's direction only, and is
 // linear in every line by itself).  A tail is given up (H = I) where its sum of squares is
-// below `least`: 2^-50 (f32) or 2^-480 (f64) beside an entry of 2 or more, 2^-106 / 2^-980 of a line that was
+// below `least`: 2^-47 (f32) or 2^-477 (f64) beside an entry of 2 or more, 2^-106 / 2^-980 of a line that was
 // moved.  Without the move, bands of entries near 2^-65 (f32) or 2^-515 (f64) lost their tails
 // altogether; with squares below the normal range used as they are, tiny lines beside large ones gave
-// reflectors that were not orthogonal.  `least` also keeps the entries of T, up to 4 / least, finite.
+// reflectors that were not orthogonal.  The other lines are moved down by 8: u^T u is up to four times the sum of
+// squares, which may lie at the end of the range.  `least` also keeps the entries of T, up to 4 / least, finite.
 template <typename C> struct LineRange;
 template <> struct LineRange<float> { static constexpr float up = 0x1p56f, down = 0x1p-56f, least = 0x1p-100f, floor = 0x1p-126f; };
 template <> struct LineRange<double> { static constexpr double up = 0x1p500, down = 0x1p-500, least = 0x1p-960, floor = 0x1p-1022; };
@@ -237,8 +238,9 @@ __device__ __forceinline__ void panel_wave(const C* P, C* Vs, PanelTail<C>& tail
             for (int j = 0; j < NV; ++j) x[i + j] = v[j];
         }
     }
-    const C up = rows_or(exponent_bits(x)) & 0x40000000u ? (C)1 : LineRange<C>::up;
-    tail.down = up == (C)1 ? (C)1 : LineRange<C>::down;
+    const bool large = rows_or(exponent_bits(x)) & 0x40000000u;
+    const C up = large ? (C)0.125 : LineRange<C>::up;
+    tail.down = large ? (C)8 : LineRange<C>::down;
     tail.ss = tail.alpha = 0;
 #pragma unroll
     for (int i = 0; i < QN; ++i) x[i] *= up;
