@@ -120,7 +120,7 @@ __device__ __attribute__((noinline)) int64_t qd_count(const double* __restrict__
 // against 92 for the qd form above; the whole stage at n = 8192: 7.02 -> 3.37 ms (f64), 4.04 -> 1.81
 // (f32), at n = 32768: 50 -> 23 and 27 -> 12.
 // f 2^fe: the last member of the sequence, det up to its sign, a polynomial in x whose zeros are the values
-// (f = NaN where the count was done again in the other form); formed if POLY, for some 5 % of the time.
+// (f = 0 where the count was done again in the other form); formed if POLY, for some 5 % of the time.
 template <int EVERY, bool POLY>
 __device__ __forceinline__ int64_t sequence_count(const double* __restrict__ z, int64_t n, double x, double& f, int& fe)
 {
@@ -198,7 +198,7 @@ __device__ __forceinline__ int64_t sequence_count(const double* __restrict__ z, 
     const bool redo = (EVERY < R && x >= kSmallPoint ? low_block : low) < 0x1p-800;
     int64_t count = n - changes;
     if (POLY) {
-        f = redo ? (double)NAN : b;
+        f = redo ? 0.0 : b;
         fe = -shift;
     }
     if (__any(redo)) {
@@ -229,12 +229,19 @@ __global__ __launch_bounds__(64) void bd_grid_kernel(const double* __restrict__ 
     if (i == 0) gcnt[kGrid] = (int)n;
 }
 
-// Where the polynomial through the nodes of a bracket vanishes inside it: t in (0, 1), 0 and 1 being the bracket's
-// ends, nodes 0 and 1.  NC nodes; Newton's form, Newton's method kept inside a shrinking bracket.
-template <int M>
-__device__ __forceinline__ double interpolated_zero(const double (&t)[6], const double (&c)[6], double y0, double y1)
+// 1 / x for guesses
+__device__ __forceinline__ double quick_rcp(double x)
 {
-    double a = 0.0, b = 1.0, x = y0 / (y0 - y1);
+    const double r = __builtin_amdgcn_rcp(x);
+    return fma(r, fma(-x, r, 1.0), r);
+}
+
+// Where the polynomial through the nodes of a bracket vanishes inside it: t in (0, 1), 0 and 1 being the bracket's
+// ends, nodes 0 and 1.  M nodes; Newton's form, Newton's method from x on, kept inside a shrinking bracket.
+template <int M>
+__device__ __forceinline__ double interpolated_zero(const double (&t)[6], const double (&c)[6], bool negative, double x)
+{
+    double a = 0.0, b = 1.0;
 #pragma unroll 1
     for (int it = 0; it < 7; ++it) {
         double p = c[M - 1], dp = 0.0;
@@ -243,9 +250,9 @@ __device__ __forceinline__ double interpolated_zero(const double (&t)[6], const 
             dp = fma(dp, x - t[i], p);
             p = fma(p, x - t[i], c[i]);
         }
-        if ((p < 0.0) == (y0 < 0.0)) a = x;
+        if ((p < 0.0) == negative) a = x;
         else b = x;
-        const double nx = x - p / dp;
+        const double nx = fma(-p, quick_rcp(dp), x);
         x = nx > a && nx < b ? nx : 0.5 * (a + b);
     }
     return x;
@@ -263,10 +270,12 @@ __device__ __forceinline__ double interpolated_zero(const double (&t)[6], const 
 // what the tolerance still asks for.  The counts alone decide which interval is taken, so a bad guess costs a round
 // and nothing else; the points are equally spaced after a round that gained less than that, where the interpolation has
 // not settled, and where equal spacing is enough to end.
+// The polynomial is formed, and known ends asked for, only for values that are alone (and in the first round), the
+// ends only once: a point where it is not to be had (the count was done again: singular matrices) counts as known, and
+// at zero it is a product of the diagonal.  A form that asked for both ends in every round of every value until it
+// had them took 3.3 times as long as equal spacing on singular matrices (0.44 -> 1.59 ms at n = 700) and up to 1.4 times on
+// tight clusters.
 // Values that share an interval see the same points, those that do not are in order already: they come out in order.
-// Bidiagonal of a Gaussian matrix, rounds and ms with equal spacing only -> with guesses (whole stage): f64 n = 500 0.161
-// -> 0.133, n = 6000 10 -> 5, 2.49 -> 1.66, n = 20000 13.0 -> 8.7; f32 n = 6000 5 -> 3, 1.38 -> 1.16.  What is left at
-// n = 6000 is a wave and a half per SIMD, the last of which take seven rounds.
 template <typename C, int P, bool GUESS>
 __global__ __launch_bounds__(64) void bd_multisect_kernel(const double* __restrict__ ws, int64_t n,
                                                            C* __restrict__ sigma, double rel_tol,
@@ -286,13 +295,6 @@ __global__ __launch_bounds__(64) void bd_multisect_kernel(const double* __restri
         if (kraw < n && q == 0) sigma[n - 1 - k] = (C)0;
         return;
     }
-    // the round's nodes of every value: 0 the interval's lower end, P + 1 its upper end
-    __shared__ double sx[VPW][P + 2], sf[VPW][P + 2];
-    __shared__ int se[VPW][P + 2], sc[VPW][P + 2];
-    double* const X = sx[grp];
-    double* const Fv = sf[grp];
-    int* const E = se[grp];
-    int* const N = sc[grp];
     // first interval from the shared partition: gcnt[a] < k+1 <= gcnt[b] with b = a+1
     int a = 0, b = kGrid;
     while (b - a > 1) {
@@ -301,97 +303,161 @@ __global__ __launch_bounds__(64) void bd_multisect_kernel(const double* __restri
         else a = m;
     }
     double lo = hi0 * ((double)a / kGrid), hi = b == kGrid ? hi0 : hi0 * ((double)b / kGrid);
-    double flo = NAN, fhi = NAN;          // the polynomial at the ends, where known
-    int elo = 0, ehi = 0, nlo = gcnt[a], nhi = gcnt[b];
-    // equally spaced points: inside the interval, or, where the polynomial at an end is not known, with the ends
-    const double frac = (double)(q + 1) / (P + 1), frac_ends = (double)q / (P > 1 ? P - 1 : 1);
-    bool guess = false;
-    double centre = 0.0, delta = 0.0;
-    // this lane's offset from a guess, in units of delta: -G^(P/2-1) .. -1, 1 .. G^(P/2-1), G = 4, 16, 256
-    const int step = GUESS ? 32 / P * (q < P / 2 ? P / 2 - 1 - q : q - P / 2) : 0;
-    const double offset = __builtin_amdgcn_ldexp(q < P / 2 ? -1.0 : 1.0, step);
-    for (int it = 0; it < 200; ++it) {
-        const double w = hi - lo, mid = 0.5 * (lo + hi);
-        // width relative to the value, or to floor_frac times the bound on the largest value if that is more
-        const double wanted = rel_tol * fmax(hi, floor_frac * hi0) + 1e-38 * hi0;
-        const bool open = (w > wanted) && (mid > lo && mid < hi);
-        if (!__any(open)) break;            // wave-uniform exit: the row hand-over needs every lane
-        // this lane's point; rounding may put it on an end of the interval, where the count is known
-        const double x = fmin(fmax(guess ? fma(delta, offset, centre)
-                                              : fma(w, GUESS && flo + fhi != flo + fhi ? frac_ends : frac, lo), lo), hi);
-        double f = 0.0;
-        int fe = 0;
-        const int64_t cnt = sturm_count<GUESS>(z, n, x, f, fe);
-        const bool above = x >= hi || (x > lo && cnt >= k + 1);   // the value lies below this point
-        // the points of a value are ascending, so its lanes read: below .. below, above .. above
-        const unsigned long long m = __ballot(above) >> (grp * P);
+    // width relative to the value, or to floor_frac times the bound on the largest value if that is more
+    auto wanted = [&]() -> double { return rel_tol * fmax(hi, floor_frac * hi0) + 1e-38 * hi0; };
+    // whether to go on, and the first of the round's points that is above the value (P: none); the points of a value
+    // are ascending, so its lanes read: below .. below, above .. above.  Rounding may have put a point on an end of
+    // the interval, where the count is known.
+    auto is_open = [&]() -> bool {
+        const double mid = 0.5 * (lo + hi);
+        return (hi - lo > wanted()) && (mid > lo && mid < hi);
+    };
+    auto first_above = [&](double x, int64_t cnt) -> int {
+        const unsigned long long m = __ballot(x >= hi || (x > lo && cnt >= k + 1)) >> (grp * P);
         const unsigned long long mine = P == 64 ? m : (m & ((1ull << P) - 1ull));
-        const int first = mine ? __builtin_ctzll(mine) : P;          // first point above the value
-        X[q + 1] = x; Fv[q + 1] = f; E[q + 1] = fe; N[q + 1] = (int)min(cnt, n);
-        if (q == 0) {
-            X[0] = lo; Fv[0] = flo; E[0] = elo; N[0] = nlo;
-            X[P + 1] = hi; Fv[P + 1] = fhi; E[P + 1] = ehi; N[P + 1] = nhi;
-        }
-        __syncthreads();
-        if (open) {
-            lo = X[first]; flo = Fv[first]; elo = E[first]; nlo = N[first];
-            hi = X[first + 1]; fhi = Fv[first + 1]; ehi = E[first + 1]; nhi = N[first + 1];
-            const bool gained = (hi - lo) * (P - 1) <= w * 1.0001;
-            guess = false;
-            if (GUESS && gained && nlo == k && nhi == k + 1 && flo * fhi < 0.0) {
-                // nodes outwards from the bracket, those between the neighbouring values only
-                double t[6], y[6], c[6];
-                const double wi = 1.0 / (hi - lo);
-                const int e0 = max(elo, ehi);
-                t[0] = 0.0; t[1] = 1.0;
-                y[0] = __builtin_amdgcn_ldexp(flo, elo - e0);
-                y[1] = __builtin_amdgcn_ldexp(fhi, ehi - e0);
-                int l = first, r = first + 1, nodes = 2;
-#pragma unroll
-                for (int j = 2; j < 6; ++j) {
-                    const int i = (j & 1) ? r + 1 : l - 1;
-                    const int ic = min(max(i, 0), P + 1);
-                    const double xi = X[ic], fi = Fv[ic];
-                    const bool use = nodes == j && i >= 0 && i <= P + 1 && fi == fi && fi != 0.0 &&
-                                     ((j & 1) ? (xi > X[r] && N[ic] == k + 1) : (xi < X[l] && N[ic] == k));
-                    t[j] = (xi - lo) * wi;
-                    y[j] = __builtin_amdgcn_ldexp(fi, min(max(E[ic] - e0, -1000), 500));
-                    if (use) {
-                        ++nodes;
-                        if (j & 1) r = i;
-                        else l = i;
-                    }
-                }
-                // divided differences
-#pragma unroll
-                for (int j = 0; j < 6; ++j) c[j] = y[j];
-#pragma unroll
-                for (int d = 1; d < 6; ++d)
-#pragma unroll
-                    for (int j = 5; j >= d; --j)
-                        if (j < nodes) c[j] = (c[j] - c[j - 1]) / (t[j] - t[j - d]);
-                double z0, z1;
-                if (nodes == 6) {
-                    z0 = interpolated_zero<6>(t, c, y[0], y[1]);
-                    z1 = interpolated_zero<4>(t, c, y[0], y[1]);
-                } else if (nodes >= 4) {
-                    z0 = interpolated_zero<4>(t, c, y[0], y[1]);
-                    z1 = interpolated_zero<3>(t, c, y[0], y[1]);
-                } else {
-                    z0 = y[0] / (y[0] - y[1]);
-                    z1 = z0 + z0 * (1.0 - z0);
-                }
-                const double wn = hi - lo, want = rel_tol * fmax(hi, floor_frac * hi0) + 1e-38 * hi0;
-                centre = fma(wn, z0, lo);
-                // (the next two nodes would change about d1 d1 / d2 more, d1 and d2 being what the last and the ones
-                // before them changed)
-                const double d1 = fabs(z0 - z1), d2 = fabs(z1 - y[0] / (y[0] - y[1]));
-                const double d = nodes >= 4 ? 0.5 * fmin(fmax(d1 * d1 / fmax(d2, 1e-300), d1 * (1.0 / 4096)), d1) : 0.25 * d1;
-                delta = fmax(wn * d, 0.45 * want);
-                guess = centre >= lo && centre <= hi && d1 < 0.05 && wn > (P + 1) * want;
+        return mine ? __builtin_ctzll(mine) : P;
+    };
+    const double frac = (double)(q + 1) / (P + 1);
+    if constexpr (!GUESS) {
+        for (int it = 0; it < 200; ++it) {
+            const bool open = is_open();
+            if (!__any(open)) break;            // wave-uniform exit: the row hand-over needs every lane
+            const double w = hi - lo, x = fmin(fmax(fma(w, frac, lo), lo), hi);
+            double f;
+            int fe;
+            const int first = first_above(x, sturm_count<false>(z, n, x, f, fe));
+            if (open) {
+                // (the same expressions the lanes first - 1 and first evaluated their points with)
+                const double nlo = first == 0 ? lo : fmin(fmax(fma(w, (double)first / (P + 1), lo), lo), hi);
+                const double nhi = first == P ? hi : fmin(fmax(fma(w, (double)(first + 1) / (P + 1), lo), lo), hi);
+                lo = nlo;
+                hi = nhi;
             }
         }
-        __syncthreads();
+    } else {
+        // the round's nodes of every value: 0 the interval's lower end, P + 1 its upper end
+        __shared__ double sx[VPW][P + 2], sf[VPW][P + 2];
+        __shared__ int se[VPW][P + 2], sc[VPW][P + 2];
+        double* const X = sx[grp];
+        double* const Fv = sf[grp];
+        int* const E = se[grp];
+        int* const N = sc[grp];
+        // the polynomial at the ends: NaN where not formed, 0 where not to be had
+        double flo = NAN, fhi = NAN;
+        int elo = 0, ehi = 0, nlo = gcnt[a], nhi = gcnt[b];
+        bool guess = false;
+        double centre = 0.0, delta = 0.0;
+        // this lane's offset from a guess, in units of delta: -G^(P/2-1) .. -1, 1 .. G^(P/2-1), G = 4, 16, 256
+        const int step = 32 / P * (q < P / 2 ? P / 2 - 1 - q : q - P / 2);
+        const double offset = __builtin_amdgcn_ldexp(q < P / 2 ? -1.0 : 1.0, step), frac_ends = (double)q / (P - 1);
+        // the polynomial at zero, (-1)^n d_1^2 d_2^2 .., by all lanes together
+        auto at_zero = [&](int& fe) -> double {
+            double p = 1.0;
+            int e = 0;
+            auto scaled = [&](double v) {
+                const int d = __builtin_amdgcn_frexp_exp(v);
+                p = __builtin_amdgcn_ldexp(v, -d);
+                e += d;
+            };
+            for (int64_t j = lane; j < n; j += kWave) scaled(p * z[2 * j + 1]);
+            for (int off = 32; off > 0; off >>= 1) {
+                const double p2 = __shfl_xor(p, off, kWave);
+                const int e2 = __shfl_xor(e, off, kWave);
+                scaled(p * p2);
+                e += e2;
+            }
+            fe = e;
+            return (n & 1) ? -p : p;
+        };
+        // intervals up to this many times the wanted width (one round, P = 4: two) are left to equal spacing
+        constexpr double kNear = P >= 8 ? P + 1.0 : (P + 1.0) * (P + 1.0);
+        for (int it = 0; it < 200; ++it) {
+            const bool open = is_open();
+            if (!__any(open)) break;
+            const double w = hi - lo, far = w * quick_rcp(kNear * wanted());
+            const bool alone = nlo == k && nhi == k + 1, at0 = open && alone && lo == 0.0 && flo != flo && far > P + 1;
+            if (__any(at0)) {
+                int e;
+                const double p = at_zero(e);
+                if (at0) { flo = p; elo = e; }
+            }
+            // equally spaced points inside the interval, or, where the polynomial at an end is still to be formed, with
+            // the ends
+            const bool known = flo + fhi == flo + fhi, useless = flo == 0.0 || fhi == 0.0;
+            const bool ends = alone && lo > 0.0 && !known && !useless && far > P - 1;
+            const double x = fmin(fmax(guess ? fma(delta, offset, centre) : fma(w, ends ? frac_ends : frac, lo), lo), hi);
+            const bool poly = guess || ends || ((alone ? !useless : it == 0 && nhi - nlo <= P) && far > P + 1);
+            double f = NAN;
+            int fe = 0;
+            const int64_t cnt = __any(open && poly) ? sturm_count<true>(z, n, x, f, fe) : sturm_count<false>(z, n, x, f, fe);
+            const int first = first_above(x, cnt);
+            X[q + 1] = x; Fv[q + 1] = f; E[q + 1] = fe; N[q + 1] = (int)min(cnt, n);
+            if (q == 0) {
+                X[0] = lo; Fv[0] = flo; E[0] = elo; N[0] = nlo;
+                X[P + 1] = hi; Fv[P + 1] = fhi; E[P + 1] = ehi; N[P + 1] = nhi;
+            }
+            __syncthreads();
+            if (open) {
+                lo = X[first]; flo = Fv[first]; elo = E[first]; nlo = N[first];
+                hi = X[first + 1]; fhi = Fv[first + 1]; ehi = E[first + 1]; nhi = N[first + 1];
+                const bool gained = (hi - lo) * (P - 1) <= w * 1.0001;
+                guess = false;
+                const double wn = hi - lo, want = wanted();
+                if (gained && nlo == k && nhi == k + 1 && flo * fhi < 0.0 && wn > kNear * want) {
+                    // nodes outwards from the bracket, those between the neighbouring values only
+                    double t[6], y[6], c[6];
+                    const double wi = quick_rcp(wn);
+                    const int e0 = max(elo, ehi);
+                    t[0] = 0.0; t[1] = 1.0;
+                    y[0] = __builtin_amdgcn_ldexp(flo, elo - e0);
+                    y[1] = __builtin_amdgcn_ldexp(fhi, ehi - e0);
+                    int l = first, r = first + 1, nodes = 2;
+#pragma unroll
+                    for (int j = 2; j < 6; ++j) {
+                        const int i = (j & 1) ? r + 1 : l - 1;
+                        const int ic = min(max(i, 0), P + 1);
+                        const double xi = X[ic], fi = Fv[ic];
+                        const bool use = nodes == j && i >= 0 && i <= P + 1 && fi == fi && fi != 0.0 &&
+                                         ((j & 1) ? (xi > X[r] && N[ic] == k + 1) : (xi < X[l] && N[ic] == k));
+                        t[j] = (xi - lo) * wi;
+                        y[j] = __builtin_amdgcn_ldexp(fi, min(max(E[ic] - e0, -1000), 500));
+                        if (use) {
+                            ++nodes;
+                            if (j & 1) r = i;
+                            else l = i;
+                        }
+                    }
+                    // divided differences
+#pragma unroll
+                    for (int j = 0; j < 6; ++j) c[j] = y[j];
+#pragma unroll
+                    for (int d = 1; d < 6; ++d)
+#pragma unroll
+                        for (int j = 5; j >= d; --j)
+                            if (j < nodes) c[j] = (c[j] - c[j - 1]) * quick_rcp(t[j] - t[j - d]);
+                    const double zs = y[0] * quick_rcp(y[0] - y[1]);
+                    double z0, z1;
+                    if (nodes == 6) {
+                        z0 = interpolated_zero<6>(t, c, y[0] < 0.0, zs);
+                        z1 = interpolated_zero<4>(t, c, y[0] < 0.0, zs);
+                    } else if (nodes >= 4) {
+                        z0 = interpolated_zero<4>(t, c, y[0] < 0.0, zs);
+                        z1 = interpolated_zero<3>(t, c, y[0] < 0.0, zs);
+                    } else {
+                        z0 = zs;
+                        z1 = z0 + z0 * (1.0 - z0);
+                    }
+                    centre = fma(wn, z0, lo);
+                    // (the next two nodes would change about d1 d1 / d2 more, d1 and d2 being what the last and the ones
+                    // before them changed)
+                    const double d1 = fabs(z0 - z1), d2 = fabs(z1 - zs);
+                    const double d = nodes >= 4 ? 0.5 * fmin(fmax(d1 * d1 * quick_rcp(fmax(d2, 1e-300)), d1 * (1.0 / 4096)), d1) : 0.25 * d1;
+                    delta = fmax(wn * d, 0.45 * want);
+                    guess = centre >= lo && centre <= hi && d1 < 0.05;
+                }
+            }
+            __syncthreads();
+        }
     }
     if (kraw < n && q == 0) sigma[n - 1 - k] = (C)(0.5 * (lo + hi) * scale);
 }
