@@ -483,8 +483,15 @@ int run_bdsvals_dev(int64_t n, const C* d, const C* e, C* sigma, void* work, dou
         hipLaunchKernelGGL(kern, dim3((unsigned)((n + vpw - 1) / vpw)), dim3(64), 0, s, ws, n, sigma, rel_tol, floor_frac,
                            gcnt);
     };
-    // (four points at least to interpolate, and rows enough that a round costs more than the interpolation)
-    const bool guess = n >= kMinGuess;
+    // Guessed rounds need four points at least to interpolate, rows enough that a round costs more than the
+    // interpolation, and rounds enough to save some: a wave goes on until the last of its values is done, so where equal
+    // spacing takes five rounds a single guess that misses costs what the others gained.  Time with guesses over time
+    // without, Gaussian / log-uniform / graded bidiagonals, n = 500 .. 32768, by the width asked for, relative to every value:
+    // 2^-20 .75 - .98 / 1.0 - 1.2 / .96 - 1.1; 2^-29 .72 - .82 / .89 - .99 / .87 - .93 (n > 16384, four points: .96 / 1.05
+    // / .99); 2^-37 .62 - .80 / .80 - .93 / .79 - .93; 2^-52 .65 - .85 / .70 - .87 / .75 - .90; relative to an eighth of the
+    // bound at least: 2^-29 .86 - 1.07 / 1.0 - 1.14 / 1.1 - 1.2; 2^-37 .77 - .89 / .86 - .98 / 1.06 - 1.11; 2^-52 .66 - .92 /
+    // .70 - .98 / .87 - 1.1.  Tight clusters gain nothing and lose up to 1.19 (2^-29, 2^-37), 1.06 (2^-52).
+    const bool guess = n >= kMinGuess && (rel_tol <= 0x1p-36 || (rel_tol <= 0x1p-28 && floor_frac == 0.0 && p >= 8));
     if (p >= 16) guess ? launch(bd_multisect_kernel<C, 16, true>, 16) : launch(bd_multisect_kernel<C, 16, false>, 16);
     else if (p >= 8) guess ? launch(bd_multisect_kernel<C, 8, true>, 8) : launch(bd_multisect_kernel<C, 8, false>, 8);
     else if (p >= 4) guess ? launch(bd_multisect_kernel<C, 4, true>, 4) : launch(bd_multisect_kernel<C, 4, false>, 4);
