@@ -483,12 +483,14 @@ __device__ __forceinline__ void apply_tile(C* base, int es, int ls, int nvalid, 
 // (columns) the lanes of an access fall into.  Eight lanes per line, two rounds of eight lines, V re-read from LDS for
 // every line, took 35 us for the rows of a step of the in-band kernel (f64, B = 128), 10 so; the columns are at 14 in
 // both.  The reduction at n = 8192: 124 -> 86 ms.
+// Two partial sums in the first product: against one 101.6 -> 99.9 ms (both phases, n = 8192) and 2 % less error; four
+// 102.3 ms.
 template <typename C, int B, int D>
 __device__ __forceinline__ void apply_tile_g(C* p, int64_t es, int64_t ls, int nvalid, int ne, const C* Vs, const C* Ts)
 {
     using F = Frag<C>;
     typedef typename F::acc_t acc_t;
-    constexpr int NTL = B / 16;
+    constexpr int NTL = B / 16, NP = 2;   // partial sums of the first product
     int lane = threadIdx.x & 63;
     asm volatile("" : "+v"(lane));
     const int i = lane & 15, gq = lane >> 4, j = i & 7;
@@ -518,13 +520,19 @@ __device__ __forceinline__ void apply_tile_g(C* p, int64_t es, int64_t ls, int n
                 q += r < 3 ? e1 : e2;
             }
     }
-    acc_t w, z;
+    acc_t w, z, part[NP];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) { w[r] = 0; z[r] = 0; }
+    for (int r = 0; r < 4; ++r) {
+        z[r] = 0;
+#pragma unroll
+        for (int q = 0; q < NP; ++q) part[q][r] = 0;
+    }
 #pragma unroll
     for (int a = 0; a < NTL; ++a)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) w = F::mma(Vs[vidx<B, D>(16 * a + F::roff(r, gq)) + j], y[a][r], w);
+        for (int r = 0; r < 4; ++r) part[r % NP] = F::mma(Vs[vidx<B, D>(16 * a + F::roff(r, gq)) + j], y[a][r], part[r % NP]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w[r] = part[0][r] + part[1][r];
 #pragma unroll
     for (int r = 0; r < 2; ++r) z = F::mma(-Ts[F::roff(r, gq) * D + j], w[r], z);
 #pragma unroll
@@ -588,20 +596,31 @@ template <typename C, int B, int LDV> struct BlockRefl {
         v1 = s1 * LDV + i;
         asm volatile("" : "+v"(o1), "+v"(t0), "+v"(t1), "+v"(v0), "+v"(v1));
     }
-    // p = V^T y
+    // p = V^T y.  In f32 four partial sums: with one, the error of the whole reduction was larger by 3, 7 and 7 % (nb =
+    // 32, 64, 128; n = 600, mean of 48 bands), for the same time; in f64 they cost 0.4 (two) to 4 % for an error within
+    // the means' spread of 3 %.
     __device__ __forceinline__ acc_t inner(const C* V, const acc_t (&y)[NTL]) const
     {
-        acc_t p;
+        constexpr int NP = sizeof(C) == 4 ? 4 : 1;
+        acc_t p[NP];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) p[r] = 0;
+        for (int q = 0; q < NP; ++q)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) p[q][r] = 0;
 #pragma unroll
         for (int a = 0; a < NTL; ++a) {
             C v[4];
             Frag<C>::ld4(V + o1 + 16 * a, 0, v);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) p = Frag<C>::mma(v[r], y[a][r], p);
+            for (int r = 0; r < 4; ++r) p[r % NP] = Frag<C>::mma(v[r], y[a][r], p[r % NP]);
         }
-        return p;
+#pragma unroll
+        for (int w = NP; w > 1; w /= 2)
+#pragma unroll
+            for (int q = 0; q < w / 2; ++q)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) p[q][r] += p[q + w / 2][r];
+        return p[0];
     }
     // z = -T^T p in registers 0 and 1; lines that are not `on` get zero
     __device__ __forceinline__ acc_t middle(const C* T, const acc_t& p, bool on) const
