@@ -1349,9 +1349,10 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
                 } else {
                     const int nrow = (int)min((int64_t)B, n - c0);
                     const int64_t cg = c0 + B + 16 * (wv - 8);
-                    apply_tile_g<C, B, D>(band + (c0 - cg + ku) + cg * ldab, 1, ldm1, (int)max((int64_t)0, min((int64_t)16, n - cg)),
-                                          nrow, Vs, Ts);
-                    stores_done();
+                    if (cg < n) {   // (none of the sixteen inside, as in all of a sweep's last step: most of the work at n <= 136)
+                        apply_tile_g<C, B, D>(band + (c0 - cg + ku) + cg * ldab, 1, ldm1, (int)min((int64_t)16, n - cg), nrow, Vs, Ts);
+                        stores_done();
+                    }
                 }
             }
             lds_barrier();
