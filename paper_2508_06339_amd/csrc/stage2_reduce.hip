@@ -29,6 +29,7 @@
 // 50 -> 31.8 (128); f64 16.5 -> 11.1 (32), 29.3 -> 18.4 (64).
 //
 // Packed band: entry (i,j) at band[(i - j + ku) + j*ldab], ku = 2B-1, ldab >= 3B.
+#include <type_traits>
 #include <utility>
 
 #include "svb_internal.h"
@@ -661,7 +662,8 @@ template <typename C, int B> struct ReduceShape {
     static constexpr int PER = RG * 16 / CG;                   // accesses
 };
 
-template <typename C, int B>
+// WIDE: lane offsets into a block of up to 15 columns do not fit 32 bits.
+template <typename C, int B, bool WIDE>
 __global__ __launch_bounds__((ReduceShape<C, B>::NT)) void band_reduce_kernel(C* __restrict__ band, int64_t ldab, int64_t n,
                                                                              int* __restrict__ ctrl,
                                                                              int* __restrict__ progress, int spin_limit)
@@ -721,7 +723,9 @@ __global__ __launch_bounds__((ReduceShape<C, B>::NT)) void band_reduce_kernel(C*
     asm volatile("" : "+v"(me.lrow), "+v"(me.rrow), "+v"(me.lcol), "+v"(me.rcol));
     BlockRefl<C, B, LDV> refl;
     refl.init(me.i, me.gq);
-    const int ldm1 = (int)(ldab - 1);
+    using Ld = std::conditional_t<WIDE, int64_t, int>;
+    using Off = std::conditional_t<WIDE, int64_t, unsigned>;
+    const Ld ldm1 = (Ld)(ldab - 1);
     const int64_t ku = 2 * (int64_t)B - 1;
     const int64_t nsweeps = (n - 1) / D;
 #ifdef SVB_CHASE_TIMING
@@ -774,12 +778,12 @@ __global__ __launch_bounds__((ReduceShape<C, B>::NT)) void band_reduce_kernel(C*
     auto entry = [&](int64_t r0, int64_t cb, int col) -> char* {
         return reinterpret_cast<char*>(band + ((r0 - cb + ku) + cb * ldab) + (int64_t)col * ldm1);
     };
-    auto at = [](char* p, unsigned off) -> C* { return reinterpret_cast<C*>(p + off); };
+    auto at = [](char* p, Off off) -> C* { return reinterpret_cast<C*>(p + off); };
     // (entries outside the matrix, or above row `from`, are not touched and read as zero)
     auto load_cols = [&](C (&pre)[PER], int64_t r0, int64_t cb, int k0, int k1, int from) {
         const bool full = r0 + B <= n && cb + B <= n && from == 0;
         const int nrow = (int)min((int64_t)B, n - r0), ncol = (int)max((int64_t)0, min((int64_t)B, n - cb));
-        const unsigned off = (unsigned)(me.mrow + me.mcol * ldm1) * (unsigned)sizeof(C);
+        const Off off = (Off)(me.mrow + me.mcol * ldm1) * (Off)sizeof(C);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int kc = h ? k1 : k0;
@@ -814,7 +818,7 @@ __global__ __launch_bounds__((ReduceShape<C, B>::NT)) void band_reduce_kernel(C*
     auto store_cols = [&](const C* src, int64_t r0, int64_t cb, int k0, int k1) {
         const bool full = r0 + B <= n && cb + B <= n;
         const int nrow = (int)min((int64_t)B, n - r0), ncol = (int)min((int64_t)B, n - cb);
-        const unsigned off = (unsigned)(me.mrow + me.mcol * ldm1) * (unsigned)sizeof(C);
+        const Off off = (Off)(me.mrow + me.mcol * ldm1) * (Off)sizeof(C);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int kc = h ? k1 : k0;
@@ -1011,7 +1015,7 @@ __global__ __launch_bounds__((ReduceShape<C, B>::NT)) void band_reduce_kernel(C*
                     for (int r = 0; r < 4; ++r) {
                         const int col = F::roff(r, me.gq);
                         if (j >= 0 && j < D && col < D && c0 + col < n)
-                            rgst(at(p, (unsigned)(me.rline + col * ldm1) * (unsigned)sizeof(C)), rr[0][r]);
+                            rgst(at(p, (Off)(me.rline + col * ldm1) * (Off)sizeof(C)), rr[0][r]);
                     }
                 }
                 lds_barrier();
@@ -1034,7 +1038,7 @@ __global__ __launch_bounds__((ReduceShape<C, B>::NT)) void band_reduce_kernel(C*
                         }
                         // (straight from the registers: sixteen consecutive rows a column)
                         char* p = entry(c0 - B, c0, 0);
-                        const unsigned off = (unsigned)(me.rline + F::roff(0, me.gq) * ldm1) * (unsigned)sizeof(C);
+                        const Off off = (Off)(me.rline + F::roff(0, me.gq) * ldm1) * (Off)sizeof(C);
                         const bool full = t > 0 && c0 + B <= n;
                         const int ncol = (int)min((int64_t)B, n - c0) - F::roff(0, me.gq);
                         if (full) {
@@ -1091,7 +1095,7 @@ __global__ __launch_bounds__((ReduceShape<C, B>::NT)) void band_reduce_kernel(C*
                     for (int r = 0; r < 4; ++r) {
                         const int row = F::roff(r, me.gq);
                         if (me.rline < D && row < D && c0 + row < n && c0 + me.rline < n)
-                            rgst(at(p, (unsigned)(row + me.rline * ldm1) * (unsigned)sizeof(C)), cr[0][r]);
+                            rgst(at(p, (Off)(row + me.rline * ldm1) * (Off)sizeof(C)), cr[0][r]);
                     }
                 }
                 lds_barrier();
@@ -1397,19 +1401,21 @@ int launch_band_reduce(int64_t n, C* band, int64_t ldab, int* ctrl, hipStream_t 
     void (*kern)(C*, int64_t, int64_t, int*, int*, int);
     size_t smem;
     int nt;
+    const bool wide = !inband && ldab > ((int64_t)1 << 26);
     if constexpr (inband) {
         kern = band_reduce_inband_kernel<C, B, D>;
         smem = sizeof(C) * (size_t)(((B * (B + 1) + 3) & ~3) + (B + 4) * D + D * D);
         nt = InbandShape<B>::NT;
     } else {
-        kern = band_reduce_kernel<C, B>;
+        // (offsets of 32 bits: 7 columns of f64, 12 of f32 from the first of a block are less than 2^32 bytes away)
+        kern = wide ? band_reduce_kernel<C, B, true> : band_reduce_kernel<C, B, false>;
         smem = ReduceShape<C, B>::kSmemBytes;
         nt = ReduceShape<C, B>::NT;
     }
-    static bool attr_set = false;
-    if (!attr_set) {
+    static bool attr_set[2] = {false, false};
+    if (!attr_set[wide]) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        attr_set = true;
+        attr_set[wide] = true;
     }
     const int64_t nsweeps = (n - 1) / D;
     const int64_t count = 64 + nsweeps * kProgressStride;

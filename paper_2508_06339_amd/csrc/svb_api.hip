@@ -86,10 +86,10 @@ size_t gb2bd_bytes(int64_t n, int nb)
 }
 
 // two-phase stage 2 (band -> 8 super-diagonals -> bidiagonal) unless switched off or unsupported
-// (the band reduction's lane offsets into a block are 32-bit: a leading dimension beyond 2^26 takes the one-phase chase)
+// (the band reduction's in-band form keeps the leading dimension in 32 bits: beyond 2^31 the one-phase chase is taken)
 bool two_phase(int nb, size_t elem_size, int64_t n, int64_t ldab)
 {
-    return nb != 8 && n >= 3 && ldab <= ((int64_t)1 << 26) && env_int("SVB_CHASE_IMPL", 2) == 2 && band_reduce_supported(nb, elem_size);
+    return nb != 8 && n >= 3 && ldab <= ((int64_t)1 << 31) && env_int("SVB_CHASE_IMPL", 2) == 2 && band_reduce_supported(nb, elem_size);
 }
 
 // Algorithmic bytes of the two stage-2 kernels: the band reduction reads and writes every nb x nb
