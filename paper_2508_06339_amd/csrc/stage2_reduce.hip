@@ -276,8 +276,11 @@ template <typename C> __device__ __forceinline__ void panel_rest(const PanelTail
         t[K] = fma(-tail.g[K], acc[K], ln == K ? tail.g[K] : (C)0);   // (acc is zero in lines K and on)
         if constexpr (K < 7) row_lane_columns<K>(acc, tail.c, t[K]);
     }, std::make_integer_sequence<int, 8>{});
-    const C x2 = fma(tail.alpha, tail.alpha, tail.ss) + LineRange<C>::floor;
-    const C beta = tail.ss < LineRange<C>::least ? tail.alpha : -copysign(newton_sqrt(x2), tail.alpha);
+    // (times 16 under the root: where u^T u, up to four times this, may be beyond the quarter of the range that the
+    // reciprocal instruction does not answer with zero, the factor becomes a NaN.  Lines of entries whose squares do not sum
+    // up inside the type's range get there; with a zero the reflector was left out and finite, wrong values came out.)
+    const C x2 = (fma(tail.alpha, tail.alpha, tail.ss) + LineRange<C>::floor) * 16;
+    const C beta = tail.ss < LineRange<C>::least ? tail.alpha : -copysign((C)0.25 * newton_sqrt(x2), tail.alpha);
     if (lane < 8) {
 #pragma unroll
         for (int k = 0; k < 8; k += NV) {
