@@ -122,7 +122,10 @@ template <int K> __device__ __forceinline__ double row_lane(double v)
 // Multiply-adds whose first factor is the value of lane K of the lane's row of sixteen, taken as the operand is
 // read: p[i mod 4] = sum of row_lane<K>(x[i]) x[i], and x[i] += row_lane<K>(x[i]) w.  (The compiler makes a move
 // and a multiply-add of these.  An operand that is read across lanes may not have been written by the last two
-// vector instructions: two wait states in front; inside a group of eight nothing that was written is read so.)
+// vector instructions: two wait states in front; inside a group of eight nothing that was written is read so.  The
+// compiler does not see what a group writes, so behind it the caller has to keep the same distance: the results go
+// through an ordinary vector instruction or another of these groups before a lane operation (permlane, readlane, a
+// data-parallel move) reads them.)
 #define SVB_BCAST " row_mask:0xf bank_mask:0xf\n\t"
 #define SVB_DOT8(T, FIRST, C0)                                                                             \
     asm("s_nop 1\n\t"                                                                                      \

@@ -25,8 +25,8 @@
 // all traffic with the band, run beside the next panel.  Per step the workgroup holds the upper block U (rows
 // c0-B .., the previous step's A3) and Z in LDS; every block is read once and written once per sweep.
 // us per eight columns (one sweep), n = 8192, before (each block reflector in one piece between the panels,
-// applied from LDS line by line; whole blocks published) -> now: f32 13.5 -> 8.6 (nb = 32), 20.8 -> 13.2 (64),
-// 50 -> 31.8 (128); f64 16.5 -> 11.1 (32), 29.3 -> 18.4 (64).
+// applied from LDS line by line; whole blocks published) -> now: f32 13.5 -> 8.7 (nb = 32), 20.8 -> 13.5 (64),
+// 50 -> 32.0 (128); f64 16.5 -> 11.2 (32), 29.3 -> 18.5 (64).
 //
 // Packed band: entry (i,j) at band[(i - j + ku) + j*ldab], ku = 2B-1, ldab >= 3B.
 #include <type_traits>
@@ -75,10 +75,6 @@ template <typename C> __device__ __forceinline__ void rgst(C* p, C v)
 }
 
 // value of lane (l ^ pattern) through the data-parallel-primitive path (no LDS traffic)
-template <int CTRL> __device__ __forceinline__ float dpp_get(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
 template <int CTRL> __device__ __forceinline__ double dpp_get(double v)
 {
     const long long b = __builtin_bit_cast(long long, v);
@@ -92,13 +88,8 @@ constexpr int kDppHalfMirror = 0x141; // lane i <-> 7-i inside groups of 8
 
 constexpr int kDppRor8 = 0x128;       // lane i <-> i^8 inside rows of 16 (rotate by 8)
 
-__device__ __forceinline__ float rrcp(float x)
-{
-    // hardware reciprocal (1 ulp, biased) refined by one Newton step: a biased tau or scale
-    // makes every reflector slightly non-orthogonal in the same direction, which adds up
-    const float r = __builtin_amdgcn_rcpf(x);
-    return fmaf(r, fmaf(-x, r, 1.0f), r);
-}
+// hardware reciprocal refined by Newton steps: a biased tau or scale makes every reflector slightly non-orthogonal in
+// the same direction, which adds up
 __device__ __forceinline__ double rrcp(double x)
 {
     double r = __builtin_amdgcn_rcp(x);
@@ -299,9 +290,10 @@ template <typename C> __device__ __forceinline__ void panel_rest(const PanelTail
 
 // The same factorisation with a lane per element (every 64th of all eight lines): eight sums over the
 // wave per reflector.  Kept for the in-band form of the kernel (two blocks do not fit in LDS: f64 at
-// B = 128), whose 128 registers a lane the form above does not fit beside the lines: 16.9 against
-// 15.4 us a column for the whole reduction.  It does not move tiny lines either (every form of it that
-// did spilled more: 15.7 to 17.0): its reflectors are orthogonal to 2^-1075 / ss, so lines of entries below
+// B = 128), which has 128 registers a lane: an earlier form of the factorisation above did not fit beside the lines that the
+// apply waves then held (16.9 against 15.4 us a column for the whole reduction, before the tiles of apply_tile_g; it is at
+// 10.5 now and the present form has not been tried in it).  It does not move tiny lines either (every form of it that
+// did spilled more: 15.7 to 17.0 then): its reflectors are orthogonal to 2^-1075 / ss, so lines of entries below
 // about 2^-515 (f64) are reduced to the accuracy of their own squares, and so is what they are applied to.
 // Sums of eight per-lane values over the 64 lanes of a wave, as wave-uniform scalars.
 // The first three stages halve the number of values while doubling the lanes summed
@@ -601,7 +593,7 @@ template <typename C, int B, int LDV> struct BlockRefl {
         asm volatile("" : "+v"(o1), "+v"(t0), "+v"(t1), "+v"(v0), "+v"(v1));
     }
     // p = V^T y.  In f32 four partial sums: with one, the error of the whole reduction was larger by 3, 7 and 7 % (nb =
-    // 32, 64, 128; n = 600, mean of 48 bands), for the same time; in f64 they cost 0.4 (two) to 4 % for an error within
+    // 32, 64, 128; n = 600, mean of 48 bands), for the same time (nb = 64: 1 to 2 % more up to n = 200, 0.1 at 8192); in f64 they cost 0.4 (two) to 4 % for an error within
     // the means' spread of 3 %.
     __device__ __forceinline__ acc_t inner(const C* V, const acc_t (&y)[NTL]) const
     {
@@ -1127,18 +1119,18 @@ __global__ __launch_bounds__((ReduceShape<C, B>::NT)) void band_reduce_kernel(C*
 
 // The in-band form, where two blocks do not fit in LDS (f64 at B = 128): only the diagonal block Z lives in
 // LDS, the upper block U and the block right of Z are transformed where they lie, in the packed band in
-// device memory.  8*B apply threads, wave 0 of which factors the panels.  Blocks are moved
+// device memory.  8*B apply threads, wave 0 of which factors the panels.  Z is moved
 // by "traffic" waves, each lane keeping one block row: a wave covers 64 consecutive rows of
-// CPG columns at a time and steps through the columns with a fixed stride, so that its
+// a column at a time and steps through the columns with a fixed stride, so that its
 // addresses are a scalar base, advanced by a scalar per step, plus a fixed lane offset.
 template <int B> struct InbandShape {
+    static_assert(B >= kWave, "whole groups of 64 rows a column");
     static constexpr int NT = 8 * B;
     static constexpr int NWV = NT / kWave;
     static constexpr int PWV = 0;                                 // the panel wave
-    static constexpr int GPC = B >= kWave ? B / kWave : 1;        // 64-row groups per block column
-    static constexpr int CPG = B >= kWave ? 1 : kWave / B;        // block columns per wave access
-    static constexpr int NTW = (NWV - 1) / GPC * GPC;             // waves that move blocks
-    static constexpr int JS = NTW / GPC * CPG;                    // column step of a traffic wave
+    static constexpr int GPC = B / kWave;                         // 64-row groups per block column
+    static constexpr int NTW = (NWV - 1) / GPC * GPC;             // waves that move Z
+    static constexpr int JS = NTW / GPC;                          // column step of a traffic wave
     static constexpr int PER = (B + JS - 1) / JS;                 // accesses per traffic wave and block
 };
 
@@ -1148,9 +1140,8 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
                                                                         int* __restrict__ progress, int spin_limit)
 {
     // The panel wave draws the sweep, waits for the predecessor, factors the two panels of a
-    // step and publishes progress.  The traffic waves move the blocks between device memory
-    // and LDS.  The panel wave's work overlaps the traffic: the right panel of step t with the
-    // write-back of Z of step t-1, the left panel with the write-back of U.
+    // step and publishes progress.  The traffic waves move Z between device memory
+    // and LDS; the right panel of step t runs beside the exchange of step t-1's Z for this step's.
     using SH = InbandShape<B>;
     static_assert(SH::NT == 1024 && sizeof(C) == 8, "waves 0-7 on LDS lines, waves 8-15 on band lines, sixteen each; Frag of f64");
     constexpr int LD = B + 1, PER = SH::PER, JS = SH::JS;
@@ -1166,8 +1157,8 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
     const int tw = wv - 1;                       // index among the traffic waves
     const bool traffic = !pw && tw < SH::NTW;
     // this lane's block row and first block column
-    const int ii = (tw % SH::GPC) * kWave + (B >= kWave ? lane : lane % B);
-    const int jj0 = (tw / SH::GPC) * SH::CPG + (B >= kWave ? 0 : lane / B);
+    const int ii = (tw % SH::GPC) * kWave + lane;
+    const int jj0 = tw / SH::GPC;
     const int ldm1 = (int)(ldab - 1);
     const int64_t ku = 2 * (int64_t)B - 1;
 #ifdef SVB_CHASE_TIMING
@@ -1192,8 +1183,8 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
     // lds0 + q*JS*LD in LDS; loads of elements outside the matrix read the band's first entry
     // and are masked where the value is consumed (masking at once would wait for the load)
     auto inside = [&](const Blk& k, int q) -> bool { return ii < k.nrow && jj0 + q * JS < k.ncol; };
-    auto gload = [&](const Blk& k, int q, bool also) -> C {
-        const C* p = (inside(k, q) && also) ? k.p + (int64_t)(q * JS) * ldm1 : band;
+    auto gload = [&](const Blk& k, int q) -> C {
+        const C* p = inside(k, q) ? k.p + (int64_t)(q * JS) * ldm1 : band;
         return rgld(p);
     };
     auto gstore = [&](const Blk& k, int q, C v) { rgst(k.p + (int64_t)(q * JS) * ldm1, v); };
@@ -1259,12 +1250,12 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
         __syncthreads();
         bool failed = sh_fail != 0;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        C pre[PER];   // traffic waves: A3 of the step, then Z of the next one
+        C pre[PER];   // traffic waves: the next Z
         if (!failed && traffic) {
             const Blk zb = block_at(c00, c00);
             const int lds0 = ii + jj0 * LD;
 #pragma unroll
-            for (int q = 0; q < PER; ++q) pre[q] = gload(zb, q, true);
+            for (int q = 0; q < PER; ++q) pre[q] = gload(zb, q);
 #pragma unroll
             for (int q = 0; q < PER; ++q) {
                 if (jj0 + q * JS < B) S[lds0 + q * JS * LD] = inside(zb, q) ? pre[q] : (C)0;
@@ -1275,7 +1266,6 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
         int seen_next = 0;   // the predecessor's progress as polled during the previous step's last phase
         for (int t = 0; t < nsteps && !failed; ++t) {
             const int64_t c0 = c00 + (int64_t)t * B;
-            const int xoff = (t == 0) ? B - D : 0;
             // opaque per-step copy: without it every LDS index below is hoisted out of the step
             // loop and held in (spilled) registers
             int lds0 = ii + jj0 * LD;
@@ -1301,7 +1291,7 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
                 // in-band applies, which need theirs), the previous Z goes back meanwhile
                 const Blk zp = block_at(c0 - B, c0 - B), zc = block_at(c0, c0);
 #pragma unroll
-                for (int q = 0; q < PER; ++q) pre[q] = gload(zc, q, true);
+                for (int q = 0; q < PER; ++q) pre[q] = gload(zc, q);
 #pragma unroll
                 for (int q = 0; q < PER; ++q)
                     if (inside(zp, q)) gstore(zp, q, S[lds0 + q * JS * LD]);
@@ -1318,7 +1308,6 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
             stores_done();
             lds_barrier();
             RMARK(1);
-            RMARK(2);
             // ---- S3: block reflector onto the rows below X
             {
                 // (waves 0 .. 7: the rows of Z, in LDS; waves 8 .. 15: rows D .. B-1 of U, in the band; none in the
@@ -1332,12 +1321,12 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
                 }
             }
             lds_barrier();
-            RMARK(3);
+            RMARK(2);
             publish(s, 2 * t + 1);   // U was transformed where it lies; the stores are acknowledged
-            // ---- S4: left panel (QR of Z's first D columns)  ||  A3 requested, U back, A3 in
+            // ---- S4: left panel (QR of Z's first D columns)
             const int seen2 = poll(s);
             if (pw) panel_wave_spread<C, B, D, false>(S, LD, 1, Vs, Ts, B);
-            RMARK(4);
+            RMARK(3);
             lds_barrier();
             // the block right of Z (transformed where it lies in S5) was last touched by the right
             // half of the predecessor's step t+2, whose result is that step's upper block
@@ -1345,7 +1334,7 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
             lds_barrier();
             failed = sh_fail != 0;
             if (failed) break;
-            RMARK(5);
+            RMARK(4);
             seen_next = poll(s);
             // ---- S5: block reflector onto the other columns of Z and onto A3
             {
@@ -1363,7 +1352,7 @@ __global__ __launch_bounds__(InbandShape<B>::NT) void band_reduce_inband_kernel(
                 }
             }
             lds_barrier();
-            RMARK(6);
+            RMARK(5);
         }
         // ---- epilogue: the last step's Z back (nothing is right of it)
         if (!failed && traffic) {

@@ -206,8 +206,8 @@ void launch_extract_bidiag(const C* band, int64_t ldab, int64_t n, int b, C* d, 
 template <typename C>
 int run_chase_narrow(int64_t n, C* band, int64_t ldab, int64_t ku, int* ctrl, int* spread, hipStream_t s);
 size_t chase_narrow_workspace_bytes(int64_t n);
-// band of nb super-diagonals -> band of 8 (blocked chase, same storage); false / SVB_ERR_UNSUPPORTED
-// where two nb x nb blocks do not fit in LDS
+// band of nb super-diagonals -> band of 8 (blocked chase, same storage); false / SVB_ERR_UNSUPPORTED for other nb
+// than 32, 64, 128
 bool band_reduce_supported(int nb, size_t elem_size);
 template <typename C>
 int run_band_reduce(int64_t n, int nb, C* band, int64_t ldab, int* ctrl, hipStream_t s);
