@@ -48,3 +48,18 @@ def test_make_small_variants_and_fingerprint():
     a1, info1 = workloads.make("c1")
     assert a1.dtype == np.float64 and info1["nb"] == 32
     assert abs(np.sum(a1.astype(np.float64) ** 2) / 256 ** 2 - 1) < 0.02
+
+
+def test_counter_summaries_hold_the_kernels_the_benchmark_looks_for():
+    # each committed traffic summary names stage 2's two kernels once (whichever form of them ran)
+    import glob
+    import json
+    import os
+
+    import bench
+    files = glob.glob(os.path.join(os.path.dirname(os.path.abspath(bench.__file__)), "profiles", "hbm_traffic_*.json"))
+    assert files
+    for f in files:
+        names = [k for k in json.load(open(f)) if not k.startswith("_")]
+        for prefix in bench.STAGE2_KERNELS:
+            assert sum(n.startswith(prefix) for n in names) == 1, (f, prefix)
