@@ -5,9 +5,10 @@
 //
 // Same scheme as stage1_fused.hip (W = Y_d^T C, then C -= V_d W, the block C_d[:, strip] resident
 // in accumulator registers, Y_d and V_d streamed through LDS), rebuilt around
-// v_mfma_f32_32x32x2_f32: on this machine a wave issues the 16 x 16 x 4 f32 instruction at no more
-// than 80 % of the matrix pipe's rate and two waves per SIMD reach 80 % of the nominal peak, the
-// 32 x 32 x 2 instruction 97 % (measured with register-only loops).  A 32 x 32 accumulator tile
+// v_mfma_f32_32x32x2_f32: on this machine a lone wave fills the matrix pipe with it (97 % of the nominal
+// peak), while the 16 x 16 x 4 f32 instruction needs several independent accumulators for that (62, 87,
+// 92, 95 % with 1, 2, 4, 8; register-only loops).  Stand-alone on a 32768 x 32768 trailing matrix 131
+// against 111 TFLOP/s.  A 32 x 32 accumulator tile
 // costs 16 registers, so a wave cannot hold 512 rows by 32 columns; the workgroup's block
 // (512 rows, 64 columns) is split 2 x 2 instead: wave (rh, ch) keeps rows 256 rh .. 256 rh + 255,
 // columns 32 ch .. 32 ch + 31 as eight tiles (128 registers).

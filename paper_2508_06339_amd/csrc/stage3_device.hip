@@ -276,6 +276,9 @@ __device__ __forceinline__ double interpolated_zero(const double (&t)[6], const 
 // had them took 3.3 times as long as equal spacing on singular matrices (0.44 -> 1.59 ms at n = 700) and up to 1.4 times on
 // tight clusters.
 // Values that share an interval see the same points, those that do not are in order already: they come out in order.
+// Bidiagonal of a Gaussian matrix, ms with equal spacing only -> with guesses (whole stage): f64 n = 500 0.145 -> 0.107,
+// n = 6000 (10 -> 5 rounds) 2.35 -> 1.53, n = 20000 13.5 -> 8.4; f32 n = 6000 (5 -> 3) 1.32 -> 1.03.  What is left at n = 6000 is a
+// wave and a half per SIMD, the last of which take seven rounds.
 template <typename C, int P, bool GUESS>
 __global__ __launch_bounds__(64) void bd_multisect_kernel(const double* __restrict__ ws, int64_t n,
                                                            C* __restrict__ sigma, double rel_tol,

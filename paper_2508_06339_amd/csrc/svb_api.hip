@@ -30,12 +30,10 @@ bool nb_ok(int nb) { return nb == 32 || nb == 64 || nb == 128; }
 // hardware, Section 4 and Table 3).  From timings of svb_svdvals on MI355X at orders 1024 .. 32768:
 // small tiles shorten the panel chain and stage 2, large tiles raise the arithmetic intensity of
 // the trailing update, which only pays once the update dominates.  In f32 arithmetic nb = 64 is
-// fastest from order 1024 up to about 30000 (16384: 276 ms against 325 ms at nb = 128), nb = 128
-// beyond (32768: 1389 ms against 1413 ms); in f64, where a register-resident domain holds half as
-// many rows, nb = 32 up to about 5000 (4096: 45.4 ms against 46.4 ms at nb = 64) and nb = 64 beyond
-// (8192: 128 ms against 134 ms, 16384: 519 ms against 799 ms at nb = 128).  The thresholds below are
-// those of earlier kernels: 1 % above the fastest in f32 from 26624 to 30000, 2 to 4 % in f64
-// from 2560 to 5000.
+// fastest from order 1024 up to 20480 (16384: 259 ms against 287 ms at nb = 128), the two are equal at 24576
+// (659 ms) and nb = 128 is faster beyond (28672: 937 ms against 971 ms, 32768: 1307 against 1372); in f64, where
+// a register-resident domain holds half as many rows, nb = 32 up to 2048 (17.2 ms against 17.9 ms at nb = 64)
+// and nb = 64 from 3072 on (28.5 against 28.7; 8192: 115 against 125; 16384: 490 ms against 712 ms at nb = 128).
 int choose_nb(svb_dtype dt, int64_t m, int64_t n)
 {
     const int64_t k = m < n ? m : n;
