@@ -593,7 +593,7 @@ template <typename C, int B, int LDV> struct BlockRefl {
         asm volatile("" : "+v"(o1), "+v"(t0), "+v"(t1), "+v"(v0), "+v"(v1));
     }
     // p = V^T y.  In f32 four partial sums: with one, the error of the whole reduction was larger by 3, 7 and 7 % (nb =
-    // 32, 64, 128; n = 600, mean of 48 bands), for the same time (nb = 64: 1 to 2 % more up to n = 200, 0.1 at 8192); in f64 they cost 0.4 (two) to 4 % for an error within
+    // 32, 64, 128; n = 600, mean of 48 bands), for the same time; in f64 they cost 0.4 (two) to 4 % for an error within
     // the means' spread of 3 %.
     __device__ __forceinline__ acc_t inner(const C* V, const acc_t (&y)[NTL]) const
     {
@@ -704,20 +704,23 @@ __global__ __launch_bounds__((ReduceShape<C, B>::NT)) void band_reduce_kernel(C*
         int lrow, rrow, lcol, rcol;   // offsets of the tiles' first elements as rows, as columns
     };
     Me me;
-    me.i = lane & 15;
-    me.gq = lane >> 4;
-    me.mrow = B >= kWave ? lane : lane % B;
-    me.mcol = B >= kWave ? 0 : lane / B;
-    me.lline = 16 * tile + me.i;
-    me.rline = (D + 16 * tile + me.i) & (B - 1);
-    me.ron = me.rline >= D;
-    me.lrow = me.lline + F::roff(0, me.gq) * LD;
-    me.rrow = me.rline + F::roff(0, me.gq) * LD;
-    me.lcol = me.lline * LD + F::roff(0, me.gq);
-    me.rcol = me.rline * LD + F::roff(0, me.gq);
-    asm volatile("" : "+v"(me.lrow), "+v"(me.rrow), "+v"(me.lcol), "+v"(me.rcol));
     BlockRefl<C, B, LDV> refl;
-    refl.init(me.i, me.gq);
+    auto place = [&](int l) {
+        me.i = l & 15;
+        me.gq = l >> 4;
+        me.mrow = B >= kWave ? l : l % B;
+        me.mcol = B >= kWave ? 0 : l / B;
+        me.lline = 16 * tile + me.i;
+        me.rline = (D + 16 * tile + me.i) & (B - 1);
+        me.ron = me.rline >= D;
+        me.lrow = me.lline + F::roff(0, me.gq) * LD;
+        me.rrow = me.rline + F::roff(0, me.gq) * LD;
+        me.lcol = me.lline * LD + F::roff(0, me.gq);
+        me.rcol = me.rline * LD + F::roff(0, me.gq);
+        asm volatile("" : "+v"(me.lrow), "+v"(me.rrow), "+v"(me.lcol), "+v"(me.rcol));
+        refl.init(me.i, me.gq);
+    };
+    place(lane);
     using Ld = std::conditional_t<WIDE, int64_t, int>;
     using Off = std::conditional_t<WIDE, int64_t, unsigned>;
     const Ld ldm1 = (Ld)(ldab - 1);
@@ -939,6 +942,14 @@ __global__ __launch_bounds__((ReduceShape<C, B>::NT)) void band_reduce_kernel(C*
         auto apply = [&](auto role) {
             constexpr bool look = decltype(role)::value != 1, rest = decltype(role)::value != 0;
             const bool corner = rest && tile == NTL - 1;   // the wave whose tile takes the panel's lines along
+            // Places are formed here, once a sweep, and not held across the ticket loop for both roles: held, 27 to 35
+            // registers were spilled at nb = 64 (reloaded at each sweep's start; f32, n = 8192: 14.2 -> 12.8 ms inside
+            // svb_svdvals, 13.8 -> 12.8 by itself).  (One role at nb = 128: nothing to separate, and it would spill two.)
+            if constexpr (!BOTH) {
+                int l = lane;
+                asm volatile("" : "+v"(l));
+                place(l);
+            }
             if (look) __builtin_amdgcn_s_setprio(2);
             int early_z = 0, early_a = 0;
             acc_t cl[NTL], cr[NTL], clz, crz;   // tiles of the left reflectors, P4 to the next step's P1
