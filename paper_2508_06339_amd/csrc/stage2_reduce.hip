@@ -25,8 +25,8 @@
 // all traffic with the band, run beside the next panel.  Per step the workgroup holds the upper block U (rows
 // c0-B .., the previous step's A3) and Z in LDS; every block is read once and written once per sweep.
 // us per eight columns (one sweep), n = 8192, before (each block reflector in one piece between the panels,
-// applied from LDS line by line; whole blocks published) -> now: f32 13.5 -> 8.7 (nb = 32), 20.8 -> 13.5 (64),
-// 50 -> 32.0 (128); f64 16.5 -> 11.2 (32), 29.3 -> 18.5 (64).
+// applied from LDS line by line; whole blocks published) -> now: f32 13.5 -> 8.3 (nb = 32), 20.8 -> 12.4 (64),
+// 50 -> 32.0 (128); f64 16.5 -> 11.1 (32), 29.3 -> 18.3 (64).
 //
 // Packed band: entry (i,j) at band[(i - j + ku) + j*ldab], ku = 2B-1, ldab >= 3B.
 #include <type_traits>

@@ -30,10 +30,10 @@ bool nb_ok(int nb) { return nb == 32 || nb == 64 || nb == 128; }
 // hardware, Section 4 and Table 3).  From timings of svb_svdvals on MI355X at orders 1024 .. 32768:
 // small tiles shorten the panel chain and stage 2, large tiles raise the arithmetic intensity of
 // the trailing update, which only pays once the update dominates.  In f32 arithmetic nb = 64 is
-// fastest from order 1024 up to 20480 (16384: 259 ms against 287 ms at nb = 128), the two are equal at 24576
-// (659 ms) and nb = 128 is faster beyond (28672: 937 ms against 971 ms, 32768: 1307 against 1372); in f64, where
-// a register-resident domain holds half as many rows, nb = 32 up to 2048 (17.2 ms against 17.9 ms at nb = 64)
-// and nb = 64 from 3072 on (28.5 against 28.7; 8192: 115 against 125; 16384: 490 ms against 712 ms at nb = 128).
+// fastest from order 1024 up to 20480 (16384: 257 ms against 288 ms at nb = 128), the two are equal at 24576
+// (656 ms) and nb = 128 is faster beyond (28672: 940 ms against 966 ms, 32768: 1295 against 1364); in f64, where
+// a register-resident domain holds half as many rows, nb = 32 up to 2048 (17.1 ms against 17.4 ms at nb = 64)
+// and nb = 64 from 3072 on (28.0 against 28.6; 8192: 115 against 125; 16384: 489 ms against 711 ms at nb = 128).
 int choose_nb(svb_dtype dt, int64_t m, int64_t n)
 {
     const int64_t k = m < n ? m : n;
