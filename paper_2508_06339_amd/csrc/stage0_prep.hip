@@ -16,24 +16,25 @@ namespace {
 
 constexpr int kScanBlocks = 1024;   // partial maxima of the magnitude scan
 
-// S(i, j) = A(i, j) (or A(j, i)) inside the matrix, zero in the padding; 32 x 32 tiles, block (32, 8)
-template <typename T, bool TR>
+// S(i, j) = A(i, j) (or A(j, i)) inside the matrix, zero in the padding; 32 x 32 tiles, block (32, 8).
+// T2: A's type, or the type its arithmetic is done in
+template <typename T, typename T2, bool TR>
 __global__ __launch_bounds__(256) void stage_copy_kernel(const T* __restrict__ A, int64_t lda, int64_t m, int64_t n,
-                                                         T* __restrict__ S, int64_t lds, int64_t mp, int64_t np)
+                                                         T2* __restrict__ S, int64_t lds, int64_t mp, int64_t np)
 {
-    __shared__ T tile[32][33];
+    __shared__ T2 tile[32][33];
     const int64_t i0 = (int64_t)blockIdx.x * 32, j0 = (int64_t)blockIdx.y * 32;
     const int tx = threadIdx.x, ty = threadIdx.y;
     if (!TR) {
         for (int jj = ty; jj < 32; jj += 8) {
             const int64_t i = i0 + tx, j = j0 + jj;
-            if (i < mp && j < np) S[i + j * lds] = (i < m && j < n) ? A[i + j * lda] : T(0.0f);
+            if (i < mp && j < np) S[i + j * lds] = (i < m && j < n) ? ld_as<T2, T>(&A[i + j * lda]) : T2(0.0f);
         }
     } else {
         // S(i, j) = A(j, i): read along A's columns (j runs fastest), write along S's
         for (int ii = ty; ii < 32; ii += 8) {
             const int64_t i = i0 + ii, j = j0 + tx;     // A(j, i)
-            tile[ii][tx] = (j < m && i < n) ? A[j + i * lda] : T(0.0f);
+            tile[ii][tx] = (j < m && i < n) ? ld_as<T2, T>(&A[j + i * lda]) : T2(0.0f);
         }
         __syncthreads();
         for (int jj = ty; jj < 32; jj += 8) {
@@ -126,13 +127,13 @@ __global__ __launch_bounds__(256) void rescale_bidiag_kernel(C* __restrict__ d, 
 
 }  // namespace
 
-template <typename T>
-void launch_stage_copy(const T* A, int64_t lda, int64_t m, int64_t n, bool transpose, T* S, int64_t lds,
+template <typename T, typename T2>
+void launch_stage_copy(const T* A, int64_t lda, int64_t m, int64_t n, bool transpose, T2* S, int64_t lds,
                        int64_t mp, int64_t np, hipStream_t s)
 {
     dim3 grid((unsigned)((mp + 31) / 32), (unsigned)((np + 31) / 32)), block(32, 8);
-    if (transpose) hipLaunchKernelGGL((stage_copy_kernel<T, true>), grid, block, 0, s, A, lda, m, n, S, lds, mp, np);
-    else hipLaunchKernelGGL((stage_copy_kernel<T, false>), grid, block, 0, s, A, lda, m, n, S, lds, mp, np);
+    if (transpose) hipLaunchKernelGGL((stage_copy_kernel<T, T2, true>), grid, block, 0, s, A, lda, m, n, S, lds, mp, np);
+    else hipLaunchKernelGGL((stage_copy_kernel<T, T2, false>), grid, block, 0, s, A, lda, m, n, S, lds, mp, np);
 }
 
 // factors: 8 doubles, followed by kScanBlocks partial maxima
@@ -164,8 +165,8 @@ void launch_rescale_bidiag(C* d, C* e, int64_t n, const double* factors, hipStre
 }
 
 #define SVB_PREP_INST(T)                                                                                            \
-    template void launch_stage_copy<T>(const T*, int64_t, int64_t, int64_t, bool, T*, int64_t, int64_t, int64_t, \
-                                       hipStream_t);                                                                \
+    template void launch_stage_copy<T, T>(const T*, int64_t, int64_t, int64_t, bool, T*, int64_t, int64_t, int64_t, \
+                                          hipStream_t);                                                             \
     template void launch_scale_to_range<T>(T*, int64_t, int64_t, int64_t, double*, hipStream_t);                   \
     template void launch_scale_to_range<T>(T*, int64_t, int64_t, int64_t, double*, hipStream_t, int, int, int);
 SVB_PREP_INST(double)
@@ -173,6 +174,8 @@ SVB_PREP_INST(float)
 SVB_PREP_INST(__half)
 SVB_PREP_INST(bf16_t)
 #undef SVB_PREP_INST
+template void launch_stage_copy<__half, float>(const __half*, int64_t, int64_t, int64_t, bool, float*, int64_t, int64_t, int64_t, hipStream_t);
+template void launch_stage_copy<bf16_t, float>(const bf16_t*, int64_t, int64_t, int64_t, bool, float*, int64_t, int64_t, int64_t, hipStream_t);
 template void launch_rescale_bidiag<double>(double*, double*, int64_t, const double*, hipStream_t);
 template void launch_rescale_bidiag<float>(float*, float*, int64_t, const double*, hipStream_t);
 

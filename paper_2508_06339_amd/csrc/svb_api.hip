@@ -4,6 +4,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "svb_internal.h"
@@ -44,6 +45,7 @@ int choose_nb(svb_dtype dt, int64_t m, int64_t n)
 
 inline int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
+
 // The shape stage 1 works on: rows >= cols, both whole numbers of tiles.  `staged` says the input
 // has to be copied (zero padded, transposed if it is wider than tall) into the workspace first.
 struct Shape {
@@ -61,6 +63,17 @@ Shape shape_of(int64_t m, int64_t n, int nb)
     sh.k = c;
     sh.staged = sh.transpose || sh.rows != r || sh.cols != c;
     return sh;
+}
+
+// 16-bit storage: svb_svdvals works on an f32 copy up to this many rows.  With one block reflector per panel an entry
+// changes by a little in every half-sweep, and rounded to 16 bits each time those changes are lost (n = 4096, values
+// spread evenly: error 2.0e-4 against 6.9e-5 with the tree, whose domains change fewer entries by more; 3.0e-7 on the
+// copy).  Beyond, the tree's update on the 16-bit matrix instructions is the faster one: n = 8192 60 ms against 73,
+// 16384 231 against 240 at nb = 64 and 307 against 259 at nb = 128 (f16).
+constexpr int64_t kWidenRows = 8192;
+bool widens(svb_dtype dt, const Shape& sh)
+{
+    return (dt == SVB_F16 || dt == SVB_BF16) && sh.rows <= kWidenRows;
 }
 
 int check_shape(svb_dtype dt, int64_t m, int64_t n, int nb)
@@ -150,12 +163,21 @@ bool aligned_for_vectors(const void* A, int64_t lda, svb_dtype dt)
 // measurement; the launch loops consult this copy).
 struct Switches {
     int domain_chunks, pipeline_layout, tree_spin, update_h16, ext_events, update_t, event_fence, stage3_host, stage3_relative, no_scale;
+    int stage1;
     bool loaded = false;
+    // one block reflector per panel, unless the panel tree is asked for, or a variant of it
+    bool block_reflector() const
+    {
+        return stage1 == 1 && domain_chunks == 0 && pipeline_layout == 2 && tree_spin == kTreeSpin && update_h16 == 1 &&
+               ext_events == 1 && update_t == 1 && event_fence == 0 && env_int("SVB_PANEL_IMPL", 2) == 2;
+    }
+    static constexpr int kTreeSpin = 1 << 22;
     void load()
     {
+        stage1 = env_int("SVB_STAGE1", 1);
         domain_chunks = env_int("SVB_DOMAIN_CHUNKS", 0);
         pipeline_layout = env_int("SVB_PIPELINE_LAYOUT", 2);
-        tree_spin = env_int("SVB_TREE_SPIN", 1 << 22);
+        tree_spin = env_int("SVB_TREE_SPIN", kTreeSpin);
         update_h16 = env_int("SVB_UPDATE_H16", 1);
         ext_events = env_int("SVB_EXT_EVENTS", 1);
         update_t = env_int("SVB_UPDATE_T", 1);
@@ -182,12 +204,17 @@ int domain_chunks(svb_dtype dt, int nb, const Switches& sw)
 }
 constexpr int kMinDomainChunks = 2;  // workspace is sized for any g >= this
 constexpr size_t kTreeHead = 4;      // ints in front of the tickets of the panel tree's control block
+constexpr size_t kStopInt = 2;       // one of them: the half-sweep (from 1) at which ge2gb_block stopped, or 0
 
 // Workspace layout.  V, Y, T: the panels and factors of one half-sweep's tree (element counts in
 // the compute type); stage: the zero-padded copy of an input that is not a whole number of tiles
 // or is wider than tall (storage type).
 struct Carve {
     size_t panel_elems, t_elems, band_elems, de_elems, stage_elems, tree_ints;
+    // one block reflector per panel (ge2gb_block): work panel, V in both orders, T, W2, partial sums of W; in the
+    // place of the tree's V, Y and T, which are used before or after it, never beside it
+    int64_t blk_ld, blk_q;
+    size_t off_bP, off_bV, off_bVt, off_bT, off_bW2, off_bWp, off_bG;
     size_t off_V, off_Y, off_T, off_band, off_d, off_e, off_sig, off_s3, off_fac, off_gb, off_tree, off_stage, total;
 };
 
@@ -201,13 +228,24 @@ Carve carve(svb_dtype dt, const Shape& sh, int nb)
     c.t_elems = 2 * (size_t)(rows / nb + 1) * nb * nb;  // T per domain, plus room for the v^T v products
     c.band_elems = (size_t)(3 * nb) * (size_t)cols;
     c.de_elems = (size_t)cols;
-    c.stage_elems = sh.staged ? (size_t)rows * (size_t)cols : 0;
+    c.stage_elems = sh.staged || widens(dt, sh) ? (size_t)rows * (size_t)cols : 0;
     // panel tree hand-over: error flag, one ticket counter per half-sweep, one flag per domain
     c.tree_ints = kTreeHead + 2 * (size_t)(cols / nb) + 2 + (size_t)(rows / nb) + kMaxLevels + 2;
     size_t off = 0;
     c.off_V = off; off += align_up(c.panel_elems * cs);
     c.off_Y = off; off += align_up(c.panel_elems * cs);
     c.off_T = off; off += align_up(c.t_elems * cs);
+    c.blk_ld = rows;
+    c.blk_q = rows;   // (rows >= cols)
+    size_t bo = c.off_V;
+    c.off_bP = bo; bo += align_up((size_t)c.blk_ld * nb * cs);
+    c.off_bV = bo; bo += align_up((size_t)c.blk_ld * nb * cs);
+    c.off_bVt = bo; bo += align_up((size_t)c.blk_ld * nb * cs);
+    c.off_bT = bo; bo += align_up((size_t)nb * nb * cs);
+    c.off_bW2 = bo; bo += align_up((size_t)c.blk_q * nb * cs);
+    c.off_bWp = bo; bo += align_up((size_t)block_wp_elems(c.blk_q, nb) * cs);
+    c.off_bG = bo; bo += align_up(recon_scratch_doubles(rows, nb) * sizeof(double));
+    if (bo > off) off = bo;
     c.off_band = off; off += align_up(c.band_elems * cs);
     c.off_d = off; off += align_up(c.de_elems * cs);
     c.off_e = off; off += align_up(c.de_elems * cs);
@@ -216,7 +254,7 @@ Carve carve(svb_dtype dt, const Shape& sh, int nb)
     c.off_fac = off; off += align_up(scale_workspace_bytes());
     c.off_gb = off; off += align_up(gb2bd_bytes(sh.k, nb));
     c.off_tree = off; off += align_up(c.tree_ints * sizeof(int));
-    c.off_stage = off; off += align_up(c.stage_elems * storage_size(dt));
+    c.off_stage = off; off += align_up(c.stage_elems * (widens(dt, sh) ? sizeof(float) : storage_size(dt)));
     c.total = off;
     return c;
 }
@@ -314,6 +352,7 @@ struct Lookahead {
     hipEvent_t lvl[2][kMaxLevels] = {}, udone[2] = {nullptr, nullptr};
     // stage boundaries of svb_svdvals, reused by every call
     hipEvent_t stage[4] = {nullptr, nullptr, nullptr, nullptr};
+    int* stop = nullptr;   // pinned: where ge2gb_block stopped
     bool ok = false, tried = false;
     bool init(const Switches& sw)
     {
@@ -337,6 +376,7 @@ struct Lookahead {
             return false;
         for (int i = 0; i < 4; ++i)
             if (hipEventCreate(&stage[i]) != hipSuccess) return false;
+        if (hipHostMalloc(reinterpret_cast<void**>(&stop), sizeof(int), hipHostMallocDefault) != hipSuccess) return false;
         ok = true;
         // released while the HIP runtime is still up (handlers registered later run earlier)
         std::atexit([] { g_la_release(); });
@@ -356,6 +396,7 @@ struct Lookahead {
         (void)hipEventDestroy(join);
         (void)hipEventDestroy(join_u);
         for (int i = 0; i < 4; ++i) (void)hipEventDestroy(stage[i]);
+        (void)hipHostFree(stop);
         (void)hipStreamDestroy(u);
         (void)hipStreamDestroy(m);
     }
@@ -376,9 +417,10 @@ void g_la_release() { g_la.release(); }
 // so that a half-sweep costs K_A, its updates and their launch gaps.  Kept for testing: one launch
 // per level, main: P0 P1 .. Pl Ul P0' .., side: U0 .. Ul-1 (=1), or every update on the side
 // stream (=0).
+// hs0: the half-sweep to begin with (2k: QR sweep of tile column k, 2k + 1: LQ); those before it are done.
 template <typename T, typename C>
 int ge2gb_pipeline(int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* band, int64_t ldab,
-                   unsigned char* work, const Carve& cv, int g, const Switches& sw, hipStream_t caller)
+                   unsigned char* work, const Carve& cv, int g, const Switches& sw, hipStream_t caller, int hs0)
 {
     const int64_t N = cols / nb;
     Level lv[kMaxLevels];
@@ -386,7 +428,7 @@ int ge2gb_pipeline(int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* ban
     (void)hipEventRecord(g_la.fork, caller);
     (void)hipStreamWaitEvent(ms, g_la.fork, 0);
     (void)hipStreamWaitEvent(ss, g_la.fork, 0);
-    launch_band_clear<C>(band, ldab, cols, ms);
+    if (hs0 == 0) launch_band_clear<C>(band, ldab, cols, ms);
     // control block of the panel tree: error flag, a ticket counter per half-sweep, a flag per domain
     int* const tree_err = reinterpret_cast<int*>(work + cv.off_tree);
     int* const tree_tickets = tree_err + kTreeHead;
@@ -400,10 +442,10 @@ int ge2gb_pipeline(int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* ban
     // a level's event is tied to the completion of its kernel instead of being recorded behind it
     // (one marker less in the main stream between two panel levels)
     const bool ext_events = sw.ext_events != 0;
-    int hs = 0;
+    int hs = hs0;
     bool side_pending = false;
-    for (int64_t k = 0; k < N; ++k) {
-        for (int half = 0; half < 2; ++half) {
+    for (int64_t k = hs0 / 2; k < N; ++k) {
+        for (int half = k == hs0 / 2 ? hs0 & 1 : 0; half < 2; ++half) {
             const bool lq = half == 1;
             if (lq && k == N - 1) break;
             const int set = hs & 1;
@@ -572,32 +614,104 @@ int ge2gb_pipeline(int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* ban
     return hipGetLastError() == hipSuccess ? SVB_OK : SVB_ERR_DEVICE;
 }
 
+// ge2gb_block leaves the rest to ge2gb_pipeline: panels of one tile (square blocks, whose last pivots may well be
+// small), and in f64 arithmetic, where a panel is read twice, the sweeps over at most 256 rows, a single domain of the
+// tree (one panel kernel and one update there: 50 us a half-sweep at nb = 32 against 57; with a second tree level 75
+// against 60).
+template <typename C> constexpr int64_t block_rows() { return sizeof(C) == 8 ? 256 : 0; }
+
+// Stage 1 with one block reflector per panel (stage1_recon.hip, stage1_block.hip), as far as it goes: up to the
+// panels of a single tile, or to a panel that Cholesky QR does not serve.  All on the caller's stream; returns the
+// half-sweep ge2gb_pipeline has to go on with, after waiting for the stream, or a negative status.
+template <typename T, typename C>
+int ge2gb_block(int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* band, int64_t ldab,
+                unsigned char* work, const Carve& cv, hipStream_t s)
+{
+    int* const stop = reinterpret_cast<int*>(work + cv.off_tree) + kStopInt;
+    launch_band_clear<C>(band, ldab, cols, s);
+    launch_fill_int(stop, 1, 0, s);
+    ReconPanel<T, C> rp{};
+    rp.A = A; rp.lda = lda; rp.nb = nb;
+    rp.P = reinterpret_cast<C*>(work + cv.off_bP);
+    rp.V = reinterpret_cast<C*>(work + cv.off_bV);
+    rp.Vt = reinterpret_cast<C*>(work + cv.off_bVt);
+    rp.Tf = reinterpret_cast<C*>(work + cv.off_bT);
+    rp.W2 = reinterpret_cast<C*>(work + cv.off_bW2);
+    rp.Wp = reinterpret_cast<C*>(work + cv.off_bWp);
+    rp.ldv = cv.blk_ld; rp.qmax = cv.blk_q;
+    rp.Gp = reinterpret_cast<double*>(work + cv.off_bG);
+    const int nbp = nb < 64 ? nb : 64;
+    rp.X = rp.Gp + (recon_scratch_doubles(rows, nb) - 2 * (size_t)nbp * nbp);
+    rp.band = band; rp.ldab = ldab; rp.stop = stop;
+    int hs = 0;
+    for (;; ++hs) {
+        const int64_t k = hs / 2;
+        const bool lq = hs & 1;
+        const int64_t row0 = k * nb, col0 = lq ? (k + 1) * nb : k * nb;
+        const int64_t len = lq ? cols - (k + 1) * nb : rows - k * nb;
+        const int64_t qlen = lq ? rows - (k + 1) * nb : cols - (k + 1) * nb;
+        if (len <= nb || qlen <= 0 || rows - row0 <= block_rows<C>()) break;
+        rp.arow = row0; rp.acol = col0; rp.src = A + row0 + col0 * lda;
+        rp.lq = lq ? 1 : 0; rp.len = len; rp.row0 = row0; rp.col0 = col0; rp.hs = hs;
+        prof_begin(SVB_PROF_PANEL, s, 2.0 * (double)len * nb * nb, 0.0);
+        launch_panel_recon<T, C>(rp, s);
+        prof_end(s);
+        T* Cb = A + (lq ? (k + 1) * nb : k * nb) + (k + 1) * nb * lda;
+        prof_begin(SVB_PROF_UPDATE, s, 4.0 * (double)len * nb * (double)qlen, 2.0 * (double)len * (double)qlen * sizeof(T));
+        const int ns = launch_block_wt<T, C>(nb, lq, Cb, lda, len, qlen, rp.qmax, rp.V, rp.ldv, rp.Wp, s);
+        launch_block_tw<C>(nb, rp.Wp, ns, qlen, rp.Tf, nb, rp.W2, s);
+        launch_block_sub<T, C>(lq, Cb, lda, len, qlen, nb, rp.Vt, nb, rp.W2, nb, stop, s);
+        prof_end(s);
+    }
+    if (hipMemcpyAsync(g_la.stop, stop, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
+        return -1;
+    return *g_la.stop ? *g_la.stop - 1 : hs;
+}
+
 template <typename T, typename C>
 int ge2gb_typed(svb_dtype dt, int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* band, int64_t ldab,
-                unsigned char* work, const Carve& cv, const Switches& sw, hipStream_t s)
+                unsigned char* work, const Carve& cv, const Switches& sw, hipStream_t s, bool may_wait)
 {
     if (!g_la.init(sw)) return SVB_ERR_DEVICE;
     const int g = domain_chunks(dt, nb, sw);
-    return ge2gb_pipeline<T, C>(rows, cols, A, lda, nb, band, ldab, work, cv, g, sw, s);
+    int hs0 = 0;
+    if constexpr (std::is_same_v<T, C>) {   // (16-bit storage comes widened, or goes to the tree)
+        // (stage1_block.hip addresses 128 lines of the matrix with 32-bit byte offsets)
+        if (may_wait && sw.block_reflector() && lda * (int64_t)sizeof(T) < ((int64_t)1 << 32) / 128 && cols > nb &&
+            rows > block_rows<C>()) {
+            hs0 = ge2gb_block<T, C>(rows, cols, A, lda, nb, band, ldab, work, cv, s);
+            if (hs0 < 0) return SVB_ERR_DEVICE;
+        }
+    }
+    return ge2gb_pipeline<T, C>(rows, cols, A, lda, nb, band, ldab, work, cv, g, sw, s, hs0);
 }
 
 int ge2gb_dispatch(svb_dtype dt, int64_t rows, int64_t cols, void* A, int64_t lda, int nb, void* band, int64_t ldab,
-                   void* work, const Carve& cv, const Switches& sw, hipStream_t s)
+                   void* work, const Carve& cv, const Switches& sw, hipStream_t s, bool may_wait)
 {
     unsigned char* w = static_cast<unsigned char*>(work);
     switch (dt) {
-    case SVB_F64: return ge2gb_typed<double, double>(dt, rows, cols, (double*)A, lda, nb, (double*)band, ldab, w, cv, sw, s);
-    case SVB_F32: return ge2gb_typed<float, float>(dt, rows, cols, (float*)A, lda, nb, (float*)band, ldab, w, cv, sw, s);
-    case SVB_F16: return ge2gb_typed<__half, float>(dt, rows, cols, (__half*)A, lda, nb, (float*)band, ldab, w, cv, sw, s);
-    case SVB_BF16: return ge2gb_typed<bf16_t, float>(dt, rows, cols, (bf16_t*)A, lda, nb, (float*)band, ldab, w, cv, sw, s);
+    case SVB_F64: return ge2gb_typed<double, double>(dt, rows, cols, (double*)A, lda, nb, (double*)band, ldab, w, cv, sw, s, may_wait);
+    case SVB_F32: return ge2gb_typed<float, float>(dt, rows, cols, (float*)A, lda, nb, (float*)band, ldab, w, cv, sw, s, may_wait);
+    case SVB_F16: return ge2gb_typed<__half, float>(dt, rows, cols, (__half*)A, lda, nb, (float*)band, ldab, w, cv, sw, s, may_wait);
+    case SVB_BF16: return ge2gb_typed<bf16_t, float>(dt, rows, cols, (bf16_t*)A, lda, nb, (float*)band, ldab, w, cv, sw, s, may_wait);
     default: return SVB_ERR_UNSUPPORTED;
     }
 }
 
 // staging copy and scaling, by storage type
-void stage_copy_dispatch(svb_dtype dt, const void* A, int64_t lda, int64_t m, int64_t n, const Shape& sh, void* S,
+void stage_copy_dispatch(svb_dtype dt, bool wide, const void* A, int64_t lda, int64_t m, int64_t n, const Shape& sh, void* S,
                          hipStream_t s)
 {
+    if (wide && dt == SVB_F16) {
+        launch_stage_copy<__half>((const __half*)A, lda, m, n, sh.transpose, (float*)S, sh.rows, sh.rows, sh.cols, s);
+        return;
+    }
+    if (wide) {
+        launch_stage_copy<bf16_t>((const bf16_t*)A, lda, m, n, sh.transpose, (float*)S, sh.rows, sh.rows, sh.cols, s);
+        return;
+    }
     switch (dt) {
     case SVB_F64: launch_stage_copy<double>((const double*)A, lda, m, n, sh.transpose, (double*)S, sh.rows, sh.rows, sh.cols, s); break;
     case SVB_F32: launch_stage_copy<float>((const float*)A, lda, m, n, sh.transpose, (float*)S, sh.rows, sh.rows, sh.cols, s); break;
@@ -693,7 +807,7 @@ int svb_ge2gb(svb_dtype dt, int64_t m, int64_t n, void* A_dev, int64_t lda, int 
     const Shape sh = shape_of(m, n, nb);
     const Carve cv = carve(dt, sh, nb);
     if (work_bytes < cv.total) return SVB_ERR_WORKSPACE;
-    return ge2gb_dispatch(dt, m, n, A_dev, lda, nb, band_dev, ldab, work_dev, cv, switches(), (hipStream_t)stream);
+    return ge2gb_dispatch(dt, m, n, A_dev, lda, nb, band_dev, ldab, work_dev, cv, switches(), (hipStream_t)stream, false);
 }
 
 static int gb2bd_checked(svb_dtype band_dt, int64_t n, int nb, void* band_dev, int64_t ldab, void* d_dev,
@@ -798,16 +912,18 @@ int svb_svdvals(svb_dtype dt, int64_t m, int64_t n, void* A_dev, int64_t lda, vo
 
     hipEvent_t* ev = g_la.stage;
     (void)hipEventRecord(ev[0], s);
-    // the matrix stage 1 works on: the caller's, or its zero-padded (transposed) copy
+    // the matrix stage 1 works on: the caller's, or its zero-padded (transposed, widened) copy
     void* A1 = A_dev;
     int64_t ld1 = lda;
-    if (sh.staged) {
+    const bool wide = widens(dt, sh) && sw.block_reflector();
+    const svb_dtype dt1 = wide ? SVB_F32 : dt;
+    if (sh.staged || wide) {
         A1 = w + cv.off_stage;
         ld1 = sh.rows;
-        stage_copy_dispatch(dt, A_dev, lda, m, n, sh, A1, s);
+        stage_copy_dispatch(dt, wide, A_dev, lda, m, n, sh, A1, s);
     }
-    if (scaled) scale_dispatch(dt, A1, ld1, sh.rows, sh.cols, factors, s);
-    rc = ge2gb_dispatch(dt, sh.rows, sh.cols, A1, ld1, nb, band, ldab, work_dev, cv, sw, s);
+    if (scaled) scale_dispatch(dt1, A1, ld1, sh.rows, sh.cols, factors, s);
+    rc = ge2gb_dispatch(dt1, sh.rows, sh.cols, A1, ld1, nb, band, ldab, work_dev, cv, sw, s, true);
     (void)hipEventRecord(ev[1], s);
     if (rc == SVB_OK) {
         // columns min(m, n) .. of the padded band are zero: stage 2 runs on the leading part

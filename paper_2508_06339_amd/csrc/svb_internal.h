@@ -165,6 +165,31 @@ void launch_update_fused16(int nb, bool lq, T* Cbase, int64_t lda, int64_t qlen,
                            int64_t ldp, int chunks, int g, int64_t stride, bool tri, const float* Tw, bool credited,
                            hipStream_t s);
 
+// ---- stage 1 with one block reflector per panel -------------------------------------------------------
+// Cholesky QR and Householder reconstruction of one panel (stage1_recon.hip)
+template <typename T, typename C> struct ReconPanel {
+    const T* A; int64_t lda, arow, acol;   // the matrix and the panel's corner in it
+    const T* src;                          // &A[arow + acol * lda]
+    int lq, nb; int64_t len;               // orientation, tile size, panel length
+    C *P, *V, *Vt, *Tf, *Wp, *W2;     // work panel, V in both orders, T, scratch of the updates
+    int64_t ldv, qmax;                     // leading dimension of P and V (at least len); what Wp is sized for
+    double *Gp, *X;                        // recon_scratch_doubles(): partial Gram sums; X and the first R
+    C* band; int64_t ldab, row0, col0;
+    int* stop; int hs;
+};
+template <typename T, typename C> void launch_panel_recon(const ReconPanel<T, C>& a, hipStream_t s);
+size_t recon_scratch_doubles(int64_t rows, int nb);
+// the products of a half-sweep (stage1_block.hip); launch_block_wt returns the number of partial sums
+template <typename T, typename C>
+int launch_block_wt(int nbw, bool lq, const T* Cm, int64_t lda, int64_t len, int64_t nq, int64_t qmax, const C* V,
+                    int64_t ldv, C* Wp, hipStream_t s);
+template <typename C>
+void launch_block_tw(int nbw, const C* Wp, int ns, int64_t nq, const C* T, int64_t ldt, C* W2, hipStream_t s);
+template <typename T, typename C>
+void launch_block_sub(bool lq, T* Cm, int64_t lda, int64_t len, int64_t nq, int K, const C* Vt, int64_t ldvt,
+                      const C* W2, int64_t ldw, const int* stop, hipStream_t s);
+int64_t block_wp_elems(int64_t qmax, int nb);   // elements of Wp
+
 // per-kernel timing hooks (no-ops unless profiling is enabled)
 void prof_begin(int kind, hipStream_t s, double flops, double bytes);
 void prof_end(hipStream_t s);
@@ -176,9 +201,9 @@ bool prof_take(int kind, double flops, double bytes, hipEvent_t* start, hipEvent
 // ---- preparation: staging copy, magnitude scan, scaling ------------------------
 // factors (device, doubles): [0] = power of two the matrix is multiplied by before stage 1,
 // [1] = its reciprocal (applied to the bidiagonal), [2] = largest magnitude found.
-// S (mp x np, leading dimension lds, zero padded) = A (m x n) or, with transpose, A^T.
-template <typename T>
-void launch_stage_copy(const T* A, int64_t lda, int64_t m, int64_t n, bool transpose, T* S, int64_t lds,
+// S (mp x np, leading dimension lds, zero padded, of A's type or of its arithmetic's) = A (m x n) or, with transpose, A^T.
+template <typename T, typename T2>
+void launch_stage_copy(const T* A, int64_t lda, int64_t m, int64_t n, bool transpose, T2* S, int64_t lds,
                        int64_t mp, int64_t np, hipStream_t s);
 // largest magnitude of the m x n matrix -> factors (NaN if an entry is not finite); then the
 // matrix is multiplied by factors[0] where that is not 1
