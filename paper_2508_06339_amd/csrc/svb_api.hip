@@ -171,6 +171,7 @@ struct Switches {
         return stage1 == 1 && domain_chunks == 0 && pipeline_layout == 2 && tree_spin == kTreeSpin && update_h16 == 1 &&
                ext_events == 1 && update_t == 1 && event_fence == 0 && env_int("SVB_PANEL_IMPL", 2) == 2;
     }
+    bool plain_chase() const { return env_int("SVB_CHASE_IMPL", 2) == 2 && env_int("SVB_CHASE_SPIN", -1) == -1; }
     static constexpr int kTreeSpin = 1 << 22;
     void load()
     {
@@ -700,6 +701,16 @@ int ge2gb_dispatch(svb_dtype dt, int64_t rows, int64_t cols, void* A, int64_t ld
     }
 }
 
+void small_bidiag_dispatch(svb_dtype dt, void* A, int64_t lda, int64_t m, int64_t n, bool in_place, void* d, void* e, hipStream_t s)
+{
+    switch (dt) {
+    case SVB_F64: launch_small_bidiag<double, double>((double*)A, lda, m, n, in_place, (double*)d, (double*)e, s); break;
+    case SVB_F32: launch_small_bidiag<float, float>((float*)A, lda, m, n, in_place, (float*)d, (float*)e, s); break;
+    case SVB_F16: launch_small_bidiag<__half, float>((__half*)A, lda, m, n, in_place, (float*)d, (float*)e, s); break;
+    default: launch_small_bidiag<bf16_t, float>((bf16_t*)A, lda, m, n, in_place, (float*)d, (float*)e, s); break;
+    }
+}
+
 // staging copy and scaling, by storage type
 void stage_copy_dispatch(svb_dtype dt, bool wide, const void* A, int64_t lda, int64_t m, int64_t n, const Shape& sh, void* S,
                          hipStream_t s)
@@ -912,20 +923,24 @@ int svb_svdvals(svb_dtype dt, int64_t m, int64_t n, void* A_dev, int64_t lda, vo
 
     hipEvent_t* ev = g_la.stage;
     (void)hipEventRecord(ev[0], s);
+    // Both dimensions up to 256: straight to the bidiagonal in one workgroup, and no stages 1 and 2 (ms a call, without and
+    // with: f32 64 0.39, 0.16; 256 1.40, 0.67; f64 64 0.46, 0.20; 192 1.24, 0.62; 256 1.67, 1.18; 256 x 64 0.46, 0.24).
+    const bool small = m <= kSmallMax && n <= kSmallMax && scaled && sw.block_reflector() && sw.plain_chase();
+    if (small) small_bidiag_dispatch(dt, A_dev, lda, m, n, !sh.staged, dd, de, s);
     // the matrix stage 1 works on: the caller's, or its zero-padded (transposed, widened) copy
     void* A1 = A_dev;
     int64_t ld1 = lda;
-    const bool wide = widens(dt, sh) && sw.block_reflector();
+    const bool wide = !small && widens(dt, sh) && sw.block_reflector();
     const svb_dtype dt1 = wide ? SVB_F32 : dt;
-    if (sh.staged || wide) {
+    if (!small && (sh.staged || wide)) {
         A1 = w + cv.off_stage;
         ld1 = sh.rows;
         stage_copy_dispatch(dt, wide, A_dev, lda, m, n, sh, A1, s);
     }
-    if (scaled) scale_dispatch(dt1, A1, ld1, sh.rows, sh.cols, factors, s);
-    rc = ge2gb_dispatch(dt1, sh.rows, sh.cols, A1, ld1, nb, band, ldab, work_dev, cv, sw, s, true);
+    if (scaled && !small) scale_dispatch(dt1, A1, ld1, sh.rows, sh.cols, factors, s);
+    if (!small) rc = ge2gb_dispatch(dt1, sh.rows, sh.cols, A1, ld1, nb, band, ldab, work_dev, cv, sw, s, true);
     (void)hipEventRecord(ev[1], s);
-    if (rc == SVB_OK) {
+    if (rc == SVB_OK && !small) {
         // columns min(m, n) .. of the padded band are zero: stage 2 runs on the leading part
         rc = gb2bd_checked(bdt, k, nb, band, ldab, dd, de, w + cv.off_gb, gb2bd_bytes(k, nb), s);
         if (rc == SVB_OK && scaled) {
