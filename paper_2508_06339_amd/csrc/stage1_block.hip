@@ -105,7 +105,7 @@ __device__ __forceinline__ void lds_barrier()
 // direction.  Tiles are numbered so that an XCD works on a contiguous range of them, eight columns of tiles
 // at a time (their operands stay in its L2).
 template <typename T, typename C, int BR, int BJ>
-__global__ __launch_bounds__(256, 2) void block_sub_kernel(T* __restrict__ Cm, int64_t lda, int nr, int nj,
+__global__ __launch_bounds__(256, sizeof(C) == 4 ? 3 : 2) void block_sub_kernel(T* __restrict__ Cm, int64_t lda, int nr, int nj,
                                                            const C* __restrict__ Ar, int64_t lda_r,
                                                            const C* __restrict__ Bj, int64_t ldb_j, int K,
                                                            const int* __restrict__ stop)
