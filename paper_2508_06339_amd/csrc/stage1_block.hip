@@ -337,15 +337,18 @@ __global__ __launch_bounds__(256) void block_tw_kernel(const C* __restrict__ Wp,
         C s[VK];
         VecIO<C, C>::ld(p, s);
         int z = 1;
-        for (; z + 4 <= ns; z += 4) {
-            C x[4][VK];
+        auto batch = [&](auto n) {
+            constexpr int N = decltype(n)::value;
+            C x[N][VK];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) VecIO<C, C>::ld(p + (z + u) * plane, x[u]);
+            for (int u = 0; u < N; ++u) VecIO<C, C>::ld(p + (z + u) * plane, x[u]);
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < N; ++u)
 #pragma unroll
                 for (int q = 0; q < VK; ++q) s[q] += x[u][q];
-        }
+        };
+        for (; z + 16 <= ns; z += 16) batch(std::integral_constant<int, 16>{});
+        for (; z + 4 <= ns; z += 4) batch(std::integral_constant<int, 4>{});
         for (; z < ns; ++z) {
             C x[VK];
             VecIO<C, C>::ld(p + z * plane, x);

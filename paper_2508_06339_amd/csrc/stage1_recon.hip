@@ -733,43 +733,56 @@ __global__ __launch_bounds__(256) void panel_apply_kernel(const C* A, int64_t ld
 }
 
 // ---- T's block above the diagonal of two sub-panels: T12 = -T11 (V1^T V2) T22; the block below it is zero
-// Wp: partial sums of V1^T V2 (block_wt_kernel: element (c, q) at q * 64 + c)
+// Wp: partial sums of V1^T V2 (block_wt_kernel: element (c, q) at q * 64 + c).  There are up to 64 of them of 4096
+// elements, too much for the one workgroup of the products (one after the other in its threads they took 231 us of
+// every half-sweep at n = 32768, 9 % of the call), so they are added up by the whole chip first: 16 elements a
+// workgroup, 16 threads an element, in a fixed order.
 template <typename C>
-__global__ __launch_bounds__(256) void panel_join_kernel(const C* __restrict__ Wp, int ns, C* __restrict__ T, int64_t ldt)
+__global__ __launch_bounds__(256) void join_sum_kernel(const C* __restrict__ Wp, int ns, double* __restrict__ M)
+{
+    __shared__ double red[16][17];
+    const int e = threadIdx.x & 15, z0 = threadIdx.x >> 4, idx = blockIdx.x * 16 + e;
+    double s = 0;
+#pragma unroll 4
+    for (int z = z0; z < ns; z += 16) s += (double)Wp[(int64_t)z * 4096 + idx];
+    red[z0][e] = s;
+    __syncthreads();
+    if (z0 != 0) return;
+#pragma unroll
+    for (int z = 1; z < 16; ++z) s += red[z][e];
+    M[idx] = s;
+}
+
+// one wave a 16 x 16 block; the three factors are held as they are stored, columns apart
+template <typename C>
+__global__ __launch_bounds__(1024) void panel_join_kernel(const double* __restrict__ M12, C* __restrict__ T, int64_t ldt)
 {
     constexpr int NB = 64, LD = NB + 2;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     double* M = reinterpret_cast<double*>(smem_raw);
-    double *A = M + NB * LD, *Z = A + NB * LD;
+    double *A = M + NB * LD, *B = A + NB * LD, *Z = B + NB * LD;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i = lane & 15, g = lane >> 4;
-    for (int idx = tid; idx < NB * NB; idx += 256) {
-        double s = 0;
-        for (int z = 0; z < ns; ++z) s += (double)Wp[(int64_t)z * NB * NB + idx];
-        M[idx % NB * LD + idx / NB] = s;
-        A[idx % NB * LD + idx / NB] = (double)T[idx % NB + (int64_t)(idx / NB) * ldt];
-    }
-    __syncthreads();
-    for (int t = wave; t < 16; t += 4) {
-        const int bi = t / 4, bj = t % 4;
-        d4 v = zero4();
-        for (int k = bi; k < 4; ++k) v = mm16(v, A + bi * 16 * LD + k * 16, LD, 1, M + k * 16 * LD + bj * 16, LD, 1, i, g);
-        put16(Z + bi * 16 * LD + bj * 16, LD, i, g, v);
-    }
-    __syncthreads();
-    for (int idx = tid; idx < NB * NB; idx += 256)
-        A[idx % NB * LD + idx / NB] = (double)T[NB + idx % NB + (int64_t)(NB + idx / NB) * ldt];
-    __syncthreads();
-    for (int t = wave; t < 16; t += 4) {
-        const int bi = t / 4, bj = t % 4;
-        d4 v = zero4();
-        for (int k = 0; k <= bj; ++k) v = mm16(v, Z + bi * 16 * LD + k * 16, LD, 1, A + k * 16 * LD + bj * 16, LD, 1, i, g);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = bi * 16 + 4 * r + g, col = bj * 16 + i;
-            T[row + (int64_t)(NB + col) * ldt] = (C)-v[r];
-            T[NB + row + (int64_t)col * ldt] = 0;
-        }
+    for (int idx = tid; idx < NB * NB; idx += 1024) {
+        const int r = idx % NB, c = idx / NB;
+        M[c * LD + r] = M12[idx];
+        A[c * LD + r] = (double)T[r + c * ldt];
+        B[c * LD + r] = (double)T[NB + r + (NB + c) * ldt];
+    }
+    __syncthreads();
+    const int bi = wave / 4, bj = wave % 4;
+    d4 v = zero4();
+    for (int k = bi; k < 4; ++k) v = mm16(v, A + k * 16 * LD + bi * 16, 1, LD, M + bj * 16 * LD + k * 16, 1, LD, i, g);
+    put16(Z + bi * 16 * LD + bj * 16, LD, i, g, v);
+    __syncthreads();
+    v = zero4();
+    for (int k = 0; k <= bj; ++k) v = mm16(v, Z + bi * 16 * LD + k * 16, LD, 1, B + bj * 16 * LD + k * 16, 1, LD, i, g);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = bi * 16 + 4 * r + g, col = bj * 16 + i;
+        T[row + (int64_t)(NB + col) * ldt] = (C)-v[r];
+        T[NB + row + (int64_t)col * ldt] = 0;
     }
 }
 
@@ -861,13 +874,15 @@ template <typename T, typename C> void launch_panel_recon(const ReconPanel<T, C>
     subpanel<T, C, 64>(a, 64, 64, s);
     ns = launch_block_wt<C, C>(64, false, a.V + 64 * a.ldv, a.ldv, a.len, 64, a.qmax, a.V, a.ldv, a.Wp, s);
     static bool attr_set = false;
-    const size_t bytes = 3 * 64 * 66 * sizeof(double);
+    const size_t bytes = 4 * 64 * 66 * sizeof(double);
     if (!attr_set) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(panel_join_kernel<C>),
                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
         attr_set = true;
     }
-    hipLaunchKernelGGL((panel_join_kernel<C>), dim3(1), dim3(256), bytes, s, a.Wp, ns, a.Tf, (int64_t)a.nb);
+    // (X, 64 x 64 doubles, is free between the sub-panel's panel_apply_kernel and the next panel)
+    hipLaunchKernelGGL((join_sum_kernel<C>), dim3(256), dim3(256), 0, s, a.Wp, ns, a.X);
+    hipLaunchKernelGGL((panel_join_kernel<C>), dim3(1), dim3(1024), bytes, s, a.X, a.Tf, (int64_t)a.nb);
 }
 
 template void launch_panel_recon<float, float>(const ReconPanel<float, float>&, hipStream_t);
