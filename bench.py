@@ -23,7 +23,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-# dense MFMA peak of the operand type the trailing update multiplies in (f16 / bf16 storage: the
+# dense MFMA peak of the operand type the trailing update multiplies in (f16 / bf16 storage beyond 8192 rows: the
 # 16-bit matrix instructions, f32 accumulate)
 PEAK_TFLOPS = {"f64": 78.6, "f32": 157.3, "f16": 2500.0, "bf16": 2500.0}
 PEAK_HBM_GBS = 8000.0
@@ -187,23 +187,15 @@ def run_workload(args, svb, torch, workloads, config, steps, warmup):
                            ", applied to this run's algorithmic bytes")
     exact_traffic = traffic is not None and traffic_src.startswith("counters")
 
-    def counter_bytes(prefix, want_tri=None):
+    def counter_bytes(prefix):
         """(bytes, launches) per svb_svdvals call of the kernels whose name starts with prefix."""
         if traffic is None:
             return None
         tot, cnt = 0.0, 0
         for name, v in traffic.items():
-            if not name.startswith(prefix):
-                continue
-            if want_tri is not None:
-                # update_fused_kernel<T, C, NB, HT, LQ, TRI, USET> / update_fused32_kernel<T, LQ, TRI>:
-                # TRI marks the tree levels above the first
-                targs = [x.strip() for x in name[name.index("<") + 1:name.rindex(">")].split(",")]
-                tri = targs[2] if name.startswith("update_fused32") else targs[5]
-                if (tri == "true") != want_tri:
-                    continue
-            tot += (v["read_GB"] + v["write_GB"]) * 1e9
-            cnt += v["launches"]
+            if name.startswith(prefix):
+                tot += (v["read_GB"] + v["write_GB"]) * 1e9
+                cnt += v["launches"]
         return (tot, cnt) if cnt else None
 
     # The kernel class that costs the most wall time.  Panel kernels run on their own stream beside
@@ -213,28 +205,32 @@ def run_workload(args, svb, torch, workloads, config, steps, warmup):
     cost["panel"] = min(cost["panel"], exposed_panel * 1e3)
     dom = max(cost, key=cost.get)
     upd = prof["update"]
+    # one block reflector per panel (16-bit matrices of more rows than that: the tree of domain QRs)
+    block = dtype not in ("f16", "bf16") or n <= 8192
+    if block and dtype != "f64":
+        peak = PEAK_TFLOPS["f32"]
     if dom in ("update", "update_upper"):
-        # MFMA-bound contraction: credited flops of its first-level launches (both products,
-        # 4 rows nb cols per launch; 8/3 n^3 over a run) / their summed duration
+        # MFMA-bound contraction: credited flops of the trailing updates (both products, 4 rows nb cols a
+        # half-sweep; 8/3 n^3 over a run) / the summed duration of their kernels
         ach = upd["flops"] / upd["seconds"] / 1e12 if upd["seconds"] > 0 else 0.0
-        kname = ("update_fused16_kernel" if dtype in ("f16", "bf16") else
-                 "update_fused32_kernel" if (dtype == "f32" and nb == 128) else "update_fused_kernel")
-        roofline = dict(kernel=kname + " (first tree level: the launches with TRI = false)", bound="mfma", achieved=ach,
+        kname = ("block_wt_kernel + block_tw_kernel + block_sub_kernel (a launch: the three of a half-sweep)" if block else
+                 "update_fused16_kernel (first tree level: the launches with TRI = false)")
+        roofline = dict(kernel=kname, bound="mfma", achieved=ach,
                         peak=peak,
                         unit="TFLOP/s", frac=ach / peak, traffic=None,
                         launches_per_step=upd["launches"] / steps,
                         avg_launch_ms=upd["seconds"] / max(upd["launches"], 1) * 1e3,
                         algorithmic_bytes_per_launch=upd["bytes"] / max(upd["launches"], 1),
                         algorithmic_flops_per_launch=upd["flops"] / max(upd["launches"], 1))
-        cb = counter_bytes("update_fused", want_tri=False)
+        cb = counter_bytes("block_") if block else None
         if cb and exact_traffic:
-            roofline["traffic"] = cb[0] / cb[1]
-        elif cb and "update_first_level_algorithmic_GB" in traffic["_meta"]:
-            ratio = cb[0] / (traffic["_meta"]["update_first_level_algorithmic_GB"] * 1e9)
+            roofline["traffic"] = cb[0] * steps / max(upd["launches"], 1)
+        elif cb and "update_algorithmic_GB" in traffic["_meta"]:
+            ratio = cb[0] / (traffic["_meta"]["update_algorithmic_GB"] * 1e9)
             roofline["traffic"] = ratio * roofline["algorithmic_bytes_per_launch"]
             roofline["traffic_to_algorithmic_ratio"] = ratio
         if cb:
-            roofline["traffic_unit"] = "HBM bytes per launch (FETCH_SIZE + WRITE_SIZE, calibrated), first tree level"
+            roofline["traffic_unit"] = "HBM bytes per launch (FETCH_SIZE + WRITE_SIZE, calibrated)"
             roofline["traffic_source"] = traffic_src
         allsec = upd["seconds"] + prof["update_upper"]["seconds"]
         roofline["frac_all_tree_levels"] = upd["flops"] / allsec / 1e12 / peak if allsec > 0 else None
@@ -250,7 +246,7 @@ def run_workload(args, svb, torch, workloads, config, steps, warmup):
     roofline_update = dict(bound="mfma", achieved=upd["flops"] / upd["seconds"] / 1e12 if upd["seconds"] > 0 else 0.0,
                            peak=peak, unit="TFLOP/s")
     roofline_update["frac"] = roofline_update["achieved"] / peak
-    # the same launches against the HBM roofline by their algorithmic bytes (the block read once and
+    # the same launches against the HBM roofline by their algorithmic bytes (the trailing matrix read twice and
     # written once): the bound that matters where the operands are 16 bits wide
     roofline_update["algorithmic_gbs"] = upd["bytes"] / upd["seconds"] / 1e9 if upd["seconds"] > 0 else 0.0
     roofline_update["hbm_frac"] = roofline_update["algorithmic_gbs"] / PEAK_HBM_GBS

@@ -18,26 +18,30 @@
  *     fixed array inside the library's device image.
  *   - GPU work is ordered after what the HIP stream passed as `stream` (a
  *     hipStream_t cast to void*, NULL = the default stream) holds at the call,
- *     and that stream waits for it: stage 1 runs on two internal streams that
- *     are forked from and joined back to `stream` with events (the first
- *     level of every panel tree and the updates on one, the tree's upper
- *     levels beside them on the other), the rest on `stream`.
+ *     and that stream waits for it.  svb_svdvals runs on `stream` throughout;
+ *     where its stage 1 uses the tree of domain QRs, and in svb_ge2gb, that
+ *     tree runs on two internal streams that are forked from and joined back
+ *     to `stream` with events (the first level of every panel tree and the
+ *     updates on one, the tree's upper levels beside them on the other).
  *   - Return value: an svb_status.  On SVB_ERR_ARG / SVB_ERR_UNSUPPORTED /
  *     SVB_ERR_WORKSPACE nothing has been read or written.
  *   - dtype: SVB_F64, SVB_F32, and the storage-only types SVB_F16 / SVB_BF16
  *     (every sum is formed in f32, as the paper does for half precision,
- *     Section 4.3; the trailing update multiplies on the 16-bit matrix
- *     instructions with its f32 operands split into 16-bit terms, which keeps
- *     f32 accuracy; the band, the bidiagonal and the result are f32).
+ *     Section 4.3; the band, the bidiagonal and the result are f32).
+ *     svb_svdvals works on an f32 copy in the workspace of up to 8192 rows; of
+ *     more, and in svb_ge2gb, the transformed matrix is kept in 16 bits and the
+ *     trailing update multiplies on the 16-bit matrix instructions with its
+ *     f32 operands split into 16-bit terms, which keeps their f32 accuracy.
  *   - nb (the paper's TILESIZE): 32, 64 or 128; 0 lets the library choose
  *     (svb_choose_nb).
  *   - Magnitudes: entries may be anywhere in the finite range of the storage
  *     type.  svb_svdvals multiplies the matrix by a power of two first when its
  *     largest magnitude lies outside [2^-40, 2^40] (f32 arithmetic) or
  *     [2^-400, 2^400] (f64), because the kernels form sums of squares without
- *     scaling them, and multiplies the bidiagonal back.  An SVB_F16 matrix is
- *     scaled so that max|a| sqrt(m n) is about 2^11: the transformed matrix is
- *     written back in f16, where an entry can reach a column's norm.  The stage-split entry
+ *     scaling them, and multiplies the bidiagonal back.  An SVB_F16 matrix of
+ *     more than 8192 rows is scaled so that max|a| sqrt(m n) is about 2^11: the
+ *     transformed matrix is written back in f16, where an entry can reach a
+ *     column's norm.  The stage-split entry
  *     points svb_ge2gb / svb_gb2bd do not rescale: their inputs must keep
  *     sums of squares of n entries inside the arithmetic type's range (and an
  *     SVB_F16 matrix its Frobenius norm below 2^13).  Entries far below the
@@ -118,7 +122,8 @@ int svb_choose_nb(svb_dtype dt, int64_t m, int64_t n);
  *   work_dev   [dev]  scratch of at least svb_workspace_bytes(...) bytes,
  *                     256-byte aligned.
  * Blocking: returns after the result has been copied to S_out_host (one
- * stream synchronisation).  With the environment variable SVB_STAGE3=host the
+ * stream synchronisation, and one between stage 1 and stage 2 where the
+ * matrix is larger than 256 x 256).  With the environment variable SVB_STAGE3=host the
  * bidiagonal is solved on the host (svb_bdsvals) instead of the device.
  */
 int svb_svdvals(svb_dtype dt, int64_t m, int64_t n, void* A_dev, int64_t lda,
@@ -225,15 +230,16 @@ int svb_last_timings(double* t_panel, double* t_update, double* t_stage2, double
  * kernel classes below with HIP events on the stream the kernel runs on and
  * svb_svdvals (or svb_profile_collect, after the caller synchronised the
  * stream) sums the elapsed times.  Off by default.
- *   kind: SVB_PROF_PANEL (domain QR of every tree level), SVB_PROF_UPDATE (the
- *   one-pass trailing update, first tree level: the launches whose flops are
- *   credited), SVB_PROF_UPDATE_UPPER (the same kernel on the tree levels above),
+ *   kind: SVB_PROF_PANEL (the kernels of a panel, or the domain QR of every tree
+ *   level), SVB_PROF_UPDATE (the trailing update of a half-sweep; in the tree its
+ *   first level: the launches whose flops are credited), SVB_PROF_UPDATE_UPPER
+ *   (the same kernel on the tree levels above),
  *   SVB_PROF_BAND_REDUCE (stage 2, band -> 8 super-diagonals), SVB_PROF_NARROW
  *   (stage 2, 8 super-diagonals -> bidiagonal), SVB_PROF_STAGE3.
  *   seconds / launches / flops / bytes [host] out, any may be NULL: totals
  *   since the last svb_profile_enable(1); flops and bytes are the algorithmic
- *   counts of the launches (update: 2*rows*nb*cols per product, block read once
- *   and written once; band reduction: every nb x nb block read once and written
+ *   counts of the launches (update: 2*rows*nb*cols per product, block read twice
+ *   and written once, in the tree read once; band reduction: every nb x nb block read once and written
  *   once per block sweep; narrow chase: the band's 24 stored rows read once and
  *   written once per bundle of sweeps), not hardware counters.
  */

@@ -30,11 +30,11 @@ bool nb_ok(int nb) { return nb == 32 || nb == 64 || nb == 128; }
 // Tile size chosen when the caller passes nb = 0 (the paper tunes TILESIZE per size and
 // hardware, Section 4 and Table 3).  From timings of svb_svdvals on MI355X at orders 1024 .. 32768:
 // small tiles shorten the panel chain and stage 2, large tiles raise the arithmetic intensity of
-// the trailing update, which only pays once the update dominates.  In f32 arithmetic nb = 64 is
-// fastest from order 1024 up to 20480 (16384: 257 ms against 288 ms at nb = 128), the two are equal at 24576
-// (656 ms) and nb = 128 is faster beyond (28672: 940 ms against 966 ms, 32768: 1295 against 1364); in f64, where
-// a register-resident domain holds half as many rows, nb = 32 up to 2048 (17.1 ms against 17.4 ms at nb = 64)
-// and nb = 64 from 3072 on (28.0 against 28.6; 8192: 115 against 125; 16384: 489 ms against 711 ms at nb = 128).
+// the trailing update, which only pays once the update dominates.  In f32 arithmetic nb = 64 from order
+// 1024 (16384: 232 ms against 257 at nb = 128) and nb = 128 beyond 26624 (28672: 894 ms against 929); in f64 nb = 32 up
+// to 2560 (2048: 15.3 ms against 16.3 at nb = 64) and nb = 64 beyond (8192: 100 against 119; 16384: 411 ms
+// against 511 at nb = 128).  Between 1024 and 4096 the two smaller sizes lie within 5 % of each other, square matrices
+// preferring 32 and tall ones 64.
 int choose_nb(svb_dtype dt, int64_t m, int64_t n)
 {
     const int64_t k = m < n ? m : n;
@@ -341,8 +341,8 @@ struct Profiler {
     }
 } g_prof;
 
-// Streams and events of stage 1 (created once per process).  Stage 1 runs on two internal
-// streams forked from the caller's stream and joined back to it: `m` carries the panel tree and
+// Streams and events of stage 1 (created once per process).  The panel tree (ge2gb_pipeline) runs on two
+// internal streams forked from the caller's stream and joined back to it: `m` carries the panel tree and
 // the last level's update, `u` the updates of the levels below.  (The chain does not run on the
 // caller's stream itself so that it never serialises with the NULL stream.)
 void g_la_release();
@@ -658,7 +658,7 @@ int ge2gb_block(int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* band, 
         launch_panel_recon<T, C>(rp, s);
         prof_end(s);
         T* Cb = A + (lq ? (k + 1) * nb : k * nb) + (k + 1) * nb * lda;
-        prof_begin(SVB_PROF_UPDATE, s, 4.0 * (double)len * nb * (double)qlen, 2.0 * (double)len * (double)qlen * sizeof(T));
+        prof_begin(SVB_PROF_UPDATE, s, 4.0 * (double)len * nb * (double)qlen, 3.0 * (double)len * (double)qlen * sizeof(T));
         const int ns = launch_block_wt<T, C>(nb, lq, Cb, lda, len, qlen, rp.qmax, rp.V, rp.ldv, rp.Wp, s);
         launch_block_tw<C>(nb, rp.Wp, ns, qlen, rp.Tf, nb, rp.W2, s);
         launch_block_sub<T, C>(lq, Cb, lda, len, qlen, nb, rp.Vt, nb, rp.W2, nb, stop, s);
