@@ -400,7 +400,10 @@ void wt_launch(bool lq, const T* Cm, int64_t lda, int len, int nq, const C* V, i
 }  // namespace
 
 // how the contraction over p is split: enough workgroups for the chip, at least 64 elements each, and
-// partial sums within the workspace (block_wp_elems)
+// partial sums within the workspace (block_wp_elems).  1024 workgroups where the size allows: two to four fit on
+// a compute unit, and with 512 they all begin and end together (f32 32768, nb = 128: 1208 ms a call with 512, 1198
+// with 768, 1177 with 1024, as with 2048 or 3072; f64 16384, nb = 128: 509, 507, 502; f32 16384, nb = 64: 232, 229, 227;
+// no difference at 4096 and 8192)
 static int64_t wp_cap(int64_t qmax) { return 4 * qmax > 32768 ? 4 * qmax : 32768; }
 int64_t block_wp_elems(int64_t qmax, int nb) { return wp_cap(qmax) * nb; }
 
@@ -410,7 +413,7 @@ static WtPlan wt_plan(int nbw, int64_t len, int64_t nq, int64_t qmax)
     WtPlan p;
     p.qt = nbw == 32 ? 128 : (nq >= 128 * 128 ? 128 : 64);
     const int64_t strips = (nq + p.qt - 1) / p.qt;
-    int64_t ns = (512 + strips - 1) / strips;
+    int64_t ns = (1024 + strips - 1) / strips;
     const int64_t room = wp_cap(qmax) / nq;
     if (ns > room) ns = room;
     if (ns > len / 64) ns = len / 64;
