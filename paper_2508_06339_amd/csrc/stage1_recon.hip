@@ -10,13 +10,17 @@
 //
 // (The reconstruction: Ballard, Demmel, Grigori, Jacquelin, Nguyen, Solomonik, "Reconstructing Householder
 // vectors from tall-skinny QR", 2014; Cholesky QR applied twice: Yamamoto, Nakatsukasa, Yanagisawa, Fukaya,
-// 2015.)  With f32 arithmetic everything above is formed in 64 bits and rounded once, so one pass gives a Q
-// that is orthonormal to f32 precision while 2^-52 / rho is small, rho the smallest ratio of a pivot of the
-// Cholesky factorisation to its diagonal entry of G (squared sine of the angle between a column and those
-// before it).  With f64 the pass is repeated on Q: G' = I + E with E so small that R' = I + N, N = E's upper
-// triangle with half its diagonal.  A panel whose rho is below kMinRho, or whose sums of squares leave the range, sets
-// *stop: the block_sub_kernel of this and of every later half-sweep then leaves the matrix as it is, and the host goes on
-// with the tree of domain QRs from this half-sweep on.
+// 2015.)  How far Q = A R^-1 is from orthonormal is 2^-53 times the square of the panel's condition number, with its
+// columns brought to norm 1 first (their lengths D do not matter); no pivot shows that number (unit upper triangular with
+// -a above the diagonal: pivots near 1, condition number (1 + a)^nb).
+//   f32 arithmetic: everything above is formed in 64 bits and rounded once, one pass.  ||D R^-1||_F^2 (nb times it bounds the
+//     squared condition number) is formed from R^-T, and at most kMaxInv is accepted: Q is orthonormal to about 2^-26 there
+//     (in a model on the host the deviation of H rose above f32's own rounding from 2^30 on).
+//   f64: the pass is repeated on Q: G' = I + E, R' = I + N, N = E's upper triangle with half its diagonal.  What that
+//     leaves out is N^T N, so E itself is looked at, and at most kMaxE is accepted (nb E^2 at most 2^-52).
+// A panel that is refused, that has a pivot below kMinRho times its diagonal entry of G, or whose sums of squares leave the
+// range, sets *stop: the block_sub_kernel of this and of every later half-sweep then leaves the matrix as it is, and the
+// host goes on with the tree of domain QRs, which takes any panel, from this half-sweep on.
 // Trailing columns of zeros (padding) are allowed: their reflectors are identities.
 #include <utility>
 
@@ -29,6 +33,8 @@ namespace svb {
 namespace {
 
 constexpr double kMinRho = 0x1p-22;
+constexpr double kMaxInv = 0x1p26;   // of ||D R^-1||_F^2, one pass
+constexpr double kMaxE = 0x1p-29;    // of max |E|, the first of two passes
 constexpr int kGramRows = 128;
 
 template <typename Fn, int... K> __device__ __forceinline__ void unrolled(Fn&& f, std::integer_sequence<int, K...>)
@@ -497,12 +503,13 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
         ri = wave - 2 - rj * (rj + 1) / 2;
     }
     if constexpr (MODE == kSecond) {
-        // N: E's upper triangle with half its diagonal (what it is not small enough for was refused in the first pass);
-        // I + N in the place of G, (I - N)^T in E
+        // N: E's upper triangle with half its diagonal; I + N in the place of G, (I - N)^T in E
         lds_barrier();
         for (int idx = tid; idx < NBP * NBP; idx += NTH) {
             const int c = idx % NBP, r = idx / NBP;
-            const double v = r < c ? G[r * LD + c] : (r == c ? 0.5 * (G[r * LD + c] - 1.0) : 0.0), one = r == c ? 1.0 : 0.0;
+            const double one = r == c ? 1.0 : 0.0, dev = r <= c ? G[r * LD + c] - one : 0.0;
+            if (!(fabs(dev) <= kMaxE)) sh_bad = 1;   // (a NaN as well)
+            const double v = r == c ? 0.5 * dev : dev;
             G[r * LD + c] = one + v;
             if (r <= c) E[c * LD + r] = one - v;
         }
@@ -518,6 +525,17 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
         double *Lkk = Ld + kb * 16 * LDD, *Ukk = Ud + kb * 16 * LDD;
         if (chol && wave == 0) {
             if (!chol16(blk(G, t, t), LD, blk(E, t, t), LD, g0 + t * 16, i, g) && lane == 0) sh_bad = 1;
+        }
+        if (MODE == kFull && t == NBK && wave == 0) {
+            // ||D R^-1||_F^2 beside the last LU block (R^-T is whole by now)
+            double f = 0;
+            for (int idx = lane; idx < NBP * NBP; idx += 64) {
+                const int k = idx % NBP, c = idx / NBP;
+                const double x = k <= c ? E[c * LD + k] : 0.0;
+                f = fma(g0[k] * x, x, f);
+            }
+            for (int off = 32; off > 0; off >>= 1) f += __shfl_xor(f, off, kWave);
+            if (!(f <= kMaxInv) && lane == 0) sh_bad = 1;
         }
         if (lu && wave == 1) lu16(blk(B, kb, kb), blk(G, kb, kb), LD, Lkk, Ukk, LDD, S + kb * 16, i, g);
         if (MODE == kSecond && kb == 0 && wave >= 2 && wave < NT + 2)   // R' R, a block a wave
