@@ -12,8 +12,12 @@
 // and by the chain of the two reflectors at the small ones, about 2000 cycles a column.  The columns go in phases of 64,
 // in which the finished row and column slots are left out by compilation; a wave's elements are taken a column at a time
 // where they lie in LDS (four columns at a time, 32 more registers, were spilled: f64 256 1.48 ms a call against 1.18).
-// H = I - g u u^T with u not normalised; a tail whose squares sum up to nothing gives H = I.  The matrix is scaled by a
-// power of two so that its largest entry is in [0.5, 1), and the bidiagonal scaled back.
+// H = I - g u u^T with u not normalised.  The matrix is scaled by a power of two so that its largest entry is in [0.5, 1),
+// and the bidiagonal scaled back.  A line whose sum of squares is so small that subnormal squares can be a part of it
+// (SmallRange::kLow) has to be moved up by a power of two first, or its reflector is not orthogonal, and it also hits
+// lines of order one.  That is left to a second run from the start, which only a matrix with such a line pays for: with the
+// branch in every column of the one run a call took up to 5 % longer.  A tail whose squares all underflow gives H = I, and so
+// does, in the second run, one below 2^-96 (f32) or 2^-850 (f64).
 #include <utility>
 
 #include "svb_internal.h"
@@ -136,10 +140,15 @@ template <typename C> __device__ __forceinline__ C wave_sum(C v)
 __device__ __forceinline__ float ldexp_of(float x, int e) { return __builtin_amdgcn_ldexpf(x, e); }
 __device__ __forceinline__ double ldexp_of(double x, int e) { return __builtin_amdgcn_ldexp(x, e); }
 
+// sums of squares below kLow are formed again from the line times 2^kUp (an entry is at most 2^8, the matrix's norm)
+template <typename C> struct SmallRange;
+template <> struct SmallRange<float> { static constexpr float kLow = 0x1p-96f; static constexpr int kUp = 48; };
+template <> struct SmallRange<double> { static constexpr double kLow = 0x1p-900; static constexpr int kUp = 400; };
+
 // The reflector of a line with first entry alpha and tail of squared norm ss: H = I - g u u^T, u = (alpha - beta, tail)
 template <typename C> __device__ __forceinline__ void reflector(C alpha, C ss, C& beta, C& u0, C& g)
 {
-    const bool ident = ss < (sizeof(C) == 8 ? (C)0x1p-1022 : (C)0x1p-126f);
+    const bool ident = ss < SmallRange<C>::kLow;
     const C b = copysign(newton_sqrt(fma(alpha, alpha, ss)), -alpha);
     u0 = ident ? (C)0 : alpha - b;   // (b is not a number where everything is zero)
     g = ident ? (C)0 : newton_rcp(-b * u0);
@@ -157,17 +166,15 @@ template <typename C, int RJ, int CJ> struct SmallGeom {
     static_assert(kBytes <= 160 * 1024, "LDS");
 };
 
-template <typename T, typename C, int RJ, int CJ>
-__global__ __launch_bounds__(512) void small_bidiag_kernel(T* A, int64_t lda, int m, int n, int transpose, int in_place,
-                                                           C* __restrict__ d, C* __restrict__ e)
+// One run.  True, and nothing written, where a line would have to be moved up (never with CAREFUL, which moves them).
+template <bool CAREFUL, typename T, typename C, int RJ, int CJ>
+__device__ __forceinline__ bool small_run(T* A, int64_t lda, int m, int n, int transpose, int in_place, C* __restrict__ d,
+                                          C* __restrict__ e, C* sm, double* sh_big)
 {
     using Gm = SmallGeom<C, RJ, CJ>;
     constexpr int NC = Gm::NC, LC = Gm::LC, RC = NC - LC, NR = Gm::NR, NG = NC / 4, LG = LC / 4;
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    C* sm = reinterpret_cast<C*>(smem_raw);
     C *col = sm + Gm::oCol, *ub = sm + Gm::oU, *wb = sm + Gm::oW, *zb = sm + Gm::oZ, *sq = sm + Gm::oS, *la = sm + Gm::oA;
     C *dl = sm + Gm::oD, *el = sm + Gm::oE;
-    __shared__ double sh_big[8];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     // this thread's slots in LDS: two bases, so that a slot is within an instruction's 16-bit offset of one of them
@@ -212,7 +219,7 @@ __global__ __launch_bounds__(512) void small_bidiag_kernel(T* A, int64_t lda, in
             d[i] = (C)NAN;
             e[i] = 0;
         }
-        return;
+        return false;
     }
     const int ex = big > 0.0 ? __builtin_amdgcn_frexp_exp(big) : 0;
 #pragma unroll
@@ -237,6 +244,7 @@ __global__ __launch_bounds__(512) void small_bidiag_kernel(T* A, int64_t lda, in
         }
     }
     lds_barrier();
+    bool again = false;
     // Columns 64 J0 .. 64 J0 + 63 as one phase: the rows of the slots below J0 and the columns of the groups below 2 J0
     // are finished, and only the first two groups of a phase can be finished within it.
     unroll<CJ>([&](auto phase) {
@@ -277,7 +285,7 @@ __global__ __launch_bounds__(512) void small_bidiag_kernel(T* A, int64_t lda, in
         const int kend = min(n, 64 * (J0 + 1));
         for (int k = 64 * J0; k < kend; ++k) {
             // ---- left reflector from column k
-            const C alpha = col[k];
+            C alpha = col[k];
             C v[RJ], s4 = 0;
 #pragma unroll
             for (int j = J0; j < RJ; ++j) {
@@ -285,9 +293,23 @@ __global__ __launch_bounds__(512) void small_bidiag_kernel(T* A, int64_t lda, in
                 v[j] = j > J0 || lane + 64 * j > k ? t : (C)0;
                 s4 = fma(v[j], v[j], s4);
             }
+            s4 = wave_sum(s4);
+            bool low = s4 < SmallRange<C>::kLow;   // (the same in every lane and wave)
+            again |= low && s4 > (C)0;
+            low = CAREFUL && __any(low);
+            if (low) {
+                alpha = ldexp_of(alpha, SmallRange<C>::kUp);
+                s4 = 0;
+#pragma unroll
+                for (int j = J0; j < RJ; ++j) {
+                    v[j] = ldexp_of(v[j], SmallRange<C>::kUp);
+                    s4 = fma(v[j], v[j], s4);
+                }
+                s4 = wave_sum(s4);
+            }
             C hb, hu, hg;
-            reflector(alpha, wave_sum(s4), hb, hu, hg);
-            dl[k] = hb;
+            reflector(alpha, s4, hb, hu, hg);
+            dl[k] = low ? ldexp_of(hb, -SmallRange<C>::kUp) : hb;
             if (k == n - 1) break;
             v[J0] = lane + 64 * J0 == k ? hu : v[J0];
             // products with the columns, CH columns of a wave at a time: sums over the lanes, times g, to the wave's part of LDS
@@ -332,7 +354,7 @@ __global__ __launch_bounds__(512) void small_bidiag_kernel(T* A, int64_t lda, in
             }
             lds_barrier();
             // ---- right reflector from row k
-            C s8 = 0;
+            C alpha2 = ub[(k1 & 7) * NC + (k1 >> 3)], s8;
             if constexpr (LC > 0) {
                 s8 = lane < 8 ? sq[lane & 7] : (C)0;
                 s8 += dpp<kHalfMirror>(s8);
@@ -345,9 +367,24 @@ __global__ __launch_bounds__(512) void small_bidiag_kernel(T* A, int64_t lda, in
                 for (int w = 0; w < 8; ++w) t[w] = sq[w];
                 s8 = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
             }
-            const C alpha2 = ub[(k1 & 7) * NC + (k1 >> 3)];
+            bool low2 = s8 < SmallRange<C>::kLow;
+            again |= low2 && s8 > (C)0;
+            low2 = CAREFUL && __any(low2);
+            if (low2) {   // (the row stays as it is in LDS: only the sum, u's first entry and z are moved)
+                alpha2 = ldexp_of(alpha2, SmallRange<C>::kUp);
+                s8 = 0;
+                for (int q = k1 + 1 + lane; q < 8 * NC; q += 64) {
+                    const C y = ldexp_of(ub[(q & 7) * NC + (q >> 3)], SmallRange<C>::kUp);
+                    s8 = fma(y, y, s8);
+                }
+                s8 = wave_sum(s8);
+            }
             C fb, fu, fg;
             reflector(alpha2, s8, fb, fu, fg);
+            if (low2) {
+                fb = ldexp_of(fb, -SmallRange<C>::kUp);
+                fu = ldexp_of(fu, -SmallRange<C>::kUp);
+            }
             el[k] = fb;
             C z[RJ];
 #pragma unroll
@@ -378,6 +415,10 @@ __global__ __launch_bounds__(512) void small_bidiag_kernel(T* A, int64_t lda, in
                 z[j] = -fg * (((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7])));
                 if constexpr (LC > 0) __builtin_amdgcn_sched_barrier(0);
             }
+            if (low2) {   // (fg is at most 2^96 or 2^900, an entry of z above as small as the row's)
+#pragma unroll
+                for (int j = J0; j < RJ; ++j) z[j] = ldexp_of(z[j], 2 * SmallRange<C>::kUp);
+            }
             // ---- update; column k + 1 to LDS and, finished, zero in the registers
             groups(kFirst, kAll, k, kStore, entries, [&](auto qc, auto uc, C (&x)[RJ], C y) {
                 constexpr int q = decltype(qc)::value, u = decltype(uc)::value;
@@ -395,11 +436,26 @@ __global__ __launch_bounds__(512) void small_bidiag_kernel(T* A, int64_t lda, in
         }
     });
     lds_barrier();
+    if (!CAREFUL && __any(again)) return true;
     for (int i = tid; i < n; i += 512) {
         d[i] = ldexp_of(dl[i], ex);
         e[i] = i < n - 1 ? ldexp_of(el[i], ex) : (C)0;
         // (a matrix that the method would work on in place counts as used up at this size too)
         if (in_place) st_as<T, C>(&A[i + i * lda], dl[i]);
+    }
+    return false;
+}
+
+template <typename T, typename C, int RJ, int CJ>
+__global__ __launch_bounds__(512) void small_bidiag_kernel(T* A, int64_t lda, int m, int n, int transpose, int in_place,
+                                                           C* __restrict__ d, C* __restrict__ e)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ double sh_big[8];
+    C* sm = reinterpret_cast<C*>(smem_raw);
+    if (small_run<false, T, C, RJ, CJ>(A, lda, m, n, transpose, in_place, d, e, sm, sh_big)) {
+        __syncthreads();
+        small_run<true, T, C, RJ, CJ>(A, lda, m, n, transpose, in_place, d, e, sm, sh_big);
     }
 }
 
