@@ -4,6 +4,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <utility>
 
 namespace svb {
 
@@ -214,5 +215,75 @@ template <int K, int N> __device__ __forceinline__ void row_lane_axpy(double (&x
 #undef SVB_COL7
 #undef SVB_COL_ARGS
 #undef SVB_BCAST
+
+// swap of a's upper half with b's lower half / of the odd rows of sixteen lanes of a with the even rows of b
+__device__ __forceinline__ void swap_halves(float& a, float& b)
+{
+    const auto t = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+    const unsigned t0 = t[0], t1 = t[1];
+    a = __builtin_bit_cast(float, t0);
+    b = __builtin_bit_cast(float, t1);
+}
+__device__ __forceinline__ void swap_rows(float& a, float& b)
+{
+    const auto t = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
+    const unsigned t0 = t[0], t1 = t[1];
+    a = __builtin_bit_cast(float, t0);
+    b = __builtin_bit_cast(float, t1);
+}
+__device__ __forceinline__ void swap_halves(double& a, double& b)
+{
+    const Words u = __builtin_bit_cast(Words, a), v = __builtin_bit_cast(Words, b);
+    const auto l = __builtin_amdgcn_permlane32_swap(u.lo, v.lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(u.hi, v.hi, false, false);
+    a = __builtin_bit_cast(double, Words{l[0], h[0]});
+    b = __builtin_bit_cast(double, Words{l[1], h[1]});
+}
+__device__ __forceinline__ void swap_rows(double& a, double& b)
+{
+    const Words u = __builtin_bit_cast(Words, a), v = __builtin_bit_cast(Words, b);
+    const auto l = __builtin_amdgcn_permlane16_swap(u.lo, v.lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(u.hi, v.hi, false, false);
+    a = __builtin_bit_cast(double, Words{l[0], h[0]});
+    b = __builtin_bit_cast(double, Words{l[1], h[1]});
+}
+template <int CTRL> __device__ __forceinline__ float dpp(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL> __device__ __forceinline__ double dpp(double v)
+{
+    const Words u = __builtin_bit_cast(Words, v);
+    return __builtin_bit_cast(double, Words{(unsigned)__builtin_amdgcn_update_dpp(0, (int)u.lo, CTRL, 0xF, 0xF, true),
+                                            (unsigned)__builtin_amdgcn_update_dpp(0, (int)u.hi, CTRL, 0xF, 0xF, true)});
+}
+constexpr int kRor8 = 0x128, kHalfMirror = 0x141, kSwap2 = 0x4E, kSwap1 = 0xB1;   // row_ror:8, row_half_mirror, quad_perm
+// sum over the wave in every lane
+template <typename C> __device__ __forceinline__ C wave_sum(C v)
+{
+    v = rows_sum(v);
+    v += dpp<kRor8>(v);
+    v += dpp<kHalfMirror>(v);
+    v += dpp<kSwap2>(v);
+    return v + dpp<kSwap1>(v);
+}
+
+// f(integral constant 0), f(integral constant 1), .., f(integral constant N - 1)
+template <typename Fn, int... K> __device__ __forceinline__ void unrolled(Fn&& f, std::integer_sequence<int, K...>)
+{
+    (f(std::integral_constant<int, K>{}), ...);
+}
+template <int N, typename Fn> __device__ __forceinline__ void unroll(Fn&& f)
+{
+    unrolled(f, std::make_integer_sequence<int, N>{});
+}
+
+// workgroup barrier that orders LDS traffic only (s_waitcnt lgkmcnt(0); gfx9 encoding: vmcnt = 63, expcnt = 7,
+// lgkmcnt = 0): global accesses stay in flight
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __builtin_amdgcn_s_barrier();
+}
 
 }  // namespace svb

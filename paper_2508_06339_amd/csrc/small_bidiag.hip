@@ -18,8 +18,6 @@
 // lines of order one.  That is left to a second run from the start, which only a matrix with such a line pays for: with the
 // branch in every column of the one run a call took up to 5 % longer.  A tail whose squares all underflow gives H = I, and so
 // does, in the second run, one below 2^-96 (f32) or 2^-850 (f64).
-#include <utility>
-
 #include "svb_internal.h"
 #include "lane_ops.h"
 
@@ -27,63 +25,6 @@ namespace svb {
 
 namespace {
 
-template <typename Fn, int... K> __device__ __forceinline__ void unrolled(Fn&& f, std::integer_sequence<int, K...>)
-{
-    (f(std::integral_constant<int, K>{}), ...);
-}
-template <int N, typename Fn> __device__ __forceinline__ void unroll(Fn&& f)
-{
-    unrolled(f, std::make_integer_sequence<int, N>{});
-}
-
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-}
-
-// the lower halves of a and b, and their upper halves / their even and odd rows of sixteen lanes
-__device__ __forceinline__ void swap_halves(float& a, float& b)
-{
-    const auto t = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
-    const unsigned t0 = t[0], t1 = t[1];
-    a = __builtin_bit_cast(float, t0);
-    b = __builtin_bit_cast(float, t1);
-}
-__device__ __forceinline__ void swap_rows(float& a, float& b)
-{
-    const auto t = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, a), __builtin_bit_cast(unsigned, b), false, false);
-    const unsigned t0 = t[0], t1 = t[1];
-    a = __builtin_bit_cast(float, t0);
-    b = __builtin_bit_cast(float, t1);
-}
-__device__ __forceinline__ void swap_halves(double& a, double& b)
-{
-    const Words u = __builtin_bit_cast(Words, a), v = __builtin_bit_cast(Words, b);
-    const auto l = __builtin_amdgcn_permlane32_swap(u.lo, v.lo, false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap(u.hi, v.hi, false, false);
-    a = __builtin_bit_cast(double, Words{l[0], h[0]});
-    b = __builtin_bit_cast(double, Words{l[1], h[1]});
-}
-__device__ __forceinline__ void swap_rows(double& a, double& b)
-{
-    const Words u = __builtin_bit_cast(Words, a), v = __builtin_bit_cast(Words, b);
-    const auto l = __builtin_amdgcn_permlane16_swap(u.lo, v.lo, false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap(u.hi, v.hi, false, false);
-    a = __builtin_bit_cast(double, Words{l[0], h[0]});
-    b = __builtin_bit_cast(double, Words{l[1], h[1]});
-}
-template <int CTRL> __device__ __forceinline__ float dpp(float v)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
-template <int CTRL> __device__ __forceinline__ double dpp(double v)
-{
-    const Words u = __builtin_bit_cast(Words, v);
-    return __builtin_bit_cast(double, Words{(unsigned)__builtin_amdgcn_update_dpp(0, (int)u.lo, CTRL, 0xF, 0xF, true),
-                                            (unsigned)__builtin_amdgcn_update_dpp(0, (int)u.hi, CTRL, 0xF, 0xF, true)});
-}
-constexpr int kRor8 = 0x128, kHalfMirror = 0x141, kSwap2 = 0x4E, kSwap1 = 0xB1;   // row_ror:8, row_half_mirror, quad_perm
 // a's sum in the lanes where `up` is clear, b's in the others, over pairs of lanes that a data-parallel move brings together
 template <int CTRL, typename C> __device__ __forceinline__ C pair_sum(C a, C b, bool up)
 {
@@ -127,16 +68,6 @@ template <int N, typename C> __device__ __forceinline__ C wave_sums(C (&x)[N], i
     else x[0] += dpp<kSwap2>(x[0]);
     return x[0] + dpp<kSwap1>(x[0]);
 }
-// sum over the wave in every lane
-template <typename C> __device__ __forceinline__ C wave_sum(C v)
-{
-    v = rows_sum(v);
-    v += dpp<kRor8>(v);
-    v += dpp<kHalfMirror>(v);
-    v += dpp<kSwap2>(v);
-    return v + dpp<kSwap1>(v);
-}
-
 __device__ __forceinline__ float ldexp_of(float x, int e) { return __builtin_amdgcn_ldexpf(x, e); }
 __device__ __forceinline__ double ldexp_of(double x, int e) { return __builtin_amdgcn_ldexp(x, e); }
 

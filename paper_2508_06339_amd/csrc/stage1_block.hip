@@ -10,6 +10,7 @@
 // W and W2 are stored with c running fastest; V in both orders (Vt: c fastest), so that every operand but
 // C is contiguous along the contraction and C is always touched along its contiguous direction.
 #include "svb_internal.h"
+#include "lane_ops.h"
 #include "mfma_gemm.h"
 
 namespace svb {
@@ -90,13 +91,6 @@ template <typename T> struct Buf1<float, T> {   // 16-bit storage
         __builtin_amdgcn_raw_buffer_store_b16(u, r, v, s, 0);
     }
 };
-
-// workgroup barrier that orders LDS traffic only: global accesses stay in flight
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-}
 
 // ---- C += A B^T on tiles of BR x BJ -------------------------------------------------------------------
 // C(r, j) at r * lda + j (j contiguous), A(r, k) at r * lda_r + k, B(j, k) at j * ldb_j + k; K a multiple of

@@ -80,13 +80,6 @@ template <typename C, int N> __device__ __forceinline__ void lds_stn(C* p, const
     }
 }
 
-// workgroup barrier that orders LDS traffic only (s_waitcnt lgkmcnt(0)): global accesses stay in flight
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    __builtin_amdgcn_s_barrier();
-}
-
 // f(0), f(1), .. with the index as a compile-time constant
 template <typename Fn, int... K> __device__ __forceinline__ void static_steps(Fn&& f, std::integer_sequence<int, K...>)
 {

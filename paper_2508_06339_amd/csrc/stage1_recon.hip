@@ -22,8 +22,6 @@
 // range, sets *stop: the block_sub_kernel of this and of every later half-sweep then leaves the matrix as it is, and the
 // host goes on with the tree of domain QRs, which takes any panel, from this half-sweep on.
 // Trailing columns of zeros (padding) are allowed: their reflectors are identities.
-#include <utility>
-
 #include "svb_internal.h"
 #include "lane_ops.h"
 #include "mfma_frag.h"
@@ -36,15 +34,6 @@ constexpr double kMinRho = 0x1p-22;
 constexpr double kMaxInv = 0x1p26;   // of ||D R^-1||_F^2, one pass
 constexpr double kMaxE = 0x1p-29;    // of max |E|, the first of two passes
 constexpr int kGramRows = 128;
-
-template <typename Fn, int... K> __device__ __forceinline__ void unrolled(Fn&& f, std::integer_sequence<int, K...>)
-{
-    (f(std::integral_constant<int, K>{}), ...);
-}
-template <int N, typename Fn> __device__ __forceinline__ void unroll(Fn&& f)
-{
-    unrolled(f, std::make_integer_sequence<int, N>{});
-}
 
 using F64 = Frag<double>;
 typedef F64::acc_t d4;
@@ -270,23 +259,6 @@ __device__ __forceinline__ bool chol16(double* m, int ld, double* inv, int ldi, 
     return !__any(!(piv > lim));
 }
 
-// swap of the odd rows of lanes of a with the even rows of b / of a's upper half with b's lower half
-__device__ __forceinline__ void swap_rows(double& a, double& b)
-{
-    const Words u = __builtin_bit_cast(Words, a), v = __builtin_bit_cast(Words, b);
-    const auto l = __builtin_amdgcn_permlane16_swap(u.lo, v.lo, false, false);
-    const auto h = __builtin_amdgcn_permlane16_swap(u.hi, v.hi, false, false);
-    a = __builtin_bit_cast(double, Words{l[0], h[0]});
-    b = __builtin_bit_cast(double, Words{l[1], h[1]});
-}
-__device__ __forceinline__ void swap_halves(double& a, double& b)
-{
-    const Words u = __builtin_bit_cast(Words, a), v = __builtin_bit_cast(Words, b);
-    const auto l = __builtin_amdgcn_permlane32_swap(u.lo, v.lo, false, false);
-    const auto h = __builtin_amdgcn_permlane32_swap(u.hi, v.hi, false, false);
-    a = __builtin_bit_cast(double, Words{l[0], h[0]});
-    b = __builtin_bit_cast(double, Words{l[1], h[1]});
-}
 // x[j] in row q of lanes <-> x[q] in row j
 __device__ __forceinline__ void transpose4(double (&x)[4])
 {
@@ -396,13 +368,6 @@ template <typename C> struct ReconArgs {
     int* stop; int hs;               // half-sweep number, from 0
     int above;                       // rows of V above the sub-panel (zeros there; R's block above it comes from P)
 };
-// workgroup barrier that orders LDS traffic only: global accesses stay in flight
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-    __builtin_amdgcn_s_barrier();
-}
-
 template <int NBP> constexpr int kReconThreads = NBP == 64 ? 768 : 512;
 template <typename C, int NBP, int MODE>
 __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconArgs<C> a)

@@ -45,16 +45,10 @@ constexpr int kSweepDone = 0x7fffffff;
 // by another all the time (with 4 bytes between them the reduction at n = 8192, nb = 32 took 10.8 ms in f32, 8.8 so).
 constexpr int kProgressStride = 8;
 
-// Workgroup barrier that orders LDS traffic only: s_waitcnt lgkmcnt(0) (gfx9 encoding:
-// vmcnt = 63, expcnt = 7, lgkmcnt = 0), then s_barrier.  __syncthreads() would also wait for
-// every outstanding global load and store, i.e. for the block prefetches that are meant to
-// stay in flight across the phases of a step; visibility of global data between workgroups
-// is handled separately (stores_done below, fences at the ends of a sweep).
-__device__ __forceinline__ void lds_barrier()
-{
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    __builtin_amdgcn_s_barrier();
-}
+// Barriers inside a workgroup are lds_barrier(): __syncthreads() would also wait for every outstanding
+// global load and store, i.e. for the block prefetches that are meant to stay in flight across the
+// phases of a step; visibility of global data between workgroups is handled separately (stores_done
+// below, fences at the ends of a sweep).
 // Every band access of this kernel is a device-scope atomic (written through to, and read
 // from, the level all compute dies share), so publishing a step needs no cache write-back and
 // consuming one no invalidate: the writer only waits until its stores have been acknowledged
