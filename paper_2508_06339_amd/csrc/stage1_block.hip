@@ -94,7 +94,8 @@ template <typename T> struct Buf1<float, T> {   // 16-bit storage
 
 // ---- C += A B^T on tiles of BR x BJ -------------------------------------------------------------------
 // C(r, j) at r * lda + j (j contiguous), A(r, k) at r * lda_r + k, B(j, k) at j * ldb_j + k; K a multiple of
-// 32; nr and nj multiples of 32.  Nothing is written where *stop is set.
+// 32; nr and nj multiples of 32.  Nothing is done where *stop is set.  (Looked at behind the first chunk, where the flag
+// would have come by itself: f32 32768, nb = 128 1185 ms a call against 1168; without: 1167.)
 // Four waves in a square.  A lane's column of an accumulator tile is j, so C moves along its contiguous
 // direction.  Tiles are numbered so that an XCD works on a contiguous range of them, eight columns of tiles
 // at a time (their operands stay in its L2).
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(256, sizeof(C) == 4 ? 3 : 2) void block_sub_kernel(
     __shared__ __align__(16) C Bs[BJ * LD];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = lane % TM, g = lane / TM;
-    const int halt = *stop;
+    if (*stop) return;
 
     const int ntr = (nr + BR - 1) / BR, ntj = (nj + BJ - 1) / BJ, nt = ntr * ntj;
     const int per = (nt + 7) / 8;
@@ -187,7 +188,6 @@ __global__ __launch_bounds__(256, sizeof(C) == 4 ? 3 : 2) void block_sub_kernel(
                     for (int b = 0; b < NJ; ++b) acc[a][b] = M::mma(fa[a][q], fb[b][q], acc[a][b]);
         }
     }
-    if (halt) return;
 #pragma unroll
     for (int a = 0; a < NR; ++a)
 #pragma unroll
@@ -204,10 +204,11 @@ __global__ __launch_bounds__(256, sizeof(C) == 4 ? 3 : 2) void block_sub_kernel(
 // Wp(s, q, c) at (s * nq + q) * NBW + c: the sum over p in [s * chunk, (s + 1) * chunk) of V(p, c) C(p, q),
 // V(p, c) at p + c * ldv.  len and chunk multiples of 32, nq a multiple of 32.
 // QR orientation: C's tile is staged as it lies, p fastest; LQ: q fastest, its operand read element by element.
+// *stop as in block_sub_kernel.
 template <typename T, typename C, int NBW, int QT, bool LQ>
 __global__ __launch_bounds__(256, 2) void block_wt_kernel(const T* __restrict__ Cm, int64_t lda, int len, int nq,
                                                        const C* __restrict__ V, int64_t ldv, int chunk,
-                                                       C* __restrict__ Wp)
+                                                       C* __restrict__ Wp, const int* __restrict__ stop)
 {
     using M = Mm<C>;
     typedef typename M::acc_t acc_t;
@@ -225,6 +226,7 @@ __global__ __launch_bounds__(256, 2) void block_wt_kernel(const T* __restrict__ 
     const int i = lane % TM, g = lane / TM;
     const int q0 = blockIdx.x * QT;
     const int pbeg = blockIdx.y * chunk, pend = min(len, pbeg + chunk);
+    if (*stop) return;
 
     C rv[NPV][VK], rc[NPC][VK];
     auto fetch = [&](int p0) {   // (beyond nq the last one again: those sums are not stored)
@@ -384,11 +386,11 @@ __global__ __launch_bounds__(256) void block_tw_kernel(const C* __restrict__ Wp,
 
 template <typename T, typename C, int NBW, int QT>
 void wt_launch(bool lq, const T* Cm, int64_t lda, int len, int nq, const C* V, int64_t ldv, int chunk, int ns, C* Wp,
-               hipStream_t s)
+               const int* stop, hipStream_t s)
 {
     const dim3 grid((unsigned)((nq + QT - 1) / QT), (unsigned)ns);
-    if (lq) hipLaunchKernelGGL((block_wt_kernel<T, C, NBW, QT, true>), grid, dim3(256), 0, s, Cm, lda, len, nq, V, ldv, chunk, Wp);
-    else hipLaunchKernelGGL((block_wt_kernel<T, C, NBW, QT, false>), grid, dim3(256), 0, s, Cm, lda, len, nq, V, ldv, chunk, Wp);
+    if (lq) hipLaunchKernelGGL((block_wt_kernel<T, C, NBW, QT, true>), grid, dim3(256), 0, s, Cm, lda, len, nq, V, ldv, chunk, Wp, stop);
+    else hipLaunchKernelGGL((block_wt_kernel<T, C, NBW, QT, false>), grid, dim3(256), 0, s, Cm, lda, len, nq, V, ldv, chunk, Wp, stop);
 }
 
 }  // namespace
@@ -421,15 +423,15 @@ static WtPlan wt_plan(int nbw, int64_t len, int64_t nq, int64_t qmax)
 
 template <typename T, typename C>
 int launch_block_wt(int nbw, bool lq, const T* Cm, int64_t lda, int64_t len, int64_t nq, int64_t qmax, const C* V,
-                    int64_t ldv, C* Wp, hipStream_t s)
+                    int64_t ldv, C* Wp, const int* stop, hipStream_t s)
 {
     const WtPlan p = wt_plan(nbw, len, nq, qmax);
     const int l = (int)len, q = (int)nq;
-    if (nbw == 32) wt_launch<T, C, 32, 128>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, s);
-    else if (nbw == 64 && p.qt == 64) wt_launch<T, C, 64, 64>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, s);
-    else if (nbw == 64) wt_launch<T, C, 64, 128>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, s);
-    else if (p.qt == 64) wt_launch<T, C, 128, 64>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, s);
-    else wt_launch<T, C, 128, 128>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, s);
+    if (nbw == 32) wt_launch<T, C, 32, 128>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);
+    else if (nbw == 64 && p.qt == 64) wt_launch<T, C, 64, 64>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);
+    else if (nbw == 64) wt_launch<T, C, 64, 128>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);
+    else if (p.qt == 64) wt_launch<T, C, 128, 64>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);
+    else wt_launch<T, C, 128, 128>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);
     return p.ns;
 }
 
@@ -463,7 +465,7 @@ void launch_block_sub(bool lq, T* Cm, int64_t lda, int64_t len, int64_t nq, int 
 }
 
 #define SVB_INST(T, C)                                                                                              \
-    template int launch_block_wt<T, C>(int, bool, const T*, int64_t, int64_t, int64_t, int64_t, const C*, int64_t, C*, hipStream_t); \
+    template int launch_block_wt<T, C>(int, bool, const T*, int64_t, int64_t, int64_t, int64_t, const C*, int64_t, C*, const int*, hipStream_t); \
     template void launch_block_sub<T, C>(bool, T*, int64_t, int64_t, int64_t, int, const C*, int64_t, const C*, int64_t, const int*, hipStream_t)
 SVB_INST(float, float);
 SVB_INST(double, double);

@@ -20,7 +20,9 @@
 //     leaves out is N^T N, so E itself is looked at, and at most kMaxE is accepted (nb E^2 at most 2^-52).
 // A panel that is refused, that has a pivot below kMinRho times its diagonal entry of G, or whose sums of squares leave the
 // range, sets *stop: the block_sub_kernel of this and of every later half-sweep then leaves the matrix as it is, and the
-// host goes on with the tree of domain QRs, which takes any panel, from this half-sweep on.
+// host goes on with the tree of domain QRs, which takes any panel, from this half-sweep on.  What was launched behind it
+// ends early: the kernels of a panel read the flag at their start and look at it once their first operands have come, so
+// that it is not waited for alone; the sums and small products in between run on what there is.
 // Trailing columns of zeros (padding) are allowed: their reflectors are identities.
 #include "svb_internal.h"
 #include "lane_ops.h"
@@ -45,7 +47,7 @@ __device__ __forceinline__ int ublk(int bi, int bj) { return bj * (bj + 1) / 2 +
 // block triangle, row-major.
 template <typename T, typename C, int NBP, bool LQ>
 __global__ __launch_bounds__(256) void panel_gram_kernel(const T* __restrict__ A, int64_t lda, int len, C* P, int64_t ldp,
-                                                         double* __restrict__ Gp)
+                                                         double* __restrict__ Gp, const int* __restrict__ stop)
 {
     constexpr int RB = kGramRows, NBK = NBP / 16, NT = NBK * (NBK + 1) / 2;
     constexpr int LDC = RB + (sizeof(C) == 4 ? 4 : 2);   // QR: [c][p]
@@ -55,6 +57,7 @@ __global__ __launch_bounds__(256) void panel_gram_kernel(const T* __restrict__ A
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i = lane & 15, g = lane >> 4;
     const int p0 = blockIdx.x * RB, np = min(RB, len - p0);
+    const int halt = *stop;
     if constexpr (LQ) {
         for (int idx = tid; idx < RB * NBP / VK; idx += 256) {
             const int p = idx / (NBP / VK), c = idx % (NBP / VK) * VK;
@@ -84,6 +87,7 @@ __global__ __launch_bounds__(256) void panel_gram_kernel(const T* __restrict__ A
         }
         __syncthreads();
     }
+    if (halt) return;
     double* out = Gp + (int64_t)blockIdx.x * NT * 256;
     constexpr int NTW = (NT + 3) / 4;
     d4 acc[NTW];
@@ -365,7 +369,7 @@ template <typename C> struct ReconArgs {
     C* V; int64_t ldv; C* Vt; int64_t ldvt;   // the sub-panel's top block in both orders
     C* T; int64_t ldt;
     C* band; int64_t ldab, row0, col0; int lq, nb;   // where S R goes: the sub-panel's corner of the band
-    int* stop; int hs;               // half-sweep number, from 0
+    int* stop; int* host_stop; int hs;   // half-sweep number, from 0
     int above;                       // rows of V above the sub-panel (zeros there; R's block above it comes from P)
 };
 template <int NBP> constexpr int kReconThreads = NBP == 64 ? 768 : 512;
@@ -397,6 +401,11 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
     }
     auto blk = [](double* m, int bi, int bj) { return m + bi * 16 * LD + bj * 16; };
 
+    auto refuse = [&] {
+        *a.stop = a.hs + 1;
+        __hip_atomic_store(a.host_stop, a.hs + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    };
+
     // ---- G (every 256 threads take a share of the partial sums); E = 0; the panel's top rows in B
     if (tid == 0) sh_bad = 0;
     {
@@ -423,6 +432,7 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
             for (int b = 0; b < NT; ++b) o[b * 256 + el] = s[b];
         }
         lds_barrier();
+        if (halted) return;
         if (!share) {
 #pragma unroll
             for (int bj = 0; bj < NBK; ++bj)
@@ -588,7 +598,7 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
             a.X[idx] = k <= c ? E[c * LD + k] : 0.0;
             a.R1[idx] = c <= k ? G[c * LD + k] : 0.0;   // row c, column k
         }
-        if (tid == 0 && sh_bad && !halted) *a.stop = a.hs + 1;
+        if (tid == 0 && sh_bad) refuse();
         return;
     }
     RT_MARK(2);
@@ -647,8 +657,8 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
     }
     RT_MARK(3);
     // ---- S R to the band
-    if (sh_bad && !halted && tid == 0) *a.stop = a.hs + 1;
-    if (sh_bad || halted) return;
+    if (sh_bad && tid == 0) refuse();
+    if (sh_bad) return;
     // entry (ri, ci) of R: band entry (row0 + ri, col0 + ci) in a QR sweep, (row0 + ci, col0 + ri) in an LQ sweep
     C* const base = a.band + (a.row0 - a.col0 + 2 * a.nb - 1) + a.col0 * a.ldab;
     const int64_t sr = a.lq ? a.ldab - 1 : 1, sc = a.lq ? 1 : a.ldab - 1;
@@ -684,13 +694,14 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
 template <typename C, int NBP, bool FIRST>
 __global__ __launch_bounds__(256) void panel_apply_kernel(const C* A, int64_t lda, int len, const double* __restrict__ X,
                                                           const double* __restrict__ R1, C* out, int64_t ldo, C* outt,
-                                                          int64_t ldt)
+                                                          int64_t ldt, const int* __restrict__ stop)
 {
     constexpr int NBK = NBP / 16, LDX = NBP + 2;
     __shared__ __align__(16) double Xs[NBP * LDX];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i = lane & 15, g = lane >> 4;
     const int p0 = blockIdx.x * 64 + wave * 16;
+    const int halt = *stop;
     C b[NBP / 4];
     if (p0 < len) {
 #pragma unroll
@@ -698,7 +709,7 @@ __global__ __launch_bounds__(256) void panel_apply_kernel(const C* A, int64_t ld
     }
     for (int idx = tid; idx < NBP * NBP; idx += 256) Xs[idx / NBP * LDX + idx % NBP] = X[idx];
     __syncthreads();
-    if (p0 >= len) return;
+    if (halt || p0 >= len) return;
     d4 acc[NBK];
 #pragma unroll
     for (int c = 0; c < NBK; ++c) acc[c] = zero4();
@@ -806,11 +817,11 @@ template <typename C, int NBP, int MODE> void recon_launch(const ReconArgs<C>& a
 }
 
 template <typename T, typename C, int NBP, bool LQ>
-int gram(const T* A, int64_t lda, int64_t len, C* P, int64_t ldp, double* Gp, double** sum, hipStream_t s)
+int gram(const T* A, int64_t lda, int64_t len, C* P, int64_t ldp, double* Gp, double** sum, const int* stop, hipStream_t s)
 {
     constexpr int NT = NBP / 16 * (NBP / 16 + 1) / 2;
     const int n = (int)((len + kGramRows - 1) / kGramRows);
-    hipLaunchKernelGGL((panel_gram_kernel<T, C, NBP, LQ>), dim3(n), dim3(256), 0, s, A, lda, (int)len, P, ldp, Gp);
+    hipLaunchKernelGGL((panel_gram_kernel<T, C, NBP, LQ>), dim3(n), dim3(256), 0, s, A, lda, (int)len, P, ldp, Gp, stop);
     *sum = Gp;
     if (n <= 16) return n;
     const int m = (n + 31) / 32;
@@ -828,22 +839,22 @@ void subpanel(const ReconPanel<T, C>& a, int64_t off, int64_t sub0, hipStream_t 
     C* P = a.P + off + sub0 * a.ldv;
     double* Gs = nullptr;
     int np;
-    if (a.src && a.lq) np = gram<T, C, NBP, true>(a.src, a.lda, len, P, a.ldv, a.Gp, &Gs, s);
-    else if (a.src) np = gram<T, C, NBP, false>(a.src, a.lda, len, P, a.ldv, a.Gp, &Gs, s);
-    else np = gram<C, C, NBP, false>(P, a.ldv, len, (C*)nullptr, 0, a.Gp, &Gs, s);
+    if (a.src && a.lq) np = gram<T, C, NBP, true>(a.src, a.lda, len, P, a.ldv, a.Gp, &Gs, a.stop, s);
+    else if (a.src) np = gram<T, C, NBP, false>(a.src, a.lda, len, P, a.ldv, a.Gp, &Gs, a.stop, s);
+    else np = gram<C, C, NBP, false>(P, a.ldv, len, (C*)nullptr, 0, a.Gp, &Gs, a.stop, s);
     ReconArgs<C> r{};
     r.Gp = Gs; r.np = np; r.P = P; r.ldp = a.ldv; r.X = a.X; r.R1 = a.X + NBP * NBP;
     r.V = a.V + off + sub0 * a.ldv; r.ldv = a.ldv; r.Vt = a.Vt + off * a.nb + sub0; r.ldvt = a.nb;
     r.T = a.Tf + sub0 * a.nb + sub0; r.ldt = a.nb;
     r.band = a.band; r.ldab = a.ldab;
     r.row0 = a.row0 + off; r.col0 = a.col0 + off;   // (off = sub0: rows and columns of the sub-panel's corner of R)
-    r.lq = a.lq; r.nb = a.nb; r.stop = a.stop; r.hs = a.hs; r.above = (int)off;
+    r.lq = a.lq; r.nb = a.nb; r.stop = a.stop; r.host_stop = a.host_stop; r.hs = a.hs; r.above = (int)off;
     const dim3 rest((unsigned)((len - NBP + 63) / 64));
     if constexpr (sizeof(C) == 8) {
         recon_launch<C, NBP, kFirst>(r, s);
         hipLaunchKernelGGL((panel_apply_kernel<C, NBP, true>), dim3((unsigned)((len + 63) / 64)), dim3(256), 0, s, P, a.ldv,
-                           (int)len, a.X, r.R1, P, a.ldv, (C*)nullptr, (int64_t)0);
-        r.np = gram<C, C, NBP, false>(P, a.ldv, len, (C*)nullptr, 0, a.Gp, &Gs, s);
+                           (int)len, a.X, r.R1, P, a.ldv, (C*)nullptr, (int64_t)0, a.stop);
+        r.np = gram<C, C, NBP, false>(P, a.ldv, len, (C*)nullptr, 0, a.Gp, &Gs, a.stop, s);
         r.Gp = Gs;
         recon_launch<C, NBP, kSecond>(r, s);
     } else {
@@ -851,7 +862,7 @@ void subpanel(const ReconPanel<T, C>& a, int64_t off, int64_t sub0, hipStream_t 
     }
     if (len > NBP)
         hipLaunchKernelGGL((panel_apply_kernel<C, NBP, false>), rest, dim3(256), 0, s, P + NBP, a.ldv, (int)(len - NBP), a.X,
-                           (const double*)nullptr, r.V + NBP, a.ldv, r.Vt + (int64_t)NBP * a.nb, (int64_t)a.nb);
+                           (const double*)nullptr, r.V + NBP, a.ldv, r.Vt + (int64_t)NBP * a.nb, (int64_t)a.nb, a.stop);
 }
 
 }  // namespace
@@ -875,11 +886,11 @@ template <typename T, typename C> void launch_panel_recon(const ReconPanel<T, C>
     a.src = nullptr;
     subpanel<T, C, 64>(a, 0, 0, s);
     C* right = a.P + 64 * a.ldv;
-    int ns = launch_block_wt<C, C>(64, false, right, a.ldv, a.len, 64, a.qmax, a.V, a.ldv, a.Wp, s);
+    int ns = launch_block_wt<C, C>(64, false, right, a.ldv, a.len, 64, a.qmax, a.V, a.ldv, a.Wp, a.stop, s);
     launch_block_tw<C>(64, a.Wp, ns, 64, a.Tf, a.nb, a.W2, s);
     launch_block_sub<C, C>(false, right, a.ldv, a.len, 64, 64, a.Vt, a.nb, a.W2, 64, a.stop, s);
     subpanel<T, C, 64>(a, 64, 64, s);
-    ns = launch_block_wt<C, C>(64, false, a.V + 64 * a.ldv, a.ldv, a.len, 64, a.qmax, a.V, a.ldv, a.Wp, s);
+    ns = launch_block_wt<C, C>(64, false, a.V + 64 * a.ldv, a.ldv, a.len, 64, a.qmax, a.V, a.ldv, a.Wp, a.stop, s);
     static bool attr_set = false;
     const size_t bytes = 4 * 64 * 66 * sizeof(double);
     if (!attr_set) {

@@ -353,7 +353,9 @@ struct Lookahead {
     hipEvent_t lvl[2][kMaxLevels] = {}, udone[2] = {nullptr, nullptr};
     // stage boundaries of svb_svdvals, reused by every call
     hipEvent_t stage[4] = {nullptr, nullptr, nullptr, nullptr};
-    int* stop = nullptr;   // pinned: where ge2gb_block stopped
+    // ge2gb_block: where it stopped (pinned, written by the kernel that refuses a panel), and how far the stream has come
+    int *stop = nullptr, *stop_dev = nullptr;
+    hipEvent_t look[2] = {nullptr, nullptr};
     bool ok = false, tried = false;
     bool init(const Switches& sw)
     {
@@ -377,7 +379,11 @@ struct Lookahead {
             return false;
         for (int i = 0; i < 4; ++i)
             if (hipEventCreate(&stage[i]) != hipSuccess) return false;
-        if (hipHostMalloc(reinterpret_cast<void**>(&stop), sizeof(int), hipHostMallocDefault) != hipSuccess) return false;
+        for (int i = 0; i < 2; ++i)
+            if (hipEventCreateWithFlags(&look[i], hipEventDisableTiming) != hipSuccess) return false;
+        if (hipHostMalloc(reinterpret_cast<void**>(&stop), sizeof(int), hipHostMallocCoherent) != hipSuccess ||
+            hipHostGetDevicePointer(reinterpret_cast<void**>(&stop_dev), stop, 0) != hipSuccess)
+            return false;
         ok = true;
         // released while the HIP runtime is still up (handlers registered later run earlier)
         std::atexit([] { g_la_release(); });
@@ -397,6 +403,7 @@ struct Lookahead {
         (void)hipEventDestroy(join);
         (void)hipEventDestroy(join_u);
         for (int i = 0; i < 4; ++i) (void)hipEventDestroy(stage[i]);
+        for (int i = 0; i < 2; ++i) (void)hipEventDestroy(look[i]);
         (void)hipHostFree(stop);
         (void)hipStreamDestroy(u);
         (void)hipStreamDestroy(m);
@@ -624,6 +631,9 @@ template <typename C> constexpr int64_t block_rows() { return sizeof(C) == 8 ? 2
 // Stage 1 with one block reflector per panel (stage1_recon.hip, stage1_block.hip), as far as it goes: up to the
 // panels of a single tile, or to a panel that Cholesky QR does not serve.  All on the caller's stream; returns the
 // half-sweep ge2gb_pipeline has to go on with, after waiting for the stream, or a negative status.
+// Every kLook half-sweeps the host waits for the ones launched kLook earlier and looks whether a panel has been refused:
+// at most 2 kLook half-sweeps are launched in vain, and the stream always holds kLook of them.
+constexpr int kLook = 8;
 template <typename T, typename C>
 int ge2gb_block(int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* band, int64_t ldab,
                 unsigned char* work, const Carve& cv, hipStream_t s)
@@ -643,9 +653,17 @@ int ge2gb_block(int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* band, 
     rp.Gp = reinterpret_cast<double*>(work + cv.off_bG);
     const int nbp = nb < 64 ? nb : 64;
     rp.X = rp.Gp + (recon_scratch_doubles(rows, nb) - 2 * (size_t)nbp * nbp);
-    rp.band = band; rp.ldab = ldab; rp.stop = stop;
+    rp.band = band; rp.ldab = ldab; rp.stop = stop; rp.host_stop = g_la.stop_dev;
+    volatile const int* const seen = g_la.stop;
+    *g_la.stop = 0;
     int hs = 0;
     for (;; ++hs) {
+        if (hs > 0 && hs % kLook == 0) {
+            const int b = hs / kLook;
+            if (hipEventRecord(g_la.look[b & 1], s) != hipSuccess) return -1;
+            if (b > 1 && hipEventSynchronize(g_la.look[(b - 1) & 1]) != hipSuccess) return -1;
+            if (*seen) break;
+        }
         const int64_t k = hs / 2;
         const bool lq = hs & 1;
         const int64_t row0 = k * nb, col0 = lq ? (k + 1) * nb : k * nb;
@@ -659,15 +677,13 @@ int ge2gb_block(int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* band, 
         prof_end(s);
         T* Cb = A + (lq ? (k + 1) * nb : k * nb) + (k + 1) * nb * lda;
         prof_begin(SVB_PROF_UPDATE, s, 4.0 * (double)len * nb * (double)qlen, 3.0 * (double)len * (double)qlen * sizeof(T));
-        const int ns = launch_block_wt<T, C>(nb, lq, Cb, lda, len, qlen, rp.qmax, rp.V, rp.ldv, rp.Wp, s);
+        const int ns = launch_block_wt<T, C>(nb, lq, Cb, lda, len, qlen, rp.qmax, rp.V, rp.ldv, rp.Wp, stop, s);
         launch_block_tw<C>(nb, rp.Wp, ns, qlen, rp.Tf, nb, rp.W2, s);
         launch_block_sub<T, C>(lq, Cb, lda, len, qlen, nb, rp.Vt, nb, rp.W2, nb, stop, s);
         prof_end(s);
     }
-    if (hipMemcpyAsync(g_la.stop, stop, sizeof(int), hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return -1;
-    return *g_la.stop ? *g_la.stop - 1 : hs;
+    if (hipStreamSynchronize(s) != hipSuccess) return -1;
+    return *seen ? *seen - 1 : hs;
 }
 
 template <typename T, typename C>

@@ -180,14 +180,15 @@ template <typename T, typename C> struct ReconPanel {
     int64_t ldv, qmax;                     // leading dimension of P and V (at least len); what Wp is sized for
     double *Gp, *X;                        // recon_scratch_doubles(): partial Gram sums; X and the first R
     C* band; int64_t ldab, row0, col0;
-    int* stop; int hs;
+    int* stop; int hs;                     // set to hs + 1 where a panel is refused
+    int* host_stop;                        // the same, in host memory
 };
 template <typename T, typename C> void launch_panel_recon(const ReconPanel<T, C>& a, hipStream_t s);
 size_t recon_scratch_doubles(int64_t rows, int nb);
 // the products of a half-sweep (stage1_block.hip); launch_block_wt returns the number of partial sums
 template <typename T, typename C>
 int launch_block_wt(int nbw, bool lq, const T* Cm, int64_t lda, int64_t len, int64_t nq, int64_t qmax, const C* V,
-                    int64_t ldv, C* Wp, hipStream_t s);
+                    int64_t ldv, C* Wp, const int* stop, hipStream_t s);
 template <typename C>
 void launch_block_tw(int nbw, const C* Wp, int ns, int64_t nq, const C* T, int64_t ldt, C* W2, hipStream_t s);
 template <typename T, typename C>
