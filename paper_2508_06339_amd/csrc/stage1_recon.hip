@@ -502,13 +502,20 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
             if (!chol16(blk(G, t, t), LD, blk(E, t, t), LD, g0 + t * 16, i, g) && lane == 0) sh_bad = 1;
         }
         if (MODE == kFull && t == NBK && wave == 0) {
-            // ||D R^-1||_F^2 beside the last LU block (R^-T is whole by now)
-            double f = 0;
-            for (int idx = lane; idx < NBP * NBP; idx += 64) {
-                const int k = idx % NBP, c = idx / NBP;
-                const double x = k <= c ? E[c * LD + k] : 0.0;
-                f = fma(g0[k] * x, x, f);
-            }
+            // ||D R^-1||_F^2 beside the last LU block (R^-T is whole by now), eight entries a lane at a time: one by one the
+            // reads' latency made this longer than that block, 2.4 us a panel at NBP = 64
+            constexpr int CS = 64 / NBP;
+            const int k = lane % NBP, c0 = lane / NBP;
+            double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll 1
+            for (int c = c0; c < NBP; c += 8 * CS)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    double x = E[(c + u * CS) * LD + k];
+                    x = k <= c + u * CS ? x : 0.0;
+                    s[u] = fma(x, x, s[u]);
+                }
+            double f = (((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]))) * g0[k];
             for (int off = 32; off > 0; off >>= 1) f += __shfl_xor(f, off, kWave);
             if (!(f <= kMaxInv) && lane == 0) sh_bad = 1;
         }
