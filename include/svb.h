@@ -29,7 +29,7 @@
  *     (every sum is formed in f32, as the paper does for half precision,
  *     Section 4.3; the band, the bidiagonal and the result are f32).
  *     svb_svdvals works on an f32 copy in the workspace of up to 8192 rows; of
- *     more, and in svb_ge2gb, the transformed matrix is kept in 16 bits and the
+ *     more, in svb_ge2gb, and where the workspace has no room for it, the transformed matrix is kept in 16 bits and the
  *     trailing update multiplies on the 16-bit matrix instructions with its
  *     f32 operands split into 16-bit terms, which keeps their f32 accuracy.
  *   - nb (the paper's TILESIZE): 32, 64 or 128; 0 lets the library choose
@@ -83,7 +83,11 @@ typedef enum {
  * [host] dev_bytes, host_bytes: outputs (either may be NULL).  host_bytes is
  * always 0 (host scratch is allocated internally).  A matrix that is not a
  * whole number of tiles in both directions, or has m < n, is copied into the
- * workspace, which then includes room for the zero-padded copy.
+ * workspace, which then includes room for the zero-padded copy; a matrix in
+ * 16-bit storage of more than 256 and at most 8192 rows (columns, if m < n) is copied in f32.
+ * svb_ge2gb uses neither that copy nor the block reflectors of svb_svdvals'
+ * stage 1 and asks only for what the tree of domain QRs needs; svb_svdvals with
+ * a workspace that has room for that tree only uses the tree.
  */
 int svb_workspace_bytes(svb_dtype dt, int64_t m, int64_t n, int nb,
                         size_t* dev_bytes, size_t* host_bytes);

@@ -9,6 +9,8 @@
 //   block_sub_kernel   C += V W2 (C is read and written once)
 // W and W2 are stored with c running fastest; V in both orders (Vt: c fastest), so that every operand but
 // C is contiguous along the contraction and C is always touched along its contiguous direction.
+#include <algorithm>
+
 #include "svb_internal.h"
 #include "lane_ops.h"
 #include "mfma_gemm.h"
@@ -396,24 +398,28 @@ void wt_launch(bool lq, const T* Cm, int64_t lda, int len, int nq, const C* V, i
 }  // namespace
 
 // how the contraction over p is split: enough workgroups for the chip, at least 64 elements each, and
-// partial sums within the workspace (block_wp_elems).  1024 workgroups where the size allows: two to four fit on
+// partial sums within the workspace (block_wp_cols).  1024 workgroups where the size allows: two to four fit on
 // a compute unit, and with 512 they all begin and end together (f32 32768, nb = 128: 1208 ms a call with 512, 1198
 // with 768, 1177 with 1024, as with 2048 or 3072; f64 16384, nb = 128: 509, 507, 502; f32 16384, nb = 64: 232, 229, 227;
 // no difference at 4096 and 8192)
-static int64_t wp_cap(int64_t qmax) { return 4 * qmax > 32768 ? 4 * qmax : 32768; }
-int64_t block_wp_elems(int64_t qmax, int nb) { return wp_cap(qmax) * nb; }
+constexpr int64_t kMaxRanges = 64;   // (block_tw_kernel adds them up one after the other)
+static int64_t max_ranges(int64_t len) { return std::max<int64_t>(1, std::min(len / 64, kMaxRanges)); }
+int64_t block_wp_cols(int64_t rows, int64_t cols)
+{
+    const int64_t most = std::max(cols * max_ranges(rows), rows * max_ranges(cols));   // (a QR and an LQ sweep)
+    return std::min(most, std::max<int64_t>(4 * rows, 32768));
+}
 
 struct WtPlan { int qt, ns, chunk; };
-static WtPlan wt_plan(int nbw, int64_t len, int64_t nq, int64_t qmax)
+static WtPlan wt_plan(int nbw, int64_t len, int64_t nq, int64_t wp_cols)
 {
     WtPlan p;
     p.qt = nbw == 32 ? 128 : (nq >= 128 * 128 ? 128 : 64);
     const int64_t strips = (nq + p.qt - 1) / p.qt;
     int64_t ns = (1024 + strips - 1) / strips;
-    const int64_t room = wp_cap(qmax) / nq;
+    const int64_t room = wp_cols / nq;
     if (ns > room) ns = room;
-    if (ns > len / 64) ns = len / 64;
-    if (ns > 64) ns = 64;   // (block_tw_kernel adds them up one after the other)
+    if (ns > max_ranges(len)) ns = max_ranges(len);
     if (ns < 1) ns = 1;
     int64_t chunk = ((len + ns - 1) / ns + 31) / 32 * 32;
     p.chunk = (int)chunk;
@@ -422,10 +428,10 @@ static WtPlan wt_plan(int nbw, int64_t len, int64_t nq, int64_t qmax)
 }
 
 template <typename T, typename C>
-int launch_block_wt(int nbw, bool lq, const T* Cm, int64_t lda, int64_t len, int64_t nq, int64_t qmax, const C* V,
+int launch_block_wt(int nbw, bool lq, const T* Cm, int64_t lda, int64_t len, int64_t nq, int64_t wp_cols, const C* V,
                     int64_t ldv, C* Wp, const int* stop, hipStream_t s)
 {
-    const WtPlan p = wt_plan(nbw, len, nq, qmax);
+    const WtPlan p = wt_plan(nbw, len, nq, wp_cols);
     const int l = (int)len, q = (int)nq;
     if (nbw == 32) wt_launch<T, C, 32, 128>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);
     else if (nbw == 64 && p.qt == 64) wt_launch<T, C, 64, 64>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);

@@ -893,11 +893,11 @@ template <typename T, typename C> void launch_panel_recon(const ReconPanel<T, C>
     a.src = nullptr;
     subpanel<T, C, 64>(a, 0, 0, s);
     C* right = a.P + 64 * a.ldv;
-    int ns = launch_block_wt<C, C>(64, false, right, a.ldv, a.len, 64, a.qmax, a.V, a.ldv, a.Wp, a.stop, s);
+    int ns = launch_block_wt<C, C>(64, false, right, a.ldv, a.len, 64, a.wp_cols, a.V, a.ldv, a.Wp, a.stop, s);
     launch_block_tw<C>(64, a.Wp, ns, 64, a.Tf, a.nb, a.W2, s);
     launch_block_sub<C, C>(false, right, a.ldv, a.len, 64, 64, a.Vt, a.nb, a.W2, 64, a.stop, s);
     subpanel<T, C, 64>(a, 64, 64, s);
-    ns = launch_block_wt<C, C>(64, false, a.V + 64 * a.ldv, a.ldv, a.len, 64, a.qmax, a.V, a.ldv, a.Wp, a.stop, s);
+    ns = launch_block_wt<C, C>(64, false, a.V + 64 * a.ldv, a.ldv, a.len, 64, a.wp_cols, a.V, a.ldv, a.Wp, a.stop, s);
     static bool attr_set = false;
     const size_t bytes = 4 * 64 * 66 * sizeof(double);
     if (!attr_set) {

@@ -76,6 +76,17 @@ bool widens(svb_dtype dt, const Shape& sh)
     return (dt == SVB_F16 || dt == SVB_BF16) && sh.rows <= kWidenRows;
 }
 
+// What svb_svdvals takes to ge2gb_block: matrices too large for small_bidiag_kernel, in f32 or f64 or widened.  It leaves
+// the rest to ge2gb_pipeline: panels of one tile (square blocks, whose last pivots may well be small), and in f64
+// arithmetic, where a panel is read twice, the sweeps over at most 256 rows, a single domain of the tree (one panel kernel
+// and one update there: 50 us a half-sweep at nb = 32 against 57; with a second tree level 75 against 60).
+template <typename C> constexpr int64_t block_rows() { return sizeof(C) == 8 ? 256 : 0; }
+bool block_form(svb_dtype dt, const Shape& sh, int nb)
+{
+    const bool small = !(sh.rows > kSmallMax || sh.cols > kSmallMax);
+    return !small && sh.cols > nb && (dt == SVB_F64 ? sh.rows > block_rows<double>() : dt == SVB_F32 || widens(dt, sh));
+}
+
 int check_shape(svb_dtype dt, int64_t m, int64_t n, int nb)
 {
     if (m < 0 || n < 0) return SVB_ERR_ARG;
@@ -212,16 +223,19 @@ constexpr size_t kStopInt = 2;       // one of them: the half-sweep (from 1) at 
 // or is wider than tall (storage type).
 struct Carve {
     size_t panel_elems, t_elems, band_elems, de_elems, stage_elems, tree_ints;
-    // one block reflector per panel (ge2gb_block): work panel, V in both orders, T, W2, partial sums of W; in the
-    // place of the tree's V, Y and T, which are used before or after it, never beside it
-    int64_t blk_ld, blk_q;
+    // one block reflector per panel (ge2gb_block, room for it only with `block`): work panel, V in both orders, T, W2,
+    // partial sums of W; in the place of the tree's V, Y and T, which are used before or after it, never beside it
+    bool block, wide;       // wide: `stage` holds the f32 copy of a 16-bit matrix
+    int64_t blk_ld, wp_cols;
     size_t off_bP, off_bV, off_bVt, off_bT, off_bW2, off_bWp, off_bG;
     size_t off_V, off_Y, off_T, off_band, off_d, off_e, off_sig, off_s3, off_fac, off_gb, off_tree, off_stage, total;
 };
 
-Carve carve(svb_dtype dt, const Shape& sh, int nb)
+Carve carve(svb_dtype dt, const Shape& sh, int nb, bool block)
 {
     Carve c{};
+    c.block = block;
+    c.wide = block && widens(dt, sh);
     const size_t cs = compute_size(dt);
     const int64_t rows = sh.rows, cols = sh.cols;
     // levels shrink by >= kMinDomainChunks: sum of panel rows <= 2 rows (+ one chunk per level)
@@ -229,7 +243,7 @@ Carve carve(svb_dtype dt, const Shape& sh, int nb)
     c.t_elems = 2 * (size_t)(rows / nb + 1) * nb * nb;  // T per domain, plus room for the v^T v products
     c.band_elems = (size_t)(3 * nb) * (size_t)cols;
     c.de_elems = (size_t)cols;
-    c.stage_elems = sh.staged || widens(dt, sh) ? (size_t)rows * (size_t)cols : 0;
+    c.stage_elems = sh.staged || c.wide ? (size_t)rows * (size_t)cols : 0;
     // panel tree hand-over: error flag, one ticket counter per half-sweep, one flag per domain
     c.tree_ints = kTreeHead + 2 * (size_t)(cols / nb) + 2 + (size_t)(rows / nb) + kMaxLevels + 2;
     size_t off = 0;
@@ -237,16 +251,16 @@ Carve carve(svb_dtype dt, const Shape& sh, int nb)
     c.off_Y = off; off += align_up(c.panel_elems * cs);
     c.off_T = off; off += align_up(c.t_elems * cs);
     c.blk_ld = rows;
-    c.blk_q = rows;   // (rows >= cols)
+    c.wp_cols = block_wp_cols(rows, cols);
     size_t bo = c.off_V;
     c.off_bP = bo; bo += align_up((size_t)c.blk_ld * nb * cs);
     c.off_bV = bo; bo += align_up((size_t)c.blk_ld * nb * cs);
     c.off_bVt = bo; bo += align_up((size_t)c.blk_ld * nb * cs);
     c.off_bT = bo; bo += align_up((size_t)nb * nb * cs);
-    c.off_bW2 = bo; bo += align_up((size_t)c.blk_q * nb * cs);
-    c.off_bWp = bo; bo += align_up((size_t)block_wp_elems(c.blk_q, nb) * cs);
+    c.off_bW2 = bo; bo += align_up((size_t)rows * nb * cs);   // (rows >= cols)
+    c.off_bWp = bo; bo += align_up((size_t)c.wp_cols * nb * cs);
     c.off_bG = bo; bo += align_up(recon_scratch_doubles(rows, nb) * sizeof(double));
-    if (bo > off) off = bo;
+    if (block && bo > off) off = bo;
     c.off_band = off; off += align_up(c.band_elems * cs);
     c.off_d = off; off += align_up(c.de_elems * cs);
     c.off_e = off; off += align_up(c.de_elems * cs);
@@ -255,7 +269,7 @@ Carve carve(svb_dtype dt, const Shape& sh, int nb)
     c.off_fac = off; off += align_up(scale_workspace_bytes());
     c.off_gb = off; off += align_up(gb2bd_bytes(sh.k, nb));
     c.off_tree = off; off += align_up(c.tree_ints * sizeof(int));
-    c.off_stage = off; off += align_up(c.stage_elems * (widens(dt, sh) ? sizeof(float) : storage_size(dt)));
+    c.off_stage = off; off += align_up(c.stage_elems * (c.wide ? sizeof(float) : storage_size(dt)));
     c.total = off;
     return c;
 }
@@ -622,12 +636,6 @@ int ge2gb_pipeline(int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* ban
     return hipGetLastError() == hipSuccess ? SVB_OK : SVB_ERR_DEVICE;
 }
 
-// ge2gb_block leaves the rest to ge2gb_pipeline: panels of one tile (square blocks, whose last pivots may well be
-// small), and in f64 arithmetic, where a panel is read twice, the sweeps over at most 256 rows, a single domain of the
-// tree (one panel kernel and one update there: 50 us a half-sweep at nb = 32 against 57; with a second tree level 75
-// against 60).
-template <typename C> constexpr int64_t block_rows() { return sizeof(C) == 8 ? 256 : 0; }
-
 // Stage 1 with one block reflector per panel (stage1_recon.hip, stage1_block.hip), as far as it goes: up to the
 // panels of a single tile, or to a panel that Cholesky QR does not serve.  All on the caller's stream; returns the
 // half-sweep ge2gb_pipeline has to go on with, after waiting for the stream, or a negative status.
@@ -649,7 +657,7 @@ int ge2gb_block(int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* band, 
     rp.Tf = reinterpret_cast<C*>(work + cv.off_bT);
     rp.W2 = reinterpret_cast<C*>(work + cv.off_bW2);
     rp.Wp = reinterpret_cast<C*>(work + cv.off_bWp);
-    rp.ldv = cv.blk_ld; rp.qmax = cv.blk_q;
+    rp.ldv = cv.blk_ld; rp.wp_cols = cv.wp_cols;
     rp.Gp = reinterpret_cast<double*>(work + cv.off_bG);
     const int nbp = nb < 64 ? nb : 64;
     rp.X = rp.Gp + (recon_scratch_doubles(rows, nb) - 2 * (size_t)nbp * nbp);
@@ -677,7 +685,7 @@ int ge2gb_block(int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* band, 
         prof_end(s);
         T* Cb = A + (lq ? (k + 1) * nb : k * nb) + (k + 1) * nb * lda;
         prof_begin(SVB_PROF_UPDATE, s, 4.0 * (double)len * nb * (double)qlen, 3.0 * (double)len * (double)qlen * sizeof(T));
-        const int ns = launch_block_wt<T, C>(nb, lq, Cb, lda, len, qlen, rp.qmax, rp.V, rp.ldv, rp.Wp, stop, s);
+        const int ns = launch_block_wt<T, C>(nb, lq, Cb, lda, len, qlen, rp.wp_cols, rp.V, rp.ldv, rp.Wp, stop, s);
         launch_block_tw<C>(nb, rp.Wp, ns, qlen, rp.Tf, nb, rp.W2, s);
         launch_block_sub<T, C>(lq, Cb, lda, len, qlen, nb, rp.Vt, nb, rp.W2, nb, stop, s);
         prof_end(s);
@@ -688,15 +696,14 @@ int ge2gb_block(int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* band, 
 
 template <typename T, typename C>
 int ge2gb_typed(svb_dtype dt, int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* band, int64_t ldab,
-                unsigned char* work, const Carve& cv, const Switches& sw, hipStream_t s, bool may_wait)
+                unsigned char* work, const Carve& cv, const Switches& sw, hipStream_t s)
 {
     if (!g_la.init(sw)) return SVB_ERR_DEVICE;
     const int g = domain_chunks(dt, nb, sw);
     int hs0 = 0;
     if constexpr (std::is_same_v<T, C>) {   // (16-bit storage comes widened, or goes to the tree)
         // (stage1_block.hip addresses 128 lines of the matrix with 32-bit byte offsets)
-        if (may_wait && sw.block_reflector() && lda * (int64_t)sizeof(T) < ((int64_t)1 << 32) / 128 && cols > nb &&
-            rows > block_rows<C>()) {
+        if (cv.block && lda * (int64_t)sizeof(T) < ((int64_t)1 << 32) / 128) {
             hs0 = ge2gb_block<T, C>(rows, cols, A, lda, nb, band, ldab, work, cv, s);
             if (hs0 < 0) return SVB_ERR_DEVICE;
         }
@@ -705,14 +712,14 @@ int ge2gb_typed(svb_dtype dt, int64_t rows, int64_t cols, T* A, int64_t lda, int
 }
 
 int ge2gb_dispatch(svb_dtype dt, int64_t rows, int64_t cols, void* A, int64_t lda, int nb, void* band, int64_t ldab,
-                   void* work, const Carve& cv, const Switches& sw, hipStream_t s, bool may_wait)
+                   void* work, const Carve& cv, const Switches& sw, hipStream_t s)
 {
     unsigned char* w = static_cast<unsigned char*>(work);
     switch (dt) {
-    case SVB_F64: return ge2gb_typed<double, double>(dt, rows, cols, (double*)A, lda, nb, (double*)band, ldab, w, cv, sw, s, may_wait);
-    case SVB_F32: return ge2gb_typed<float, float>(dt, rows, cols, (float*)A, lda, nb, (float*)band, ldab, w, cv, sw, s, may_wait);
-    case SVB_F16: return ge2gb_typed<__half, float>(dt, rows, cols, (__half*)A, lda, nb, (float*)band, ldab, w, cv, sw, s, may_wait);
-    case SVB_BF16: return ge2gb_typed<bf16_t, float>(dt, rows, cols, (bf16_t*)A, lda, nb, (float*)band, ldab, w, cv, sw, s, may_wait);
+    case SVB_F64: return ge2gb_typed<double, double>(dt, rows, cols, (double*)A, lda, nb, (double*)band, ldab, w, cv, sw, s);
+    case SVB_F32: return ge2gb_typed<float, float>(dt, rows, cols, (float*)A, lda, nb, (float*)band, ldab, w, cv, sw, s);
+    case SVB_F16: return ge2gb_typed<__half, float>(dt, rows, cols, (__half*)A, lda, nb, (float*)band, ldab, w, cv, sw, s);
+    case SVB_BF16: return ge2gb_typed<bf16_t, float>(dt, rows, cols, (bf16_t*)A, lda, nb, (float*)band, ldab, w, cv, sw, s);
     default: return SVB_ERR_UNSUPPORTED;
     }
 }
@@ -816,7 +823,10 @@ int svb_workspace_bytes(svb_dtype dt, int64_t m, int64_t n, int nb, size_t* dev_
     const int rc = check_shape(dt, m, n, nb);
     if (rc != SVB_OK) return rc;
     size_t total = 256;
-    if (m > 0 && n > 0) total = carve(dt, shape_of(m, n, nb), nb).total;
+    if (m > 0 && n > 0) {
+        const Shape sh = shape_of(m, n, nb);
+        total = carve(dt, sh, nb, block_form(dt, sh, nb)).total;
+    }
     if (dev_bytes) *dev_bytes = total;
     if (host_bytes) *host_bytes = 0;
     return SVB_OK;
@@ -832,9 +842,9 @@ int svb_ge2gb(svb_dtype dt, int64_t m, int64_t n, void* A_dev, int64_t lda, int 
     if (!A_dev || !band_dev || !work_dev || lda < m || ldab < 3 * (int64_t)nb) return SVB_ERR_ARG;
     if (!aligned_for_vectors(A_dev, lda, dt) || reinterpret_cast<uintptr_t>(work_dev) % 256 != 0) return SVB_ERR_UNSUPPORTED;
     const Shape sh = shape_of(m, n, nb);
-    const Carve cv = carve(dt, sh, nb);
+    const Carve cv = carve(dt, sh, nb, false);   // (returns without waiting: the tree)
     if (work_bytes < cv.total) return SVB_ERR_WORKSPACE;
-    return ge2gb_dispatch(dt, m, n, A_dev, lda, nb, band_dev, ldab, work_dev, cv, switches(), (hipStream_t)stream, false);
+    return ge2gb_dispatch(dt, m, n, A_dev, lda, nb, band_dev, ldab, work_dev, cv, switches(), (hipStream_t)stream);
 }
 
 static int gb2bd_checked(svb_dtype band_dt, int64_t n, int nb, void* band_dev, int64_t ldab, void* d_dev,
@@ -922,9 +932,11 @@ int svb_svdvals(svb_dtype dt, int64_t m, int64_t n, void* A_dev, int64_t lda, vo
     const Shape sh = shape_of(m, n, nb);
     // in place only where the kernels' 16-byte accesses are aligned
     if (!sh.staged && !aligned_for_vectors(A_dev, lda, dt)) return SVB_ERR_UNSUPPORTED;
-    const Carve cv = carve(dt, sh, nb);
-    if (work_bytes < cv.total) return SVB_ERR_WORKSPACE;
     const Switches& sw = switches();
+    Carve cv = carve(dt, sh, nb, sw.block_reflector() && block_form(dt, sh, nb));
+    // (a workspace that has no room for the block reflectors is enough for the tree)
+    if (cv.block && work_bytes < cv.total) cv = carve(dt, sh, nb, false);
+    if (work_bytes < cv.total) return SVB_ERR_WORKSPACE;
     if (!g_la.init(sw)) return SVB_ERR_DEVICE;
     hipStream_t s = (hipStream_t)stream;
     unsigned char* w = static_cast<unsigned char*>(work_dev);
@@ -946,7 +958,7 @@ int svb_svdvals(svb_dtype dt, int64_t m, int64_t n, void* A_dev, int64_t lda, vo
     // the matrix stage 1 works on: the caller's, or its zero-padded (transposed, widened) copy
     void* A1 = A_dev;
     int64_t ld1 = lda;
-    const bool wide = !small && widens(dt, sh) && sw.block_reflector();
+    const bool wide = cv.wide;
     const svb_dtype dt1 = wide ? SVB_F32 : dt;
     if (!small && (sh.staged || wide)) {
         A1 = w + cv.off_stage;
@@ -954,7 +966,7 @@ int svb_svdvals(svb_dtype dt, int64_t m, int64_t n, void* A_dev, int64_t lda, vo
         stage_copy_dispatch(dt, wide, A_dev, lda, m, n, sh, A1, s);
     }
     if (scaled && !small) scale_dispatch(dt1, A1, ld1, sh.rows, sh.cols, factors, s);
-    if (!small) rc = ge2gb_dispatch(dt1, sh.rows, sh.cols, A1, ld1, nb, band, ldab, work_dev, cv, sw, s, true);
+    if (!small) rc = ge2gb_dispatch(dt1, sh.rows, sh.cols, A1, ld1, nb, band, ldab, work_dev, cv, sw, s);
     (void)hipEventRecord(ev[1], s);
     if (rc == SVB_OK && !small) {
         // columns min(m, n) .. of the padded band are zero: stage 2 runs on the leading part

@@ -177,7 +177,7 @@ template <typename T, typename C> struct ReconPanel {
     const T* src;                          // &A[arow + acol * lda]
     int lq, nb; int64_t len;               // orientation, tile size, panel length
     C *P, *V, *Vt, *Tf, *Wp, *W2;     // work panel, V in both orders, T, scratch of the updates
-    int64_t ldv, qmax;                     // leading dimension of P and V (at least len); what Wp is sized for
+    int64_t ldv, wp_cols;                  // leading dimension of P and V (at least len); columns Wp has room for
     double *Gp, *X;                        // recon_scratch_doubles(): partial Gram sums; X and the first R
     C* band; int64_t ldab, row0, col0;
     int* stop; int hs;                     // set to hs + 1 where a panel is refused
@@ -187,14 +187,14 @@ template <typename T, typename C> void launch_panel_recon(const ReconPanel<T, C>
 size_t recon_scratch_doubles(int64_t rows, int nb);
 // the products of a half-sweep (stage1_block.hip); launch_block_wt returns the number of partial sums
 template <typename T, typename C>
-int launch_block_wt(int nbw, bool lq, const T* Cm, int64_t lda, int64_t len, int64_t nq, int64_t qmax, const C* V,
+int launch_block_wt(int nbw, bool lq, const T* Cm, int64_t lda, int64_t len, int64_t nq, int64_t wp_cols, const C* V,
                     int64_t ldv, C* Wp, const int* stop, hipStream_t s);
 template <typename C>
 void launch_block_tw(int nbw, const C* Wp, int ns, int64_t nq, const C* T, int64_t ldt, C* W2, hipStream_t s);
 template <typename T, typename C>
 void launch_block_sub(bool lq, T* Cm, int64_t lda, int64_t len, int64_t nq, int K, const C* Vt, int64_t ldvt,
                       const C* W2, int64_t ldw, const int* stop, hipStream_t s);
-int64_t block_wp_elems(int64_t qmax, int nb);   // elements of Wp
+int64_t block_wp_cols(int64_t rows, int64_t cols);   // columns of nb elements that Wp needs at most for a rows x cols matrix
 
 // per-kernel timing hooks (no-ops unless profiling is enabled)
 void prof_begin(int kind, hipStream_t s, double flops, double bytes);

@@ -75,6 +75,14 @@ def test_workspace_is_a_fraction_of_the_matrix():
     assert dev <= 1 << 30
 
 
+def test_workspace_of_small_problems():
+    # nothing for a form of stage 1 that the problem does not reach, and no floor on what it needs of it
+    assert svb.svb_workspace_bytes(svb.SVB_F64, 64, 64, 32)[1] <= 1 << 19
+    assert svb.svb_workspace_bytes(svb.SVB_F64, 256, 256, 64)[1] <= 5 << 19
+    assert svb.svb_workspace_bytes(svb.SVB_F32, 640, 320, 64)[1] <= 2 << 20
+    assert svb.svb_workspace_bytes(svb.SVB_F16, 16384, 16384, 64)[1] <= 40 << 20      # (too large for the f32 copy)
+
+
 def test_tile_size_choice():
     assert svb.svb_choose_nb(svb.SVB_F32, 256, 256) == 32
     assert svb.svb_choose_nb(svb.SVB_F32, 8192, 8192) == 64
