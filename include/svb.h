@@ -114,9 +114,10 @@ int svb_choose_nb(svb_dtype dt, int64_t m, int64_t n);
  *   the last two, and the first if m is not a multiple of nb, work on a copy
  *   of A inside the workspace.
  *   A_dev      [dev]  in/out: the matrix in storage type dt.  If m >= n and
- *                     both are multiples of nb it is DESTROYED (used as the
+ *                     both are multiples of nb it MAY BE OVERWRITTEN (it is the
  *                     in-place work area of stage 1, like the paper's
- *                     banddiag!, Algorithm 2) and must be 16-byte aligned with
+ *                     banddiag!, Algorithm 2, unless the matrix is at most
+ *                     256 x 256 or copied in f32) and must be 16-byte aligned with
  *                     lda a multiple of 4 elements (2 for SVB_F64), else
  *                     SVB_ERR_UNSUPPORTED; otherwise it is only read and has
  *                     no alignment requirement.

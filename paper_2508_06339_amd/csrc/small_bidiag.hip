@@ -99,7 +99,7 @@ template <typename C, int RJ, int CJ> struct SmallGeom {
 
 // One run.  True, and nothing written, where a line would have to be moved up (never with CAREFUL, which moves them).
 template <bool CAREFUL, typename T, typename C, int RJ, int CJ>
-__device__ __forceinline__ bool small_run(T* A, int64_t lda, int m, int n, int transpose, int in_place, C* __restrict__ d,
+__device__ __forceinline__ bool small_run(const T* A, int64_t lda, int m, int n, int transpose, C* __restrict__ d,
                                           C* __restrict__ e, C* sm, double* sh_big)
 {
     using Gm = SmallGeom<C, RJ, CJ>;
@@ -371,31 +371,29 @@ __device__ __forceinline__ bool small_run(T* A, int64_t lda, int m, int n, int t
     for (int i = tid; i < n; i += 512) {
         d[i] = ldexp_of(dl[i], ex);
         e[i] = i < n - 1 ? ldexp_of(el[i], ex) : (C)0;
-        // (a matrix that the method would work on in place counts as used up at this size too)
-        if (in_place) st_as<T, C>(&A[i + i * lda], dl[i]);
     }
     return false;
 }
 
 template <typename T, typename C, int RJ, int CJ>
-__global__ __launch_bounds__(512) void small_bidiag_kernel(T* A, int64_t lda, int m, int n, int transpose, int in_place,
+__global__ __launch_bounds__(512) void small_bidiag_kernel(const T* A, int64_t lda, int m, int n, int transpose,
                                                            C* __restrict__ d, C* __restrict__ e)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ double sh_big[8];
     C* sm = reinterpret_cast<C*>(smem_raw);
-    if (small_run<false, T, C, RJ, CJ>(A, lda, m, n, transpose, in_place, d, e, sm, sh_big)) {
+    if (small_run<false, T, C, RJ, CJ>(A, lda, m, n, transpose, d, e, sm, sh_big)) {
         __syncthreads();
-        small_run<true, T, C, RJ, CJ>(A, lda, m, n, transpose, in_place, d, e, sm, sh_big);
+        small_run<true, T, C, RJ, CJ>(A, lda, m, n, transpose, d, e, sm, sh_big);
     }
 }
 
 template <typename T, typename C, int RJ, int CJ>
-void small_launch(T* A, int64_t lda, int m, int n, bool transpose, bool in_place, C* d, C* e, hipStream_t s)
+void small_launch(const T* A, int64_t lda, int m, int n, bool transpose, C* d, C* e, hipStream_t s)
 {
     if constexpr (CJ > 1) {
         if (n <= 64 * (CJ - 1)) {
-            small_launch<T, C, RJ, CJ - 1>(A, lda, m, n, transpose, in_place, d, e, s);
+            small_launch<T, C, RJ, CJ - 1>(A, lda, m, n, transpose, d, e, s);
             return;
         }
     }
@@ -407,28 +405,27 @@ void small_launch(T* A, int64_t lda, int m, int n, bool transpose, bool in_place
                                   (int)Gm::kBytes);
         attr_set = true;
     }
-    hipLaunchKernelGGL(kern, dim3(1), dim3(512), Gm::kBytes, s, A, lda, m, n, transpose ? 1 : 0, in_place ? 1 : 0, d, e);
+    hipLaunchKernelGGL(kern, dim3(1), dim3(512), Gm::kBytes, s, A, lda, m, n, transpose ? 1 : 0, d, e);
 }
 
 }  // namespace
 
-// d, e (min(m, n) entries each) of the m x n matrix, both dimensions at most kSmallMax; A is only read, but for in_place,
-// where its diagonal is overwritten
+// d, e (min(m, n) entries each) of the m x n matrix, both dimensions at most kSmallMax
 template <typename T, typename C>
-void launch_small_bidiag(T* A, int64_t lda, int64_t m, int64_t n, bool in_place, C* d, C* e, hipStream_t s)
+void launch_small_bidiag(const T* A, int64_t lda, int64_t m, int64_t n, C* d, C* e, hipStream_t s)
 {
     const bool tr = m < n;
     const int r = (int)(tr ? n : m), c = (int)(tr ? m : n);
     switch ((r + 63) / 64) {
-    case 1: small_launch<T, C, 1, 1>(A, lda, r, c, tr, in_place, d, e, s); break;
-    case 2: small_launch<T, C, 2, 2>(A, lda, r, c, tr, in_place, d, e, s); break;
-    case 3: small_launch<T, C, 3, 3>(A, lda, r, c, tr, in_place, d, e, s); break;
-    default: small_launch<T, C, 4, 4>(A, lda, r, c, tr, in_place, d, e, s); break;
+    case 1: small_launch<T, C, 1, 1>(A, lda, r, c, tr, d, e, s); break;
+    case 2: small_launch<T, C, 2, 2>(A, lda, r, c, tr, d, e, s); break;
+    case 3: small_launch<T, C, 3, 3>(A, lda, r, c, tr, d, e, s); break;
+    default: small_launch<T, C, 4, 4>(A, lda, r, c, tr, d, e, s); break;
     }
 }
-template void launch_small_bidiag<float, float>(float*, int64_t, int64_t, int64_t, bool, float*, float*, hipStream_t);
-template void launch_small_bidiag<double, double>(double*, int64_t, int64_t, int64_t, bool, double*, double*, hipStream_t);
-template void launch_small_bidiag<__half, float>(__half*, int64_t, int64_t, int64_t, bool, float*, float*, hipStream_t);
-template void launch_small_bidiag<bf16_t, float>(bf16_t*, int64_t, int64_t, int64_t, bool, float*, float*, hipStream_t);
+template void launch_small_bidiag<float, float>(const float*, int64_t, int64_t, int64_t, float*, float*, hipStream_t);
+template void launch_small_bidiag<double, double>(const double*, int64_t, int64_t, int64_t, double*, double*, hipStream_t);
+template void launch_small_bidiag<__half, float>(const __half*, int64_t, int64_t, int64_t, float*, float*, hipStream_t);
+template void launch_small_bidiag<bf16_t, float>(const bf16_t*, int64_t, int64_t, int64_t, float*, float*, hipStream_t);
 
 }  // namespace svb

@@ -724,13 +724,13 @@ int ge2gb_dispatch(svb_dtype dt, int64_t rows, int64_t cols, void* A, int64_t ld
     }
 }
 
-void small_bidiag_dispatch(svb_dtype dt, void* A, int64_t lda, int64_t m, int64_t n, bool in_place, void* d, void* e, hipStream_t s)
+void small_bidiag_dispatch(svb_dtype dt, const void* A, int64_t lda, int64_t m, int64_t n, void* d, void* e, hipStream_t s)
 {
     switch (dt) {
-    case SVB_F64: launch_small_bidiag<double, double>((double*)A, lda, m, n, in_place, (double*)d, (double*)e, s); break;
-    case SVB_F32: launch_small_bidiag<float, float>((float*)A, lda, m, n, in_place, (float*)d, (float*)e, s); break;
-    case SVB_F16: launch_small_bidiag<__half, float>((__half*)A, lda, m, n, in_place, (float*)d, (float*)e, s); break;
-    default: launch_small_bidiag<bf16_t, float>((bf16_t*)A, lda, m, n, in_place, (float*)d, (float*)e, s); break;
+    case SVB_F64: launch_small_bidiag<double, double>((const double*)A, lda, m, n, (double*)d, (double*)e, s); break;
+    case SVB_F32: launch_small_bidiag<float, float>((const float*)A, lda, m, n, (float*)d, (float*)e, s); break;
+    case SVB_F16: launch_small_bidiag<__half, float>((const __half*)A, lda, m, n, (float*)d, (float*)e, s); break;
+    default: launch_small_bidiag<bf16_t, float>((const bf16_t*)A, lda, m, n, (float*)d, (float*)e, s); break;
     }
 }
 
@@ -954,7 +954,7 @@ int svb_svdvals(svb_dtype dt, int64_t m, int64_t n, void* A_dev, int64_t lda, vo
     // Both dimensions up to 256: straight to the bidiagonal in one workgroup, and no stages 1 and 2 (ms a call, without and
     // with: f32 64 0.39, 0.16; 256 1.40, 0.67; f64 64 0.46, 0.20; 192 1.24, 0.62; 256 1.67, 1.18; 256 x 64 0.46, 0.24).
     const bool small = m <= kSmallMax && n <= kSmallMax && scaled && sw.block_reflector() && sw.plain_chase();
-    if (small) small_bidiag_dispatch(dt, A_dev, lda, m, n, !sh.staged, dd, de, s);
+    if (small) small_bidiag_dispatch(dt, A_dev, lda, m, n, dd, de, s);
     // the matrix stage 1 works on: the caller's, or its zero-padded (transposed, widened) copy
     void* A1 = A_dev;
     int64_t ld1 = lda;

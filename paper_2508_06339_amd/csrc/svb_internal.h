@@ -168,7 +168,7 @@ void launch_update_fused16(int nb, bool lq, T* Cbase, int64_t lda, int64_t qlen,
 // ---- small matrices: straight to bidiagonal form in one workgroup (small_bidiag.hip) -----------------------
 constexpr int64_t kSmallMax = 256;
 template <typename T, typename C>
-void launch_small_bidiag(T* A, int64_t lda, int64_t m, int64_t n, bool in_place, C* d, C* e, hipStream_t s);
+void launch_small_bidiag(const T* A, int64_t lda, int64_t m, int64_t n, C* d, C* e, hipStream_t s);
 
 // ---- stage 1 with one block reflector per panel -------------------------------------------------------
 // Cholesky QR and Householder reconstruction of one panel (stage1_recon.hip)
