@@ -46,6 +46,10 @@ template <> struct Mm<double> {
 // rows read 16 bytes each without a bank conflict)
 template <typename C> constexpr int kKC = 128 / (int)sizeof(C);
 template <typename C> constexpr int kLD = 144 / (int)sizeof(C);
+// lengths, ranges and tile sizes are multiples of this many lines (wt_plan; svb_svdvals pads to whole tiles), and whole
+// chunks are read
+constexpr int kUnit = 32;
+static_assert(kUnit % kKC<float> == 0 && kUnit % kKC<double> == 0, "a chunk does not reach past the end of a range");
 
 // Global memory goes through buffer instructions: a wave-uniform base, one 32-bit byte offset a lane, wave-uniform
 // byte offsets (the host keeps 128 lines of the matrix below 2^32 bytes).
@@ -54,8 +58,8 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void* base)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0xffffffff, 0x00020000);
 }
-template <typename C, typename T> struct Buf1;
-template <> struct Buf1<float, float> {
+template <typename C> struct Buf1;
+template <> struct Buf1<float> {
     static __device__ __forceinline__ float ld(rsrc_t r, unsigned v, unsigned s)
     {
         return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, v, s, 0));
@@ -65,7 +69,7 @@ template <> struct Buf1<float, float> {
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), r, v, s, 0);
     }
 };
-template <> struct Buf1<double, double> {
+template <> struct Buf1<double> {
     typedef unsigned u2 __attribute__((ext_vector_type(2)));
     static __device__ __forceinline__ double ld(rsrc_t r, unsigned v, unsigned s)
     {
@@ -76,23 +80,6 @@ template <> struct Buf1<double, double> {
         __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, x), r, v, s, 0);
     }
 };
-template <typename T> struct Buf1<float, T> {   // 16-bit storage
-    static __device__ __forceinline__ float ld(rsrc_t r, unsigned v, unsigned s)
-    {
-        const unsigned short u = __builtin_amdgcn_raw_buffer_load_b16(r, v, s, 0);
-        T t;
-        __builtin_memcpy(&t, &u, 2);
-        return ld_as<float, T>(&t);
-    }
-    static __device__ __forceinline__ void st(rsrc_t r, unsigned v, unsigned s, float x)
-    {
-        T t;
-        st_as<T, float>(&t, x);
-        unsigned short u;
-        __builtin_memcpy(&u, &t, 2);
-        __builtin_amdgcn_raw_buffer_store_b16(u, r, v, s, 0);
-    }
-};
 
 // ---- C += A B^T on tiles of BR x BJ -------------------------------------------------------------------
 // C(r, j) at r * lda + j (j contiguous), A(r, k) at r * lda_r + k, B(j, k) at j * ldb_j + k; K a multiple of
@@ -101,8 +88,8 @@ template <typename T> struct Buf1<float, T> {   // 16-bit storage
 // Four waves in a square.  A lane's column of an accumulator tile is j, so C moves along its contiguous
 // direction.  Tiles are numbered so that an XCD works on a contiguous range of them, eight columns of tiles
 // at a time (their operands stay in its L2).
-template <typename T, typename C, int BR, int BJ>
-__global__ __launch_bounds__(256, sizeof(C) == 4 ? 3 : 2) void block_sub_kernel(T* __restrict__ Cm, int64_t lda, int nr, int nj,
+template <typename C, int BR, int BJ>
+__global__ __launch_bounds__(256, sizeof(C) == 4 ? 3 : 2) void block_sub_kernel(C* __restrict__ Cm, int64_t lda, int nr, int nj,
                                                            const C* __restrict__ Ar, int64_t lda_r,
                                                            const C* __restrict__ Bj, int64_t ldb_j, int K,
                                                            const int* __restrict__ stop)
@@ -143,8 +130,8 @@ __global__ __launch_bounds__(256, sizeof(C) == 4 ? 3 : 2) void block_sub_kernel(
     fetch(0);
 
     const int rw = r0 + (wave >> 1) * WR, jw = j0 + (wave & 1) * WJ;
-    const unsigned line = (unsigned)(lda * sizeof(T));
-    const unsigned voff = (unsigned)M::row(0, g) * line + (unsigned)(i * sizeof(T));
+    const unsigned line = (unsigned)(lda * sizeof(C));
+    const unsigned voff = (unsigned)M::row(0, g) * line + (unsigned)(i * sizeof(C));
     const bool edge = rw + WR > nr || jw + WJ > nj;
     acc_t acc[NR][NJ];
     auto tile_on = [&](int a, int b) { return !edge || (rw + a * TM < nr && jw + b * TM < nj); };
@@ -155,7 +142,7 @@ __global__ __launch_bounds__(256, sizeof(C) == 4 ? 3 : 2) void block_sub_kernel(
             if (tile_on(a, b)) {
                 const rsrc_t rs = make_rsrc(Cm + (int64_t)(rw + a * TM) * lda + jw + b * TM);
 #pragma unroll
-                for (int r = 0; r < M::NR; ++r) acc[a][b][r] = Buf1<C, T>::ld(rs, voff, (unsigned)M::row(r, 0) * line);
+                for (int r = 0; r < M::NR; ++r) acc[a][b][r] = Buf1<C>::ld(rs, voff, (unsigned)M::row(r, 0) * line);
             } else {
 #pragma unroll
                 for (int r = 0; r < M::NR; ++r) acc[a][b][r] = 0;
@@ -197,7 +184,7 @@ __global__ __launch_bounds__(256, sizeof(C) == 4 ? 3 : 2) void block_sub_kernel(
             if (tile_on(a, b)) {
                 const rsrc_t rs = make_rsrc(Cm + (int64_t)(rw + a * TM) * lda + jw + b * TM);
 #pragma unroll
-                for (int r = 0; r < M::NR; ++r) Buf1<C, T>::st(rs, voff, (unsigned)M::row(r, 0) * line, acc[a][b][r]);
+                for (int r = 0; r < M::NR; ++r) Buf1<C>::st(rs, voff, (unsigned)M::row(r, 0) * line, acc[a][b][r]);
             }
         }
 }
@@ -207,8 +194,8 @@ __global__ __launch_bounds__(256, sizeof(C) == 4 ? 3 : 2) void block_sub_kernel(
 // V(p, c) at p + c * ldv.  len and chunk multiples of 32, nq a multiple of 32.
 // QR orientation: C's tile is staged as it lies, p fastest; LQ: q fastest, its operand read element by element.
 // *stop as in block_sub_kernel.
-template <typename T, typename C, int NBW, int QT, bool LQ>
-__global__ __launch_bounds__(256, 2) void block_wt_kernel(const T* __restrict__ Cm, int64_t lda, int len, int nq,
+template <typename C, int NBW, int QT, bool LQ>
+__global__ __launch_bounds__(256, 2) void block_wt_kernel(const C* __restrict__ Cm, int64_t lda, int len, int nq,
                                                        const C* __restrict__ V, int64_t ldv, int chunk,
                                                        C* __restrict__ Wp, const int* __restrict__ stop)
 {
@@ -242,10 +229,10 @@ __global__ __launch_bounds__(256, 2) void block_wt_kernel(const T* __restrict__ 
             const int idx = tid + e * 256;
             if constexpr (LQ) {
                 const int p = idx / (QT / VK), qq = idx % (QT / VK) * VK;
-                VecIO<C, T>::ld(&Cm[(int64_t)(p0 + p) * lda + min(q0 + qq, nq - VK)], rc[e]);
+                VecIO<C, C>::ld(&Cm[(int64_t)(p0 + p) * lda + min(q0 + qq, nq - VK)], rc[e]);
             } else {
                 const int row = idx >> 3, kk = (idx & 7) * VK;
-                VecIO<C, T>::ld(&Cm[(int64_t)min(q0 + row, nq - 1) * lda + p0 + kk], rc[e]);
+                VecIO<C, C>::ld(&Cm[(int64_t)min(q0 + row, nq - 1) * lda + p0 + kk], rc[e]);
             }
         }
     };
@@ -386,13 +373,13 @@ __global__ __launch_bounds__(256) void block_tw_kernel(const C* __restrict__ Wp,
     }
 }
 
-template <typename T, typename C, int NBW, int QT>
-void wt_launch(bool lq, const T* Cm, int64_t lda, int len, int nq, const C* V, int64_t ldv, int chunk, int ns, C* Wp,
+template <typename C, int NBW, int QT>
+void wt_launch(bool lq, const C* Cm, int64_t lda, int len, int nq, const C* V, int64_t ldv, int chunk, int ns, C* Wp,
                const int* stop, hipStream_t s)
 {
     const dim3 grid((unsigned)((nq + QT - 1) / QT), (unsigned)ns);
-    if (lq) hipLaunchKernelGGL((block_wt_kernel<T, C, NBW, QT, true>), grid, dim3(256), 0, s, Cm, lda, len, nq, V, ldv, chunk, Wp, stop);
-    else hipLaunchKernelGGL((block_wt_kernel<T, C, NBW, QT, false>), grid, dim3(256), 0, s, Cm, lda, len, nq, V, ldv, chunk, Wp, stop);
+    if (lq) hipLaunchKernelGGL((block_wt_kernel<C, NBW, QT, true>), grid, dim3(256), 0, s, Cm, lda, len, nq, V, ldv, chunk, Wp, stop);
+    else hipLaunchKernelGGL((block_wt_kernel<C, NBW, QT, false>), grid, dim3(256), 0, s, Cm, lda, len, nq, V, ldv, chunk, Wp, stop);
 }
 
 }  // namespace
@@ -421,23 +408,23 @@ static WtPlan wt_plan(int nbw, int64_t len, int64_t nq, int64_t wp_cols)
     if (ns > room) ns = room;
     if (ns > max_ranges(len)) ns = max_ranges(len);
     if (ns < 1) ns = 1;
-    int64_t chunk = ((len + ns - 1) / ns + 31) / 32 * 32;
+    int64_t chunk = ((len + ns - 1) / ns + kUnit - 1) / kUnit * kUnit;
     p.chunk = (int)chunk;
     p.ns = (int)((len + chunk - 1) / chunk);
     return p;
 }
 
-template <typename T, typename C>
-int launch_block_wt(int nbw, bool lq, const T* Cm, int64_t lda, int64_t len, int64_t nq, int64_t wp_cols, const C* V,
+template <typename C>
+int launch_block_wt(int nbw, bool lq, const C* Cm, int64_t lda, int64_t len, int64_t nq, int64_t wp_cols, const C* V,
                     int64_t ldv, C* Wp, const int* stop, hipStream_t s)
 {
     const WtPlan p = wt_plan(nbw, len, nq, wp_cols);
     const int l = (int)len, q = (int)nq;
-    if (nbw == 32) wt_launch<T, C, 32, 128>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);
-    else if (nbw == 64 && p.qt == 64) wt_launch<T, C, 64, 64>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);
-    else if (nbw == 64) wt_launch<T, C, 64, 128>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);
-    else if (p.qt == 64) wt_launch<T, C, 128, 64>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);
-    else wt_launch<T, C, 128, 128>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);
+    if (nbw == 32) wt_launch<C, 32, 128>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);
+    else if (nbw == 64 && p.qt == 64) wt_launch<C, 64, 64>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);
+    else if (nbw == 64) wt_launch<C, 64, 128>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);
+    else if (p.qt == 64) wt_launch<C, 128, 64>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);
+    else wt_launch<C, 128, 128>(lq, Cm, lda, l, q, V, ldv, p.chunk, p.ns, Wp, stop, s);
     return p.ns;
 }
 
@@ -453,8 +440,8 @@ void launch_block_tw(int nbw, const C* Wp, int ns, int64_t nq, const C* T, int64
 }
 
 // (the operands' order follows the orientation: a lane's direction is the contiguous one of C)
-template <typename T, typename C>
-void launch_block_sub(bool lq, T* Cm, int64_t lda, int64_t len, int64_t nq, int K, const C* Vt, int64_t ldvt,
+template <typename C>
+void launch_block_sub(bool lq, C* Cm, int64_t lda, int64_t len, int64_t nq, int K, const C* Vt, int64_t ldvt,
                       const C* W2, int64_t ldw, const int* stop, hipStream_t s)
 {
     const int nr = (int)(lq ? len : nq), nj = (int)(lq ? nq : len);
@@ -466,17 +453,16 @@ void launch_block_sub(bool lq, T* Cm, int64_t lda, int64_t len, int64_t nq, int 
         hipLaunchKernelGGL(kern, dim3((unsigned)((nt + 7) / 8 * 8)), dim3(256), 0, s, Cm, lda, nr, nj, ar, la, bj_, lb, K, stop);
     };
     const int64_t big = (int64_t)((nr + 127) / 128) * ((nj + 127) / 128);
-    if (big >= 1024) go(block_sub_kernel<T, C, 128, 128>, 128, 128);
-    else go(block_sub_kernel<T, C, 64, 64>, 64, 64);
+    if (big >= 1024) go(block_sub_kernel<C, 128, 128>, 128, 128);
+    else go(block_sub_kernel<C, 64, 64>, 64, 64);
 }
 
-#define SVB_INST(T, C)                                                                                              \
-    template int launch_block_wt<T, C>(int, bool, const T*, int64_t, int64_t, int64_t, int64_t, const C*, int64_t, C*, const int*, hipStream_t); \
-    template void launch_block_sub<T, C>(bool, T*, int64_t, int64_t, int64_t, int, const C*, int64_t, const C*, int64_t, const int*, hipStream_t)
-SVB_INST(float, float);
-SVB_INST(double, double);
+#define SVB_INST(C)                                                                                                 \
+    template int launch_block_wt<C>(int, bool, const C*, int64_t, int64_t, int64_t, int64_t, const C*, int64_t, C*, const int*, hipStream_t); \
+    template void launch_block_tw<C>(int, const C*, int, int64_t, const C*, int64_t, C*, hipStream_t);              \
+    template void launch_block_sub<C>(bool, C*, int64_t, int64_t, int64_t, int, const C*, int64_t, const C*, int64_t, const int*, hipStream_t)
+SVB_INST(float);
+SVB_INST(double);
 #undef SVB_INST
-template void launch_block_tw<float>(int, const float*, int, int64_t, const float*, int64_t, float*, hipStream_t);
-template void launch_block_tw<double>(int, const double*, int, int64_t, const double*, int64_t, double*, hipStream_t);
 
 }  // namespace svb

@@ -45,8 +45,8 @@ __device__ __forceinline__ int ublk(int bi, int bj) { return bj * (bj + 1) / 2 +
 // ---- G = A^T A over 128 rows; the panel goes to P (leading dimension ldp) in the compute type on the way ---
 // Panel element (p, c): QR A[p + c lda], LQ A[c + p lda].  Gp: per workgroup the 16 x 16 blocks of the upper
 // block triangle, row-major.
-template <typename T, typename C, int NBP, bool LQ>
-__global__ __launch_bounds__(256) void panel_gram_kernel(const T* __restrict__ A, int64_t lda, int len, C* P, int64_t ldp,
+template <typename C, int NBP, bool LQ>
+__global__ __launch_bounds__(256) void panel_gram_kernel(const C* __restrict__ A, int64_t lda, int len, C* P, int64_t ldp,
                                                          double* __restrict__ Gp, const int* __restrict__ stop)
 {
     constexpr int RB = kGramRows, NBK = NBP / 16, NT = NBK * (NBK + 1) / 2;
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(256) void panel_gram_kernel(const T* __restrict__ A
             C v[VK];
 #pragma unroll
             for (int q = 0; q < VK; ++q) v[q] = 0;
-            if (p < np) VecIO<C, T>::ld(&A[(int64_t)(p0 + p) * lda + c], v);
+            if (p < np) VecIO<C, C>::ld(&A[(int64_t)(p0 + p) * lda + c], v);
 #pragma unroll
             for (int q = 0; q < VK; ++q) Ps[p * LDP + c + q] = v[q];
         }
@@ -80,7 +80,7 @@ __global__ __launch_bounds__(256) void panel_gram_kernel(const T* __restrict__ A
 #pragma unroll
             for (int q = 0; q < VK; ++q) v[q] = 0;
             if (p < np) {
-                VecIO<C, T>::ld(&A[p0 + p + (int64_t)c * lda], v);
+                VecIO<C, C>::ld(&A[p0 + p + (int64_t)c * lda], v);
                 if (P) VecIO<C, C>::st(&P[p0 + p + c * ldp], v);
             }
             VecIO<C, C>::st(&Ps[c * LDC + p], v);
@@ -353,14 +353,6 @@ template <int NBP> struct ReconGeom {
 // (28 us) at NBP = 64, of which each LU block 6900 and each Cholesky block 3600; 107k with one row at a time, Q formed,
 // the two factorisations one after the other and full barriers.
 enum { kFull, kFirst, kSecond };
-// Optional phase timing (compile with -DSVB_RECON_TIMING): thread 0 adds the shader-clock cycles of each phase
-#ifdef SVB_RECON_TIMING
-__device__ unsigned long long svb_recon_timing[32];
-#define RT_MARK(slot_) do { if (tid == 0) { const unsigned long long now_ = clock64(); \
-    atomicAdd(&svb_recon_timing[slot_], now_ - rt_last); rt_last = now_; } } while (0)
-#else
-#define RT_MARK(slot_) do { } while (0)
-#endif
 template <typename C> struct ReconArgs {
     const double* Gp; int np;        // partial sums of G
     const C* P; int64_t ldp;         // the panel (Q in the second pass), top rows
@@ -386,9 +378,6 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = lane & 15, g = lane >> 4;
     const int halted = *a.stop;
-#ifdef SVB_RECON_TIMING
-    unsigned long long rt_last = clock64();
-#endif
     int bi = 0, bj = 0;   // this wave's block of T, by falling length of its sums
     {
         int dist = NBK - 1, left = wave < NT ? wave : 0;
@@ -454,7 +443,6 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
         }
         for (int idx = tid; idx < NBP * LD; idx += NTH) L[idx] = 0.0;
     }
-    RT_MARK(0);
     if (wave == 0) {
         // columns of zeros: allowed at the end only; sums of squares outside the range or not finite: not
         const double d = lane < NBP ? g0[lane] : 1.0;
@@ -522,7 +510,6 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
         if (lu && wave == 1) lu16(blk(B, kb, kb), blk(G, kb, kb), LD, Lkk, Ukk, LDD, S + kb * 16, i, g);
         if (MODE == kSecond && kb == 0 && wave >= 2 && wave < NT + 2)   // R' R, a block a wave
             for (int k = ri; k <= rj; ++k) rr = mm16(rr, blk(G, ri, k), LD, 1, a.R1 + k * 16 * NBP + rj * 16, NBP, 1, i, g);
-        RT_MARK(1);
         lds_barrier();
         if (chol && wave >= 2 && wave < NBK + 1) {
             const int j0 = wave - 2, j = j0 + (j0 >= t ? 1 : 0);
@@ -608,7 +595,6 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
         if (tid == 0 && sh_bad) refuse();
         return;
     }
-    RT_MARK(2);
     lds_barrier();
     // ---- T = -(U R^-1) S L^-T, a block a wave
     static_assert(NT <= NWV, "a block a wave");
@@ -662,7 +648,6 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
         a.V[p - a.above + (int64_t)c * a.ldv] = 0;
         a.Vt[(int64_t)(p - a.above) * a.ldvt + c] = 0;
     }
-    RT_MARK(3);
     // ---- S R to the band
     if (sh_bad && tid == 0) refuse();
     if (sh_bad) return;
@@ -689,7 +674,6 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
         const int ri = idx % NBP, ci = idx / NBP;
         base[(ri - a.above) * sr + ci * sc] = a.P[ri - a.above + (int64_t)ci * a.ldp];
     }
-    RT_MARK(4);
 }
 
 // ---- Out(p, c) = sum_k A(p, k) X(k, c), X upper triangular, in 64 bits; to out (leading dimension ldo, may be A
@@ -823,12 +807,12 @@ template <typename C, int NBP, int MODE> void recon_launch(const ReconArgs<C>& a
     hipLaunchKernelGGL(kern, dim3(1), dim3(kReconThreads<NBP>), ReconGeom<NBP>::kBytes, s, a);
 }
 
-template <typename T, typename C, int NBP, bool LQ>
-int gram(const T* A, int64_t lda, int64_t len, C* P, int64_t ldp, double* Gp, double** sum, const int* stop, hipStream_t s)
+template <typename C, int NBP, bool LQ>
+int gram(const C* A, int64_t lda, int64_t len, C* P, int64_t ldp, double* Gp, double** sum, const int* stop, hipStream_t s)
 {
     constexpr int NT = NBP / 16 * (NBP / 16 + 1) / 2;
     const int n = (int)((len + kGramRows - 1) / kGramRows);
-    hipLaunchKernelGGL((panel_gram_kernel<T, C, NBP, LQ>), dim3(n), dim3(256), 0, s, A, lda, (int)len, P, ldp, Gp, stop);
+    hipLaunchKernelGGL((panel_gram_kernel<C, NBP, LQ>), dim3(n), dim3(256), 0, s, A, lda, (int)len, P, ldp, Gp, stop);
     *sum = Gp;
     if (n <= 16) return n;
     const int m = (n + 31) / 32;
@@ -839,16 +823,16 @@ int gram(const T* A, int64_t lda, int64_t len, C* P, int64_t ldp, double* Gp, do
 
 // Cholesky QR and reconstruction of one sub-panel of NBP columns that lies in the work panel (or, first_src, still
 // in the matrix)
-template <typename T, typename C, int NBP>
-void subpanel(const ReconPanel<T, C>& a, int64_t off, int64_t sub0, hipStream_t s)
+template <typename C, int NBP>
+void subpanel(const ReconPanel<C>& a, int64_t off, int64_t sub0, hipStream_t s)
 {
     const int64_t len = a.len - off;
     C* P = a.P + off + sub0 * a.ldv;
     double* Gs = nullptr;
     int np;
-    if (a.src && a.lq) np = gram<T, C, NBP, true>(a.src, a.lda, len, P, a.ldv, a.Gp, &Gs, a.stop, s);
-    else if (a.src) np = gram<T, C, NBP, false>(a.src, a.lda, len, P, a.ldv, a.Gp, &Gs, a.stop, s);
-    else np = gram<C, C, NBP, false>(P, a.ldv, len, (C*)nullptr, 0, a.Gp, &Gs, a.stop, s);
+    if (a.src && a.lq) np = gram<C, NBP, true>(a.src, a.lda, len, P, a.ldv, a.Gp, &Gs, a.stop, s);
+    else if (a.src) np = gram<C, NBP, false>(a.src, a.lda, len, P, a.ldv, a.Gp, &Gs, a.stop, s);
+    else np = gram<C, NBP, false>(P, a.ldv, len, (C*)nullptr, 0, a.Gp, &Gs, a.stop, s);
     ReconArgs<C> r{};
     r.Gp = Gs; r.np = np; r.P = P; r.ldp = a.ldv; r.X = a.X; r.R1 = a.X + NBP * NBP;
     r.V = a.V + off + sub0 * a.ldv; r.ldv = a.ldv; r.Vt = a.Vt + off * a.nb + sub0; r.ldvt = a.nb;
@@ -861,7 +845,7 @@ void subpanel(const ReconPanel<T, C>& a, int64_t off, int64_t sub0, hipStream_t 
         recon_launch<C, NBP, kFirst>(r, s);
         hipLaunchKernelGGL((panel_apply_kernel<C, NBP, true>), dim3((unsigned)((len + 63) / 64)), dim3(256), 0, s, P, a.ldv,
                            (int)len, a.X, r.R1, P, a.ldv, (C*)nullptr, (int64_t)0, a.stop);
-        r.np = gram<C, C, NBP, false>(P, a.ldv, len, (C*)nullptr, 0, a.Gp, &Gs, a.stop, s);
+        r.np = gram<C, NBP, false>(P, a.ldv, len, (C*)nullptr, 0, a.Gp, &Gs, a.stop, s);
         r.Gp = Gs;
         recon_launch<C, NBP, kSecond>(r, s);
     } else {
@@ -883,21 +867,21 @@ size_t recon_scratch_doubles(int64_t rows, int nb)
     return (n + n / 32 + 2) * nt * 256 + 2 * (size_t)nbp * nbp;
 }
 
-template <typename T, typename C> void launch_panel_recon(const ReconPanel<T, C>& in, hipStream_t s)
+template <typename C> void launch_panel_recon(const ReconPanel<C>& in, hipStream_t s)
 {
-    if (in.nb == 32) { subpanel<T, C, 32>(in, 0, 0, s); return; }
-    if (in.nb == 64) { subpanel<T, C, 64>(in, 0, 0, s); return; }
+    if (in.nb == 32) { subpanel<C, 32>(in, 0, 0, s); return; }
+    if (in.nb == 64) { subpanel<C, 64>(in, 0, 0, s); return; }
     // nb = 128: two sub-panels of 64 columns, the second one updated with the first one's reflector in the work panel
-    ReconPanel<T, C> a = in;
-    launch_panel_gather<T, C>(in.A, in.lda, in.arow, in.acol, in.lq != 0, in.len, 128, in.P, in.ldv, s);
+    ReconPanel<C> a = in;
+    launch_panel_gather<C, C>(in.A, in.lda, in.arow, in.acol, in.lq != 0, in.len, 128, in.P, in.ldv, s);
     a.src = nullptr;
-    subpanel<T, C, 64>(a, 0, 0, s);
+    subpanel<C, 64>(a, 0, 0, s);
     C* right = a.P + 64 * a.ldv;
-    int ns = launch_block_wt<C, C>(64, false, right, a.ldv, a.len, 64, a.wp_cols, a.V, a.ldv, a.Wp, a.stop, s);
+    int ns = launch_block_wt<C>(64, false, right, a.ldv, a.len, 64, a.wp_cols, a.V, a.ldv, a.Wp, a.stop, s);
     launch_block_tw<C>(64, a.Wp, ns, 64, a.Tf, a.nb, a.W2, s);
-    launch_block_sub<C, C>(false, right, a.ldv, a.len, 64, 64, a.Vt, a.nb, a.W2, 64, a.stop, s);
-    subpanel<T, C, 64>(a, 64, 64, s);
-    ns = launch_block_wt<C, C>(64, false, a.V + 64 * a.ldv, a.ldv, a.len, 64, a.wp_cols, a.V, a.ldv, a.Wp, a.stop, s);
+    launch_block_sub<C>(false, right, a.ldv, a.len, 64, 64, a.Vt, a.nb, a.W2, 64, a.stop, s);
+    subpanel<C, 64>(a, 64, 64, s);
+    ns = launch_block_wt<C>(64, false, a.V + 64 * a.ldv, a.ldv, a.len, 64, a.wp_cols, a.V, a.ldv, a.Wp, a.stop, s);
     static bool attr_set = false;
     const size_t bytes = 4 * 64 * 66 * sizeof(double);
     if (!attr_set) {
@@ -910,7 +894,7 @@ template <typename T, typename C> void launch_panel_recon(const ReconPanel<T, C>
     hipLaunchKernelGGL((panel_join_kernel<C>), dim3(1), dim3(1024), bytes, s, a.X, a.Tf, (int64_t)a.nb);
 }
 
-template void launch_panel_recon<float, float>(const ReconPanel<float, float>&, hipStream_t);
-template void launch_panel_recon<double, double>(const ReconPanel<double, double>&, hipStream_t);
+template void launch_panel_recon<float>(const ReconPanel<float>&, hipStream_t);
+template void launch_panel_recon<double>(const ReconPanel<double>&, hipStream_t);
 
 }  // namespace svb

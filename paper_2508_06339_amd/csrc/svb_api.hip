@@ -642,14 +642,14 @@ int ge2gb_pipeline(int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* ban
 // Every kLook half-sweeps the host waits for the ones launched kLook earlier and looks whether a panel has been refused:
 // at most 2 kLook half-sweeps are launched in vain, and the stream always holds kLook of them.
 constexpr int kLook = 8;
-template <typename T, typename C>
-int ge2gb_block(int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* band, int64_t ldab,
+template <typename C>
+int ge2gb_block(int64_t rows, int64_t cols, C* A, int64_t lda, int nb, C* band, int64_t ldab,
                 unsigned char* work, const Carve& cv, hipStream_t s)
 {
     int* const stop = reinterpret_cast<int*>(work + cv.off_tree) + kStopInt;
     launch_band_clear<C>(band, ldab, cols, s);
     launch_fill_int(stop, 1, 0, s);
-    ReconPanel<T, C> rp{};
+    ReconPanel<C> rp{};
     rp.A = A; rp.lda = lda; rp.nb = nb;
     rp.P = reinterpret_cast<C*>(work + cv.off_bP);
     rp.V = reinterpret_cast<C*>(work + cv.off_bV);
@@ -681,13 +681,13 @@ int ge2gb_block(int64_t rows, int64_t cols, T* A, int64_t lda, int nb, C* band, 
         rp.arow = row0; rp.acol = col0; rp.src = A + row0 + col0 * lda;
         rp.lq = lq ? 1 : 0; rp.len = len; rp.row0 = row0; rp.col0 = col0; rp.hs = hs;
         prof_begin(SVB_PROF_PANEL, s, 2.0 * (double)len * nb * nb, 0.0);
-        launch_panel_recon<T, C>(rp, s);
+        launch_panel_recon<C>(rp, s);
         prof_end(s);
-        T* Cb = A + (lq ? (k + 1) * nb : k * nb) + (k + 1) * nb * lda;
-        prof_begin(SVB_PROF_UPDATE, s, 4.0 * (double)len * nb * (double)qlen, 3.0 * (double)len * (double)qlen * sizeof(T));
-        const int ns = launch_block_wt<T, C>(nb, lq, Cb, lda, len, qlen, rp.wp_cols, rp.V, rp.ldv, rp.Wp, stop, s);
+        C* Cb = A + (lq ? (k + 1) * nb : k * nb) + (k + 1) * nb * lda;
+        prof_begin(SVB_PROF_UPDATE, s, 4.0 * (double)len * nb * (double)qlen, 3.0 * (double)len * (double)qlen * sizeof(C));
+        const int ns = launch_block_wt<C>(nb, lq, Cb, lda, len, qlen, rp.wp_cols, rp.V, rp.ldv, rp.Wp, stop, s);
         launch_block_tw<C>(nb, rp.Wp, ns, qlen, rp.Tf, nb, rp.W2, s);
-        launch_block_sub<T, C>(lq, Cb, lda, len, qlen, nb, rp.Vt, nb, rp.W2, nb, stop, s);
+        launch_block_sub<C>(lq, Cb, lda, len, qlen, nb, rp.Vt, nb, rp.W2, nb, stop, s);
         prof_end(s);
     }
     if (hipStreamSynchronize(s) != hipSuccess) return -1;
@@ -704,7 +704,7 @@ int ge2gb_typed(svb_dtype dt, int64_t rows, int64_t cols, T* A, int64_t lda, int
     if constexpr (std::is_same_v<T, C>) {   // (16-bit storage comes widened, or goes to the tree)
         // (stage1_block.hip addresses 128 lines of the matrix with 32-bit byte offsets)
         if (cv.block && lda * (int64_t)sizeof(T) < ((int64_t)1 << 32) / 128) {
-            hs0 = ge2gb_block<T, C>(rows, cols, A, lda, nb, band, ldab, work, cv, s);
+            hs0 = ge2gb_block<C>(rows, cols, A, lda, nb, band, ldab, work, cv, s);
             if (hs0 < 0) return SVB_ERR_DEVICE;
         }
     }

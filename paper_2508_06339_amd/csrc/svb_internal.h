@@ -172,9 +172,9 @@ void launch_small_bidiag(const T* A, int64_t lda, int64_t m, int64_t n, C* d, C*
 
 // ---- stage 1 with one block reflector per panel -------------------------------------------------------
 // Cholesky QR and Householder reconstruction of one panel (stage1_recon.hip)
-template <typename T, typename C> struct ReconPanel {
-    const T* A; int64_t lda, arow, acol;   // the matrix and the panel's corner in it
-    const T* src;                          // &A[arow + acol * lda]
+template <typename C> struct ReconPanel {
+    const C* A; int64_t lda, arow, acol;   // the matrix and the panel's corner in it
+    const C* src;                          // &A[arow + acol * lda]
     int lq, nb; int64_t len;               // orientation, tile size, panel length
     C *P, *V, *Vt, *Tf, *Wp, *W2;     // work panel, V in both orders, T, scratch of the updates
     int64_t ldv, wp_cols;                  // leading dimension of P and V (at least len); columns Wp has room for
@@ -183,16 +183,16 @@ template <typename T, typename C> struct ReconPanel {
     int* stop; int hs;                     // set to hs + 1 where a panel is refused
     int* host_stop;                        // the same, in host memory
 };
-template <typename T, typename C> void launch_panel_recon(const ReconPanel<T, C>& a, hipStream_t s);
+template <typename C> void launch_panel_recon(const ReconPanel<C>& a, hipStream_t s);
 size_t recon_scratch_doubles(int64_t rows, int nb);
 // the products of a half-sweep (stage1_block.hip); launch_block_wt returns the number of partial sums
-template <typename T, typename C>
-int launch_block_wt(int nbw, bool lq, const T* Cm, int64_t lda, int64_t len, int64_t nq, int64_t wp_cols, const C* V,
+template <typename C>
+int launch_block_wt(int nbw, bool lq, const C* Cm, int64_t lda, int64_t len, int64_t nq, int64_t wp_cols, const C* V,
                     int64_t ldv, C* Wp, const int* stop, hipStream_t s);
 template <typename C>
 void launch_block_tw(int nbw, const C* Wp, int ns, int64_t nq, const C* T, int64_t ldt, C* W2, hipStream_t s);
-template <typename T, typename C>
-void launch_block_sub(bool lq, T* Cm, int64_t lda, int64_t len, int64_t nq, int K, const C* Vt, int64_t ldvt,
+template <typename C>
+void launch_block_sub(bool lq, C* Cm, int64_t lda, int64_t len, int64_t nq, int K, const C* Vt, int64_t ldvt,
                       const C* W2, int64_t ldw, const int* stop, hipStream_t s);
 int64_t block_wp_cols(int64_t rows, int64_t cols);   // columns of nb elements that Wp needs at most for a rows x cols matrix
 
