@@ -28,18 +28,20 @@
  *   - dtype: SVB_F64, SVB_F32, and the storage-only types SVB_F16 / SVB_BF16
  *     (every sum is formed in f32, as the paper does for half precision,
  *     Section 4.3; the band, the bidiagonal and the result are f32).
- *     svb_svdvals works on an f32 copy in the workspace of up to 8192 rows; of
- *     more, in svb_ge2gb, and where the workspace has no room for it, the transformed matrix is kept in 16 bits and the
- *     trailing update multiplies on the 16-bit matrix instructions with its
- *     f32 operands split into 16-bit terms, which keeps their f32 accuracy.
+ *     svb_svdvals works on an f32 copy in the workspace where the matrix has up
+ *     to 8192 rows (columns, if m < n); with more, in svb_ge2gb, and where the
+ *     workspace has no room for the copy, the transformed matrix is kept in 16
+ *     bits and the trailing update multiplies on the 16-bit matrix instructions
+ *     with its f32 operands split into 16-bit terms, which keeps their f32
+ *     accuracy.
  *   - nb (the paper's TILESIZE): 32, 64 or 128; 0 lets the library choose
  *     (svb_choose_nb).
  *   - Magnitudes: entries may be anywhere in the finite range of the storage
  *     type.  svb_svdvals multiplies the matrix by a power of two first when its
  *     largest magnitude lies outside [2^-40, 2^40] (f32 arithmetic) or
  *     [2^-400, 2^400] (f64), because the kernels form sums of squares without
- *     scaling them, and multiplies the bidiagonal back.  An SVB_F16 matrix of
- *     more than 8192 rows is scaled so that max|a| sqrt(m n) is about 2^11: the
+ *     scaling them, and multiplies the bidiagonal back.  An SVB_F16 matrix
+ *     that is not copied in f32 is scaled so that max|a| sqrt(m n) is about 2^11: the
  *     transformed matrix is written back in f16, where an entry can reach a
  *     column's norm.  The stage-split entry
  *     points svb_ge2gb / svb_gb2bd do not rescale: their inputs must keep
@@ -84,7 +86,7 @@ typedef enum {
  * always 0 (host scratch is allocated internally).  A matrix that is not a
  * whole number of tiles in both directions, or has m < n, is copied into the
  * workspace, which then includes room for the zero-padded copy; a matrix in
- * 16-bit storage of more than 256 and at most 8192 rows (columns, if m < n) is copied in f32.
+ * 16-bit storage larger than 256 x 256 is copied in f32 up to 8192 rows.
  * svb_ge2gb uses neither that copy nor the block reflectors of svb_svdvals'
  * stage 1 and asks only for what the tree of domain QRs needs; svb_svdvals with
  * a workspace that has room for that tree only uses the tree.
@@ -94,7 +96,7 @@ int svb_workspace_bytes(svb_dtype dt, int64_t m, int64_t n, int nb,
 
 /*
  * The tile size that nb = 0 selects for an m x n matrix of type dt (the paper
- * tunes TILESIZE per matrix size and device, Section 4, Table 3), within 4 %
+ * tunes TILESIZE per matrix size and device, Section 4, Table 3), within 5 %
  * of the fastest on MI355X, k = min(m, n): f32 arithmetic (SVB_F32, SVB_F16, SVB_BF16): 32 for
  * k < 1024, 64 up to 26624, 128 beyond; SVB_F64: 32 up to 2560, 64 beyond.
  * Returns 0 for invalid arguments.
@@ -127,8 +129,9 @@ int svb_choose_nb(svb_dtype dt, int64_t m, int64_t n);
  *   work_dev   [dev]  scratch of at least svb_workspace_bytes(...) bytes,
  *                     256-byte aligned.
  * Blocking: returns after the result has been copied to S_out_host (one
- * stream synchronisation, and one between stage 1 and stage 2 where the
- * matrix is larger than 256 x 256).  With the environment variable SVB_STAGE3=host the
+ * stream synchronisation; where stage 1 uses block reflectors it also waits
+ * for an event every few half-sweeps, and for the stream behind the last block
+ * reflector, before the tree takes the rest of the matrix).  With the environment variable SVB_STAGE3=host the
  * bidiagonal is solved on the host (svb_bdsvals) instead of the device.
  */
 int svb_svdvals(svb_dtype dt, int64_t m, int64_t n, void* A_dev, int64_t lda,

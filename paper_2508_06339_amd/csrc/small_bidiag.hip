@@ -11,7 +11,9 @@
 // Bound by instruction issue at the larger sizes (two waves a SIMD; the multiply-adds are two thirds of it in f32 at 256)
 // and by the chain of the two reflectors at the small ones, about 2000 cycles a column.  The columns go in phases of 64,
 // in which the finished row and column slots are left out by compilation; a wave's elements are taken a column at a time
-// where they lie in LDS (four columns at a time, 32 more registers, were spilled: f64 256 1.48 ms a call against 1.18).
+// where they lie in LDS (four columns at a time, 32 more registers, were spilled: f64 256 1.48 ms a call against 1.15).
+// In f64 with four row slots the registers do not suffice all the same: of the two runs below 53 (129 to 192 columns) and 136
+// (193 to 256) registers are spilled; every other form keeps everything.
 // H = I - g u u^T with u not normalised.  The matrix is scaled by a power of two so that its largest entry is in [0.5, 1),
 // and the bidiagonal scaled back.  A line whose sum of squares is so small that subnormal squares can be a part of it
 // (SmallRange::kLow) has to be moved up by a power of two first, or its reflector is not orthogonal, and it also hits

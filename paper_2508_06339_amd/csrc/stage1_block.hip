@@ -386,9 +386,13 @@ void wt_launch(bool lq, const C* Cm, int64_t lda, int len, int nq, const C* V, i
 
 // how the contraction over p is split: enough workgroups for the chip, at least 64 elements each, and
 // partial sums within the workspace (block_wp_cols).  1024 workgroups where the size allows: two to four fit on
-// a compute unit, and with 512 they all begin and end together (f32 32768, nb = 128: 1208 ms a call with 512, 1198
-// with 768, 1177 with 1024, as with 2048 or 3072; f64 16384, nb = 128: 509, 507, 502; f32 16384, nb = 64: 232, 229, 227;
-// no difference at 4096 and 8192)
+// a compute unit, and with 512 they all begin and end together (ms a call with 512 and 1024: f32 32768, nb = 128 1209, 1172;
+// 16384, nb = 64 231, 225.5; f64 16384, nb = 128 510.5, 504).  Room for four times the longer side's columns makes 1024 the
+// most that the large sizes can have, and eight and four ranges, about 500 workgroups, at the first sweeps of order 4096 and
+// 8192.  With four times that room 1024 are reached there too, and are slower (4096 24.0 against 23.85, 8192 61.2 against 60.5:
+// more partial sums, shorter ranges); 2048 at 32768 would be 0.9 % faster (1162), for 192 MiB.
+// The order in which W is summed is no matter for the error: folding the accumulators every 512 terms left it where it is
+// (mean over random matrices, f32: 8192 1.13e-7, folded 1.11e-7; 32768 1.25e-7, 1.29e-7; the tree of domain QRs 1.17e-7, 1.26e-7).
 constexpr int64_t kMaxRanges = 64;   // (block_tw_kernel adds them up one after the other)
 static int64_t max_ranges(int64_t len) { return std::max<int64_t>(1, std::min(len / 64, kMaxRanges)); }
 int64_t block_wp_cols(int64_t rows, int64_t cols)

@@ -31,10 +31,11 @@ bool nb_ok(int nb) { return nb == 32 || nb == 64 || nb == 128; }
 // hardware, Section 4 and Table 3).  From timings of svb_svdvals on MI355X at orders 1024 .. 32768:
 // small tiles shorten the panel chain and stage 2, large tiles raise the arithmetic intensity of
 // the trailing update, which only pays once the update dominates.  In f32 arithmetic nb = 64 from order
-// 1024 (16384: 232 ms against 257 at nb = 128) and nb = 128 beyond 26624 (28672: 894 ms against 929); in f64 nb = 32 up
-// to 2560 (2048: 15.3 ms against 16.3 at nb = 64) and nb = 64 beyond (8192: 100 against 119; 16384: 411 ms
-// against 511 at nb = 128).  Between 1024 and 4096 the two smaller sizes lie within 5 % of each other, square matrices
-// preferring 32 and tall ones 64.
+// 1024 (16384: 225 ms against 252 at nb = 128) and nb = 128 beyond 26624 (28672: 851 ms against 895; at 24576 581 against
+// 588); in f64 nb = 32 up to 2560 (2048: 15.3 ms against 16.3 at nb = 64) and nb = 64 beyond (8192: 100 against 117;
+// 16384: 398 ms against 502 at nb = 128).  Between 1024 and 4096 the two smaller sizes lie within 5 % of each other, square
+// matrices preferring 32 (f32 1024 5.05 against 5.22, f64 3072 24.6 against 25.8) and tall ones 64 (f32 20000 x 1000 6.73
+// against 6.52): the lines lie where the tree of domain QRs had them.
 int choose_nb(svb_dtype dt, int64_t m, int64_t n)
 {
     const int64_t k = m < n ? m : n;
@@ -68,8 +69,11 @@ Shape shape_of(int64_t m, int64_t n, int nb)
 // 16-bit storage: svb_svdvals works on an f32 copy up to this many rows.  With one block reflector per panel an entry
 // changes by a little in every half-sweep, and rounded to 16 bits each time those changes are lost (n = 4096, values
 // spread evenly: error 2.0e-4 against 6.9e-5 with the tree, whose domains change fewer entries by more; 3.0e-7 on the
-// copy).  Beyond, the tree's update on the 16-bit matrix instructions is the faster one: n = 8192 60 ms against 73,
-// 16384 231 against 240 at nb = 64 and 307 against 259 at nb = 128 (f16).
+// copy).  The line is one of memory, not of time: the copy is twice the matrix, 256 MiB at 8192 x 8192, 1 GiB at 16384 and
+// 4 GiB at 32768 (the rest of the workspace 24, 47 and 182 MiB), and beyond the tree works on the matrix in place.  In time
+// the copy is ahead of the tree's 16-bit matrix instructions nearly everywhere (f16 / bf16, tree then copy, ms: 9000
+// 85 / 92, 72; 16384 at nb = 64 241 / 275, 228, at nb = 128 259 / 306, 254; 20000 x 500 4.3 / 4.5, 3.2; 32768 1102 / 1435,
+// 1175).
 constexpr int64_t kWidenRows = 8192;
 bool widens(svb_dtype dt, const Shape& sh)
 {
