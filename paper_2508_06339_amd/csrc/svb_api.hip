@@ -397,15 +397,20 @@ struct Lookahead {
             return false;
         for (int i = 0; i < 4; ++i)
             if (hipEventCreate(&stage[i]) != hipSuccess) return false;
-        for (int i = 0; i < 2; ++i)
-            if (hipEventCreateWithFlags(&look[i], hipEventDisableTiming) != hipSuccess) return false;
-        if (hipHostMalloc(reinterpret_cast<void**>(&stop), sizeof(int), hipHostMallocCoherent) != hipSuccess ||
-            hipHostGetDevicePointer(reinterpret_cast<void**>(&stop_dev), stop, 0) != hipSuccess)
-            return false;
         ok = true;
         // released while the HIP runtime is still up (handlers registered later run earlier)
         std::atexit([] { g_la_release(); });
         return true;
+    }
+    // what ge2gb_block needs besides (memory cannot be allocated while a stream is being captured, and svb_ge2gb, which may be,
+    // does without it)
+    bool init_block()
+    {
+        if (stop_dev) return true;
+        for (int i = 0; i < 2; ++i)
+            if (!look[i] && hipEventCreateWithFlags(&look[i], hipEventDisableTiming) != hipSuccess) return false;
+        if (!stop && hipHostMalloc(reinterpret_cast<void**>(&stop), sizeof(int), hipHostMallocCoherent) != hipSuccess) return false;
+        return hipHostGetDevicePointer(reinterpret_cast<void**>(&stop_dev), stop, 0) == hipSuccess;
     }
     void release()
     {
@@ -421,8 +426,9 @@ struct Lookahead {
         (void)hipEventDestroy(join);
         (void)hipEventDestroy(join_u);
         for (int i = 0; i < 4; ++i) (void)hipEventDestroy(stage[i]);
-        for (int i = 0; i < 2; ++i) (void)hipEventDestroy(look[i]);
-        (void)hipHostFree(stop);
+        for (int i = 0; i < 2; ++i)
+            if (look[i]) (void)hipEventDestroy(look[i]);
+        if (stop) (void)hipHostFree(stop);
         (void)hipStreamDestroy(u);
         (void)hipStreamDestroy(m);
     }
@@ -650,6 +656,7 @@ template <typename C>
 int ge2gb_block(int64_t rows, int64_t cols, C* A, int64_t lda, int nb, C* band, int64_t ldab,
                 unsigned char* work, const Carve& cv, hipStream_t s)
 {
+    if (!g_la.init_block()) return -1;
     int* const stop = reinterpret_cast<int*>(work + cv.off_tree) + kStopInt;
     launch_band_clear<C>(band, ldab, cols, s);
     launch_fill_int(stop, 1, 0, s);
