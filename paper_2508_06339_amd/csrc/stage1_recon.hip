@@ -412,6 +412,10 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
         double s[NT];
 #pragma unroll
         for (int b = 0; b < NT; ++b) s[b] = 0;
+        if (MODE == kSecond && !share && r == c) {
+#pragma unroll
+            for (int bj = 0; bj < NBK; ++bj) s[ublk(bj, bj)] = -1.0;
+        }
         for (int z = share; z < a.np; z += NS)
 #pragma unroll
             for (int b = 0; b < NT; ++b) s[b] += a.Gp[((int64_t)z * NT + b) * 256 + el];
@@ -431,7 +435,7 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
                     const int at = ublk(bi, bj) * 256 + el;
                     const double v = s[ublk(bi, bj)] + L[at] + (NS == 3 ? B[at] : 0.0);
                     blk(G, bi, bj)[r * LD + c] = v;
-                    if (bi == bj && r == c) g0[bi * 16 + r] = v;
+                    if (bi == bj && r == c) g0[bi * 16 + r] = MODE == kSecond ? v + 1.0 : v;
                 }
         }
         lds_barrier();
@@ -457,7 +461,7 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
         if (lane == 0) sh_nz = nz;
         if (lane < NBP && d == 0.0) {
             g0[lane] = 1.0;
-            G[lane * LD + lane] = 1.0;
+            G[lane * LD + lane] = MODE == kSecond ? 0.0 : 1.0;
         }
     }
     d4 rr = zero4();   // second pass: a block of R' R in each of the waves from 2 on
@@ -467,15 +471,17 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
         ri = wave - 2 - rj * (rj + 1) / 2;
     }
     if constexpr (MODE == kSecond) {
-        // N: E's upper triangle with half its diagonal; I + N in the place of G, (I - N)^T in E
+        // N: E's upper triangle with half its diagonal; I + N in the place of G, N^T in E.  (N is about 2^-53: in I + N the
+        // most of it is lost, and more of it above 1 than below, where numbers are twice as close.  With the sum of squares
+        // formed around 1 and T from U (I - N), all singular values came out smaller by 1e-16 of themselves on average.)
         lds_barrier();
         for (int idx = tid; idx < NBP * NBP; idx += NTH) {
             const int c = idx % NBP, r = idx / NBP;
-            const double one = r == c ? 1.0 : 0.0, dev = r <= c ? G[r * LD + c] - one : 0.0;
+            const double dev = r <= c ? G[r * LD + c] : 0.0;
             if (!(fabs(dev) <= kMaxE)) sh_bad = 1;   // (a NaN as well)
             const double v = r == c ? 0.5 * dev : dev;
-            G[r * LD + c] = one + v;
-            if (r <= c) E[c * LD + r] = one - v;
+            G[r * LD + c] = r == c ? 1.0 + v : v;
+            if (r <= c) E[c * LD + r] = v;
         }
     }
     lds_barrier();
@@ -509,8 +515,10 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
             if (!(f <= kMaxInv) && lane == 0) sh_bad = 1;
         }
         if (lu && wave == 1) lu16(blk(B, kb, kb), blk(G, kb, kb), LD, Lkk, Ukk, LDD, S + kb * 16, i, g);
-        if (MODE == kSecond && kb == 0 && wave >= 2 && wave < NT + 2)   // R' R, a block a wave
-            for (int k = ri; k <= rj; ++k) rr = mm16(rr, blk(G, ri, k), LD, 1, a.R1 + k * 16 * NBP + rj * 16, NBP, 1, i, g);
+        if (MODE == kSecond && kb == 0 && wave >= 2 && wave < NT + 2) {   // R' R = R + N R, a block a wave
+            rr = get16(a.R1 + ri * 16 * NBP + rj * 16, NBP, i, g);
+            for (int k = ri; k <= rj; ++k) rr = mm16(rr, blk(E, k, ri), 1, LD, a.R1 + k * 16 * NBP + rj * 16, NBP, 1, i, g);
+        }
         lds_barrier();
         if (chol && wave >= 2 && wave < NBK + 1) {
             const int j0 = wave - 2, j = j0 + (j0 >= t ? 1 : 0);
@@ -597,9 +605,15 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
         return;
     }
     lds_barrier();
-    // ---- T = -(U R^-1) S L^-T, a block a wave
+    // ---- T = -(U R^-1) S L^-T, a block a wave; in the second pass U R'^-1 = U - U N
     static_assert(NT <= NWV, "a block a wave");
     d4 ur = zero4();
+    if (MODE == kSecond && wave < NT) {
+        ur = get16(blk(B, bi, bj), LD, i, g);
+        if (bi == bj)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) ur[r] = 4 * r + g <= i ? ur[r] : 0.0;
+    }
     if (wave < NT)
         for (int k = bi; k <= bj; ++k)
 #pragma unroll
@@ -607,6 +621,7 @@ __global__ __launch_bounds__(kReconThreads<NBP>) void panel_recon_kernel(ReconAr
                 const int c = 4 * s + g;
                 double u = blk(B, bi, k)[i * LD + c];
                 if (k == bi) u = i <= c ? u : 0.0;
+                if (MODE == kSecond) u = -u;
                 ur = F64::mma(u, blk(E, bj, k)[i * LD + c], ur);
             }
     // (X, and V's top block, unit lower triangular, in both orders, while U is still in the array with L)
