@@ -351,8 +351,9 @@ template <int NBP> struct ReconGeom {
 // its factorisation.  The LU factorisation follows the Cholesky factorisation one block behind, by another wave: what
 // stands on the chain is one Cholesky block and the LU blocks.  Bound by latency: 62k cycles
 // (28 us) at NBP = 64, of which each LU block 6900 and each Cholesky block 3600; 107k with one row at a time, Q formed,
-// the two factorisations one after the other and full barriers.  At NBP = 64 nine registers a lane are spilled (three waves a
-// SIMD leave 168): the panel's top rows, fetched with the partial sums and needed behind them.
+// the two factorisations one after the other and full barriers.  At NBP = 64 nine (f32) and fourteen (f64, second
+// pass) registers a lane are spilled (three waves a SIMD leave 168): the panel's top rows, fetched with the partial sums and
+// needed behind them.
 enum { kFull, kFirst, kSecond };
 template <typename C> struct ReconArgs {
     const double* Gp; int np;        // partial sums of G
